@@ -142,7 +142,9 @@ typedef struct {
    * batches). 1 runs every batch on its own. */
   int32_t window_batches;
   /* Value written into padding rows (and padding tokens) before the forward
-   * pass. 0 in production; NaN shows that padding never reaches an output. */
+   * pass, where the padded batch is assembled (a first layer that reads the
+   * requests' rows in place takes padding rows as zeros). 0 in production;
+   * NaN shows that padding never reaches an output. */
   float pad_value;
   /* 1: time every kernel launch with HIP events (rb_sched_kernel_stats);
    * 2: the same with cold caches: before each timed launch the scheduler

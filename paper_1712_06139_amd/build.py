@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librbatch.so")
-SOURCES = ["kernels.hip", "runtime.cpp"]
+SOURCES = ["gemm.hip", "gemm_f32_split.hip", "kernels.hip", "runtime.cpp"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -31,14 +31,19 @@ CFLAGS = [
 def build(verbose: bool = False) -> str:
     tmp = tempfile.mkdtemp(prefix="rbatch_build_")
     try:
-        objs = []
-        for src in SOURCES:
+        objs, jobs = [], []
+        for src in SOURCES:  # all at once: the GEMM templates take minutes
             obj = os.path.join(tmp, src + ".o")
             cmd = [HIPCC, *CFLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
             if verbose:
                 print(" ".join(cmd), flush=True)
-            subprocess.run(cmd, check=True, stderr=None if verbose else subprocess.DEVNULL)
+            jobs.append((cmd, subprocess.Popen(cmd, stderr=None if verbose else subprocess.DEVNULL)))
             objs.append(obj)
+        for cmd, job in jobs:
+            job.wait()
+        for cmd, job in jobs:
+            if job.returncode:
+                raise subprocess.CalledProcessError(job.returncode, cmd)
         out_tmp = LIB + ".tmp"
         cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", out_tmp, *objs, "-lpthread"]
         subprocess.run(cmd, check=True)

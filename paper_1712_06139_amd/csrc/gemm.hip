@@ -1,0 +1,691 @@
+// Dense layers on matrix cores: bf16 operands (a model's layers, and a last
+// hidden layer fused with its head), and fp32 operands on the fp32 MFMA (the
+// C ABI's fp32 entry points; an fp32 model's layers run in gemm_f32_split.hip).
+#include "device.h"
+
+namespace {
+
+// Y = act(X W^T + b): X [M, K] and W [N, K] of element type TI (bf16 or
+// fp32), K contiguous; fp32 accumulation with v_mfma_f32_32x32x16_bf16 or
+// v_mfma_f32_32x32x2f32.
+//
+// Workgroup tile BM x BN, k-step of RB bytes per row (64 or 128: 32 or 64
+// bf16, 16 or 32 fp32), NT/64 waves each owning a WM x WN sub-tile
+// ((WM/32) x (WN/32) accumulators). Operand tiles go straight from global
+// memory into a ring of S >= 2 LDS stages (global_load_lds: each wave load
+// instruction fills 1 KB of consecutive LDS rows; no register staging).
+// K-step kt reads stage kt % S while the stage of k-step kt - 1 is refilled
+// with k-step kt - 1 + S, its loads spread one every few MFMAs over the step
+// (over its first half when S = 2, where that refill is the next k-step):
+// issued back to back they stall the wave on the texture path with no MFMA in
+// flight. A sub-step covers 32 bytes of every row (16 bf16 or 8 fp32 k values)
+// and its MFMAs have the next sub-step's fragment reads between them. In the
+// last sub-step, after half of its MFMAs (three quarters with S = 2), the wave
+// waits for its loads of the next k-step and for its LDS reads, and all waves
+// meet at one barrier: the next stage has landed and nobody reads the current
+// one again. The rest of the sub-step then runs with the next k-step's first
+// fragment reads between the MFMAs. The order of MFMAs, LDS reads and loads
+// within a step is fixed with scheduling barriers.
+//
+// A fragment is 16 bytes of one row: lane l holds row l % 32 and chunk
+// 2 kk + l / 32 of sub-step kk. bf16: one 32x32x16 MFMA per accumulator and
+// sub-step. fp32: chunk c holds k = 4c .. 4c + 3, and MFMA t (t = 0..3) of the
+// sub-step takes dword t, so it adds the products of k = 8 kk + t (lanes
+// 0..31) and k = 8 kk + 4 + t (lanes 32..63); the MFMAs of a sub-step run
+// t-major over the accumulators, so two MFMAs into one accumulator are NM
+// instructions apart.
+//
+// LDS rows hold RB/16 16-byte chunks; chunk c of row r sits at chunk
+// c ^ ((r / (16 / (RB/16))) % (RB/16)), so the 16 rows one fragment read
+// serves per LDS cycle hit 16 distinct bank groups (64 banks).
+//
+// Every tile shape, k-step, stage count and tile order accumulates each output
+// element in the same k order with the same instructions, so results do not
+// depend on them, nor on which rows share a tile.
+//
+// skip_rows (sequence layout, slot e owning rows [e skip_T, (e + 1) skip_T),
+// skip_T a multiple of BM): a workgroup whose rows are all padding tokens
+// (at or past its slot's length, or in a padding slot) returns at once.
+constexpr int G16_KALIGN = 64;  // K multiple the bf16 entry point accepts
+constexpr int G32_KALIGN = 32;  // K multiple the fp32 entry point accepts
+constexpr int G32_BM = 64;      // fp32 tile height (the padding-token skip granularity)
+
+template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, bool OUT_F32,
+          bool PERSIST, int HEAD = -1>
+__device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, const TI* __restrict__ W, int ldw,
+                                          const float* __restrict__ bias, void* __restrict__ Y, int ldy, int M,
+                                          int N, int K, const rb_k_row* __restrict__ skip_rows, int skip_T,
+                                          const HeadArgs ha = HeadArgs{}, const OutMap om = OutMap{}) {
+  constexpr bool F32 = sizeof(TI) == 4;
+  constexpr int ES = sizeof(TI);  // bytes per element
+  constexpr int BK = RB / ES;     // k values per k-step
+  constexpr int NW = NT / 64;
+  static_assert((BM / WM) * (BN / WN) == NW, "one wave per sub-tile");
+  static_assert(RB == 64 || RB == 128, "k-step of 64 or 128 bytes per row");
+  static_assert(S >= 2 && S <= 4, "2..4 stages");
+  constexpr int CPR = RB / 16;   // 16-byte chunks per LDS row
+  constexpr int RPI = 64 / CPR;  // rows filled per wave load instruction
+  constexpr int SWZ = 16 / CPR;  // rows sharing one swizzle pattern
+  constexpr int EPC = 16 / ES;   // elements per chunk
+  constexpr int TM = WM / 32, TN = WN / 32;
+  static_assert(TM % 2 == 0 || F32, "the last sub-step splits the A fragments in halves");
+  constexpr int SA = BM / RPI / NW, SB = BN / RPI / NW;  // load instructions per wave per stage
+  static_assert(SA * NW * RPI == BM && SB * NW * RPI == BN, "loads cover the tile");
+  constexpr int OPS = SA + SB;
+  constexpr int KK = RB / 32;    // MFMA sub-steps per k-step
+  constexpr int NM = TM * TN;    // accumulators
+  constexpr int MPF = F32 ? 4 : 1;  // MFMAs per accumulator and sub-step
+  constexpr int NU = NM * MPF;   // MFMAs per sub-step
+  constexpr int NR = TM + TN;    // fragment reads per sub-step
+  // the last sub-step's MFMAs before the barrier: half of them, three quarters
+  // with two stages (more time for the loads of the next k-step to land)
+  constexpr int UB = S == 2 ? NU * 3 / 4 : NU / 2;
+  constexpr int PRE = (KK - 1) * NU + UB;  // MFMAs of a step before its barrier
+  // MFMA slots the refill loads are spread over: with two stages the stage
+  // refilled during a step is the one the next step reads, so its loads go in
+  // the first half of the step to land before the barrier
+  constexpr int LPOS = S == 2 ? PRE / 2 : PRE;
+  // fragment read slot -> fragment (A fragments q < TM, then B). With two
+  // stages (bf16) in the order the next sub-step's MFMAs consume them (A0, B0
+  // .. B(TN-1), A1 .. A(TM-1)), so the fragment needed first is read first;
+  // otherwise A0 .. A(TM-1), B0 .. B(TN-1).
+  auto qmap = [](auto sc) {
+    constexpr int q = decltype(sc)::value;
+    if constexpr (S != 2 || F32 || q == 0)
+      return ic<q>{};
+    else if constexpr (q <= TN)
+      return ic<TM + q - 1>{};
+    else
+      return ic<q - TN>{};
+  };
+  __shared__ u32x4_t sA[S][BM * CPR];
+  __shared__ u32x4_t sB[S][BN * CPR];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wid / (BN / WN), wn = wid % (BN / WN);
+  const int tiles_n = N / BN;
+  const int ntiles = ((M + BM - 1) / BM) * tiles_n;
+  // v: this workgroup's index in the tile sequence (blockIdx.x, then + gridDim.x
+  // per tile when persistent; gridDim.x is a multiple of 8, so v % 8 stays the
+  // XCD the workgroup runs on)
+  int v = blockIdx.x;
+  auto tile_origin = [&](int vv, int& m0_, int& n0_) {
+    const int tile = ORDER ? xcd_tile(vv, ntiles) : vv;
+    const int bm = tile / tiles_n;
+    m0_ = bm * BM;
+    n0_ = (tile - bm * tiles_n) * BN;
+  };
+  int m0, n0;
+  tile_origin(v, m0, n0);
+  if (skip_rows) {  // uniform per workgroup
+    const int e = m0 / skip_T;
+    const rb_k_row rw = skip_rows[e];
+    if (rw.src < 0 || m0 - e * skip_T >= rw.aux) return;
+  }
+
+  // lane l of a load instruction fills LDS row l / CPR (of its RPI), chunk l % CPR
+  const int lr = lane / CPR, lc = lane % CPR;
+  // byte offsets from the tile's first row (buffer resources based there; the
+  // k-step's byte offset goes in the scalar offset)
+  auto a_offsets = [&](int m0_, uint32_t (&va_)[SA]) {
+#pragma unroll
+    for (int i = 0; i < SA; ++i) {
+      const int row = (wid * SA + i) * RPI + lr;
+      const int ra = min(row, M - 1 - m0_);  // rows past M are computed on a copy and never stored
+      va_[i] = (uint32_t)(ra * ldx + (lc ^ ((row / SWZ) % CPR)) * EPC) * (uint32_t)ES;
+    }
+  };
+  i32x4_t rA = buffer_rsrc(X + (int64_t)m0 * ldx), rB = buffer_rsrc(W + (int64_t)n0 * ldw);
+  uint32_t va[SA], vb[SB];
+  a_offsets(m0, va);
+#pragma unroll
+  for (int i = 0; i < SB; ++i) {
+    const int row = (wid * SB + i) * RPI + lr;
+    vb[i] = (uint32_t)(row * ldw + (lc ^ ((row / SWZ) % CPR)) * EPC) * (uint32_t)ES;
+  }
+  // persistent: the next tile's origin, resources and A offsets (a copy of the
+  // current tile's when there is none)
+  int m0n = m0, n0n = n0;
+  bool has_next = false;
+  i32x4_t rAn = rA, rBn = rB;
+  uint32_t van[SA];
+#pragma unroll
+  for (int i = 0; i < SA; ++i) van[i] = va[i];
+  auto next_tile = [&]() {
+    has_next = v + (int)gridDim.x < ntiles;
+    if (has_next) {
+      tile_origin(v + (int)gridDim.x, m0n, n0n);
+      rAn = buffer_rsrc(X + (int64_t)m0n * ldx);
+      rBn = buffer_rsrc(W + (int64_t)n0n * ldw);
+      a_offsets(m0n, van);
+    } else {
+      m0n = m0;
+      n0n = n0;
+      rAn = rA;
+      rBn = rB;
+#pragma unroll
+      for (int i = 0; i < SA; ++i) van[i] = va[i];
+    }
+  };
+  if constexpr (PERSIST) next_tile();
+
+  floatx16_t acc[TM][TN];
+  auto zero_acc = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  };
+  zero_acc();
+
+  const int nk = K / BK;
+  // load instruction o (A rows for o < SA, then B rows) of k-step kt into
+  // stage st. K-steps past the end reload the last one into a stage that is
+  // never read again, so every step runs the same branch-free code; when
+  // persistent, they are the next tile's first k-steps instead (the load stream
+  // runs on across tiles, so the next tile's operands are in flight during this
+  // tile's last steps and epilogue).
+  auto issue_one = [&](int kt, auto stc, auto oc) {
+    constexpr int st = decltype(stc)::value, o = decltype(oc)::value;
+    if constexpr (PERSIST) {
+      const bool nx = kt >= nk;  // uniform
+      const uint32_t kb = (uint32_t)((nx ? (has_next ? kt - nk : nk - 1) : kt) * RB);
+      if constexpr (o < SA)
+        buffer_to_lds(nx ? rAn : rA, nx ? van[o] : va[o], kb, lds_addr(&sA[st][0]) + (wid * SA + o) * 1024);
+      else
+        buffer_to_lds(nx ? rBn : rB, vb[o - SA], kb, lds_addr(&sB[st][0]) + (wid * SB + o - SA) * 1024);
+    } else {
+      const uint32_t kb = (uint32_t)(min(kt, nk - 1) * RB);
+      if constexpr (o < SA)
+        buffer_to_lds(rA, va[o], kb, lds_addr(&sA[st][0]) + (wid * SA + o) * 1024);
+      else
+        buffer_to_lds(rB, vb[o - SA], kb, lds_addr(&sB[st][0]) + (wid * SB + o - SA) * 1024);
+    }
+  };
+  u32x4_t fa[2][TM], fb[2][TN];
+  // fragment read q (A fragment q for q < TM, then B) of sub-step kk of stage st
+  auto read_one = [&](auto stc, int kk, auto qc, auto bufc) {
+    constexpr int st = decltype(stc)::value, q = decltype(qc)::value, bf = decltype(bufc)::value;
+    // lane l holds row l % 32, chunk 2 kk + l / 32
+    const int ch = kk * 2 + (lane >> 5);
+    if constexpr (q < TM) {
+      const int r = wm * WM + q * 32 + (lane & 31);
+      fa[bf][q] = sA[st][r * CPR + (ch ^ ((r / SWZ) % CPR))];
+    } else {
+      const int r = wn * WN + (q - TM) * 32 + (lane & 31);
+      fb[bf][q - TM] = sB[st][r * CPR + (ch ^ ((r / SWZ) % CPR))];
+    }
+  };
+  // k-step kt: stage stc, next stage nstc, refilled stage rstc (k-step kt - 1's)
+  auto step = [&](int kt, auto stc, auto nstc, auto rstc) {
+    static_for<KK>([&](auto kkc) {
+      constexpr int kk = decltype(kkc)::value;
+      constexpr bool last = kk == KK - 1;
+      constexpr int cur = kk & 1, nxt = (kk + 1) & 1;
+      static_for<NU>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        constexpr int m = u % NM, t = u / NM;
+        if constexpr (last && u == UB) {
+          wait_vmcnt_lds<(S - 2) * OPS>();
+          lds_barrier();
+        }
+        if constexpr (F32)
+          acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+              __uint_as_float(fa[cur][m / TN][t]), __uint_as_float(fb[cur][m % TN][t]), acc[m / TN][m % TN], 0, 0, 0);
+        else
+          acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8_t, fa[cur][m / TN]), __builtin_bit_cast(bf16x8_t, fb[cur][m % TN]),
+              acc[m / TN][m % TN], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<NR>([&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          if constexpr (!last) {
+            if constexpr (q * NU / NR == u) read_one(stc, kk + 1, qmap(qc), ic<nxt>{});
+          } else if constexpr (u >= UB) {
+            if constexpr (UB + q * (NU - UB) / NR == u) read_one(nstc, 0, qmap(qc), ic<0>{});
+          }
+        });
+        constexpr int pos = kk * NU + u;
+        static_for<OPS>([&](auto oc) {
+          constexpr int o = decltype(oc)::value;
+          if constexpr (o * LPOS / OPS == pos) issue_one(kt - 1 + S, rstc, oc);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  };
+  static_for<S - 1>([&](auto sc) { static_for<OPS>([&](auto oc) { issue_one(decltype(sc)::value, sc, oc); }); });
+  wait_vmcnt_lds<(S - 2) * OPS>();
+  lds_barrier();
+  static_for<NR>([&](auto qc) { read_one(ic<0>{}, 0, qmap(qc), ic<0>{}); });
+  auto group = [&](int kt) {  // S k-steps from a multiple of S
+    step(kt, ic<0>{}, ic<1>{}, ic<S - 1>{});
+    step(kt + 1, ic<1>{}, ic<2 % S>{}, ic<0>{});
+    if constexpr (S > 2) step(kt + 2, ic<2 % S>{}, ic<3 % S>{}, ic<1>{});
+    if constexpr (S > 3) step(kt + 3, ic<3>{}, ic<0>{}, ic<2>{});
+  };
+
+  // accumulator (i, j) register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4,
+  // column l%32 of its 32 x 32 block. Bias and activation are applied per
+  // column; then each group of four registers (four consecutive rows) is
+  // transposed across the four lanes of a quad, so that a lane holds four
+  // consecutive columns of one row and stores them at once (8 bytes bf16, 16
+  // bytes fp32) instead of four single elements.
+  auto epilogue = [&]() {
+  // with an output row map: the output offsets of this lane's rows, loaded
+  // all at once before any is needed
+  const bool mapped = OUT_F32 && om.rows != nullptr;  // uniform
+  int64_t ro[TM][4];
+  if (mapped) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int r = m0 + wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
+        ro[i][g] = r < M ? om.rows[r].out : -1;
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const float bb = bias[n0 + wn * WN + j * 32 + (lane & 31)];
+    const int colq = n0 + wn * WN + j * 32 + (lane & 28);  // first column of this lane's quad
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = act_fn<ACT>(acc[i][j][4 * g + k] + bb);
+        quad_transpose4(q, lane);
+        const int row = m0 + wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
+        // streaming (nontemporal) stores: the whole chip writes its tiles'
+        // outputs at about the same time, and these drain faster than
+        // stores that allocate in L2
+        if constexpr (OUT_F32) {
+          if (mapped) {
+            const int64_t o = ro[i][g];
+            if (o >= 0) {
+              float* dst = om.out + o + colq;
+              if (colq + 3 < om.d_out && ((uintptr_t)dst & 15) == 0) {
+                const f32x4_t v = {q[0], q[1], q[2], q[3]};
+                __builtin_nontemporal_store(v, (f32x4_t*)dst);
+              } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                  if (colq + k < om.d_out) dst[k] = q[k];
+              }
+            }
+            continue;
+          }
+        }
+        if (row < M) {
+          if (OUT_F32) {
+            const f32x4_t o = {q[0], q[1], q[2], q[3]};
+            __builtin_nontemporal_store(o, (f32x4_t*)((float*)Y + (int64_t)row * ldy + colq));
+          } else {
+            const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
+            __builtin_nontemporal_store(o, (u32x2_t*)((bf16_t*)Y + (int64_t)row * ldy + colq));
+          }
+        }
+      }
+  }
+  };
+
+  // The head instead of the store: the tile's outputs, rounded to bf16 exactly
+  // as the store would round them, into LDS rows of HLD bytes (over the
+  // operand stages, once every wave is done with them); then 16 lanes per row
+  // sum w . y in the order of k_head (lane l: elements 8 l .. 8 l + 7 of every
+  // 128, then a 16-lane butterfly), so the results equal the separate layer and
+  // head bit for bit.
+  auto head_epilogue = [&]() {
+    if constexpr (HEAD >= 0) {
+    constexpr int RPP = NT / 16;  // rows per pass of the head (16 lanes each)
+    static_assert(!F32 && !OUT_F32 && BN == 256 && BM % RPP == 0, "bf16 layer of 256 outputs");
+    constexpr int HLD = BN * 2 + 16;
+    static_assert(BM * HLD <= S * BN * CPR * 16, "the output tile fits over the B stages");
+    unsigned char* hb = (unsigned char*)&sB[0][0];
+    // the output offsets of this thread's rows and its head weights, loaded
+    // before the tile goes to LDS so that their latency overlaps it
+    const int l = tid & 15;
+    int64_t outs[BM / RPP];
+#pragma unroll
+    for (int p = 0; p < BM / RPP; ++p) {
+      const int r = m0 + p * RPP + (tid >> 4);
+      outs[p] = r < M ? ha.rows[r].out : -1;
+    }
+    const u32x4_t w0 = *(const u32x4_t*)(ha.w + l * 8), w1 = *(const u32x4_t*)(ha.w + 128 + l * 8);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const float bb = bias[n0 + wn * WN + j * 32 + (lane & 31)];
+      const int colq = wn * WN + j * 32 + (lane & 28);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          float q[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) q[k] = act_fn<ACT>(acc[i][j][4 * g + k] + bb);
+          quad_transpose4(q, lane);
+          const int rl = wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
+          const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
+          *(u32x2_t*)(hb + rl * HLD + colq * 2) = o;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < BM / RPP; ++p) {
+      const int rl = p * RPP + (tid >> 4);
+      float sum = 0.f;
+      const int64_t o = outs[p];
+      {
+        if (o >= 0) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const u32x4_t hv = *(const u32x4_t*)(hb + rl * HLD + (c * 128 + l * 8) * 2), wv = c ? w1 : w0;
+            sum += bf2f(hv.x & 0xffffu) * bf2f(wv.x & 0xffffu);
+            sum += bf2f(hv.x >> 16) * bf2f(wv.x >> 16);
+            sum += bf2f(hv.y & 0xffffu) * bf2f(wv.y & 0xffffu);
+            sum += bf2f(hv.y >> 16) * bf2f(wv.y >> 16);
+            sum += bf2f(hv.z & 0xffffu) * bf2f(wv.z & 0xffffu);
+            sum += bf2f(hv.z >> 16) * bf2f(wv.z >> 16);
+            sum += bf2f(hv.w & 0xffffu) * bf2f(wv.w & 0xffffu);
+            sum += bf2f(hv.w >> 16) * bf2f(wv.w >> 16);
+          }
+        }
+      }
+      sum += __shfl_xor(sum, 1);
+      sum += __shfl_xor(sum, 2);
+      sum += __shfl_xor(sum, 4);
+      sum += __shfl_xor(sum, 8);
+      if (l == 0 && o >= 0) ha.out[o] = act_fn<HEAD>(sum + ha.b);
+    }
+    }
+  };
+
+  if constexpr (PERSIST) {
+    // K a multiple of S k-steps (so every tile starts at stage 0) and at least
+    // S k-steps (so the loads of a tile's last steps reach only the next tile)
+    for (;;) {
+      for (int kt = 0; kt < nk; kt += S) group(kt);
+      epilogue();
+      if (!has_next) break;
+      v += gridDim.x;
+      m0 = m0n;
+      n0 = n0n;
+      rA = rAn;
+      rB = rBn;
+#pragma unroll
+      for (int i = 0; i < SA; ++i) va[i] = van[i];
+      next_tile();
+      zero_acc();
+    }
+    // no load into LDS may still be in flight when the wave ends
+    wait_vmcnt_lds<0>();
+  } else {
+    int kt = 0;
+    for (; kt + S <= nk; kt += S) group(kt);
+    if (kt < nk) step(kt, ic<0>{}, ic<1>{}, ic<S - 1>{});
+    if (kt + 1 < nk) step(kt + 1, ic<1>{}, ic<2 % S>{}, ic<0>{});
+    if constexpr (S > 3)
+      if (kt + 2 < nk) step(kt + 2, ic<2 % S>{}, ic<3 % S>{}, ic<1>{});
+    // no load into LDS may still be in flight when the wave ends
+    wait_vmcnt_lds<0>();
+    if constexpr (HEAD >= 0)
+      head_epilogue();
+    else
+      epilogue();
+  }
+}
+
+// The two operand types as separately named kernels (so that traces and
+// counters tell them apart).
+template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, bool OUT_F32, bool PERSIST>
+__global__ __launch_bounds__(NT) void k_gemm_bf16(const bf16_t* __restrict__ X, int ldx,
+                                                  const bf16_t* __restrict__ W, int ldw,
+                                                  const float* __restrict__ bias, void* __restrict__ Y, int ldy,
+                                                  int M, int N, int K, OutMap om) {
+  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, OUT_F32, PERSIST>(X, ldx, W, ldw, bias, Y, ldy, M, N, K,
+                                                                            nullptr, 0, HeadArgs{}, om);
+}
+// A bf16 layer of 256 outputs with a narrow head in its epilogue (HEAD: the
+// head's activation); the layer's outputs never leave the workgroup.
+template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, int HEAD>
+__global__ __launch_bounds__(NT) void k_gemm_head(const bf16_t* __restrict__ X, int ldx,
+                                                  const bf16_t* __restrict__ W, int ldw,
+                                                  const float* __restrict__ bias, int M, int K, HeadArgs ha) {
+  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, false, false, HEAD>(X, ldx, W, ldw, bias, nullptr, BN, M,
+                                                                             BN, K, nullptr, 0, ha);
+}
+template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT>
+__global__ __launch_bounds__(NT) void k_gemm_f32(const float* __restrict__ X, int ldx, const float* __restrict__ W,
+                                                 int ldw, const float* __restrict__ bias, void* __restrict__ Y,
+                                                 int ldy, int M, int N, int K,
+                                                 const rb_k_row* __restrict__ skip_rows, int skip_T, OutMap om) {
+  gemm_mfma<float, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, true, false>(X, ldx, W, ldw, bias, Y, ldy, M, N, K,
+                                                                       skip_rows, skip_T, HeadArgs{}, om);
+}
+
+// PERSIST: a grid of at most `cap` workgroups (a multiple of 8), each taking
+// every cap-th tile
+template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, bool PERSIST = false>
+void launch_gemm(hipStream_t s, const TI* x, int ldx, const TI* w, int ldw, const float* b, void* Y, int ldy,
+                 int M, int N, int K, int act, bool out_f32, const rb_k_row* skip_rows, int skip_T,
+                 unsigned cap = 0, OutMap om = OutMap{}) {
+  const unsigned tiles = (unsigned)(((M + BM - 1) / BM) * (N / BN));
+  const unsigned g = PERSIST ? std::min(tiles, cap) : tiles;
+  if constexpr (sizeof(TI) == 4) {
+#define RB_G(A)                                                                                                     \
+  hipLaunchKernelGGL((k_gemm_f32<BM, BN, WM, WN, NT, RB, S, ORDER, A>), dim3(g), dim3(NT), 0, s, x, ldx, w, ldw, b, \
+                     Y, ldy, M, N, K, skip_rows, skip_T, om)
+    if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU);
+    else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID);
+    else RB_G(RB_ACT_NONE);
+#undef RB_G
+  } else {
+#define RB_G(A, F)                                                                                             \
+  hipLaunchKernelGGL((k_gemm_bf16<BM, BN, WM, WN, NT, RB, S, ORDER, A, F, PERSIST>), dim3(g), dim3(NT), 0, s, x, ldx, w, \
+                     ldw, b, Y, ldy, M, N, K, om)
+    if (out_f32) {
+      if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU, true);
+      else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID, true);
+      else RB_G(RB_ACT_NONE, true);
+    } else {
+      if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU, false);
+      else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID, false);
+      else RB_G(RB_ACT_NONE, false);
+    }
+#undef RB_G
+  }
+}
+
+// bf16 operands, k-step BK bf16 values
+template <int BM, int BN, int WM, int WN, int NT, int BK, int S, int ORDER, bool PERSIST>
+void launch_gemm_bf16(hipStream_t s, const bf16_t* x, int ldx, const bf16_t* w, int ldw, const float* b, void* Y,
+                      int ldy, int M, int N, int K, int act, int out_f32, unsigned cap, OutMap om) {
+  launch_gemm<bf16_t, BM, BN, WM, WN, NT, BK * 2, S, ORDER, PERSIST>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act,
+                                                                    out_f32 != 0, nullptr, 0, cap, om);
+}
+
+}  // namespace
+
+extern "C" {
+
+namespace {
+rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
+                         void* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act, int32_t out_f32,
+                         OutMap om) {
+  if (M < 0 || N <= 0 || K <= 0 || (N % 128) || (K % G16_KALIGN) || ldx < K || ldw < K) return RB_EINVAL;
+  if ((ldx & 7) || (ldw & 7) || !X || !W || !b) return RB_EINVAL;
+  // operand byte offsets within a 256-row tile are 32-bit
+  if ((int64_t)ldx * 512 >= ((int64_t)1 << 31) || (int64_t)ldw * 512 >= ((int64_t)1 << 31)) return RB_EINVAL;
+  if (act != RB_ACT_NONE && act != RB_ACT_RELU && act != RB_ACT_SIGMOID) return RB_EINVAL;
+  if (M == 0) return RB_OK;
+  hipStream_t s = (hipStream_t)stream;
+  const bf16_t* x = (const bf16_t*)X;
+  const bf16_t* w = (const bf16_t*)W;
+  // Tile shape, k-step, stage count and tile order only change speed: every
+  // choice accumulates each output in the same k order with the same
+  // instruction (identical bits). The largest tile that still gives every CU a
+  // tile: 256 x 256 (k-step 64, 2 stages, 128 KB LDS, every row's k-step a
+  // whole 128-byte line) as 4 waves of 128 x 128 when there are at least two
+  // tiles per CU (half the fragment reads per flop of 8 waves of 64 x 128), as
+  // 8 waves of 64 x 128 when fewer (two waves per SIMD hide more of the single
+  // round's start and end), else 256 x 128 (8 waves of 64 x 64, k-step
+  // 64, 3 stages, 144 KB), else
+  // 128 x 128 (8 waves of 64 x 32, k-step 64, 4 stages, 128 KB), 128 x 64 (4
+  // waves of 64 x 32, 96 KB) or 64 x 64 (2 waves of 64 x 32, 64 KB). XCD-contiguous
+  // tile order when all of W fits in one XCD's L2 (each XCD then keeps its A
+  // row-blocks and W in its own L2); plain order otherwise (contiguous ranges
+  // would stream all of W through every XCD).
+  //
+  // With more 256 x 128 tiles than compute units, the grid is persistent (one
+  // workgroup per CU, each taking every CU-count-th tile) when K is a multiple of the
+  // stage count in k-steps: the operand loads then run on across tile
+  // boundaries, so a tile's first k-steps load during the previous tile's last
+  // steps and epilogue.
+  const int64_t rows256 = (M + 255) / 256;
+  const bool xcd = (int64_t)N * K * 2 <= (4 << 20);
+  const unsigned cus = device_cus() & ~7u;
+#define RB_PICK(BM, BN, WM, WN, NT, BK, S, P)                                                                   \
+  do {                                                                                                          \
+    if (xcd)                                                                                                    \
+      launch_gemm_bf16<BM, BN, WM, WN, NT, BK, S, 1, P>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act, out_f32, cus, om); \
+    else                                                                                                        \
+      launch_gemm_bf16<BM, BN, WM, WN, NT, BK, S, 0, P>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act, out_f32, cus, om); \
+  } while (0)
+  auto persist = [&](int bm, int bn, int bk, int st) {
+    const int64_t tiles = ((M + bm - 1) / bm) * (int64_t)(N / bn);
+    const int nk = K / bk;
+    return cus >= 8 && tiles > (int64_t)cus && nk >= st && nk % st == 0;
+  };
+  if (N % 256 == 0 && rows256 * (N / 256) >= 256) {
+    if (rows256 * (N / 256) >= 2 * (int64_t)cus)
+      RB_PICK(256, 256, 128, 128, 256, 64, 2, false);
+    else
+      RB_PICK(256, 256, 64, 128, 512, 64, 2, false);
+  } else if (rows256 * (N / 128) >= 256) {
+    if (persist(256, 128, 64, 3))
+      RB_PICK(256, 128, 64, 64, 512, 64, 3, true);
+    else
+      RB_PICK(256, 128, 64, 64, 512, 64, 3, false);
+  } else {
+    // fewer tiles than that: the k-loop's latency bounds a launch of a few
+    // batches, so the largest of 128 x 128, 128 x 64 and 64 x 64 tiles that
+    // still gives half the compute units a tile (512 x 1024 x 1728: 12.5 ->
+    // 8.7 us with 64 x 64; 2816 x 512 x 1024: 9.7 -> 7.3 us with 128 x 64)
+    const int64_t rows128 = (M + 127) / 128, half = std::max<int64_t>(cus / 2, 1);
+    if (rows128 * (N / 128) >= half)
+      RB_PICK(128, 128, 64, 32, 512, 64, 4, false);
+    else if (rows128 * (N / 64) >= half)
+      RB_PICK(128, 64, 64, 32, 256, 64, 4, false);
+    else
+      RB_PICK(64, 64, 64, 32, 128, 64, 4, false);
+  }
+#undef RB_PICK
+  return launch_status();
+}
+}  // namespace
+
+rb_status rb_k_gemm_bf16(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
+                         void* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act, int32_t out_f32) {
+  if (ldy < N || (ldy & 7) || ((uintptr_t)Y & 15) || !Y) return RB_EINVAL;
+  return gemm_bf16_impl(stream, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, out_f32, OutMap{});
+}
+
+rb_status rb_k_gemm_bf16_rows(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
+                              int32_t M, int32_t N, int32_t K, int32_t act, const rb_k_row* rows, int32_t d_out,
+                              float* out) {
+  if (!rows || !out || d_out < 1 || d_out > N) return RB_EINVAL;
+  return gemm_bf16_impl(stream, X, ldx, W, ldw, b, nullptr, N, M, N, K, act, 1, OutMap{rows, out, d_out});
+}
+
+namespace {
+rb_status gemm_f32_impl(void* stream, const float* X, int32_t ldx, const float* W, int32_t ldw, const float* b,
+                        float* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act,
+                        const rb_k_row* skip_rows, int32_t skip_T, OutMap om) {
+  if (M < 0 || N <= 0 || K <= 0 || (N % 64) || (K % G32_KALIGN) || ldx < K || ldw < K) return RB_EINVAL;
+  if ((ldx & 3) || (ldw & 3) || !X || !W || !b) return RB_EINVAL;
+  if (((uintptr_t)X & 15) || ((uintptr_t)W & 15)) return RB_EINVAL;
+  // operand byte offsets within a 64-row tile are 32-bit
+  if ((int64_t)ldx * 4 * G32_BM >= ((int64_t)1 << 31) || (int64_t)ldw * 4 * 64 >= ((int64_t)1 << 31)) return RB_EINVAL;
+  if (act != RB_ACT_NONE && act != RB_ACT_RELU && act != RB_ACT_SIGMOID) return RB_EINVAL;
+  if (skip_rows && (skip_T <= 0 || skip_T % G32_BM)) return RB_EINVAL;
+  if (M == 0) return RB_OK;
+  hipStream_t s = (hipStream_t)stream;
+  // 64 x 64 tiles (64 rows: the padding-token skip granularity), 4 waves of
+  // 32 x 32, k-step 16, 3 stages (24 KB LDS, six workgroups per CU). Small
+  // wave tiles keep the work per wave small, so the CUs stay evenly loaded when
+  // padding-token blocks leave holes in the grid (64 x 64 wave tiles measured
+  // up to 1.5x slower there). XCD-contiguous tile order when W fits in one
+  // XCD's L2 (each XCD then reads its X rows once; plain order measured 1.5x
+  // slower on sequence groups).
+  const bool xcd = (int64_t)N * K * 4 <= (4 << 20);
+  if (xcd)
+    launch_gemm<float, G32_BM, 64, 32, 32, 256, 64, 3, 1>(s, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, true, skip_rows,
+                                                          skip_T, 0, om);
+  else
+    launch_gemm<float, G32_BM, 64, 32, 32, 256, 64, 3, 0>(s, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, true, skip_rows,
+                                                          skip_T, 0, om);
+  return launch_status();
+}
+}  // namespace
+
+rb_status rb_k_gemm_f32(void* stream, const float* X, int32_t ldx, const float* W, int32_t ldw, const float* b,
+                        float* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act,
+                        const rb_k_row* skip_rows, int32_t skip_T) {
+  if (ldy < N || (ldy & 3) || ((uintptr_t)Y & 15) || !Y) return RB_EINVAL;
+  return gemm_f32_impl(stream, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, skip_rows, skip_T, OutMap{});
+}
+
+rb_status rb_k_gemm_f32_rows(void* stream, const float* X, int32_t ldx, const float* W, int32_t ldw, const float* b,
+                             int32_t M, int32_t N, int32_t K, int32_t act, const rb_k_row* rows, int32_t d_out,
+                             float* out) {
+  if (!rows || !out || d_out < 1 || d_out > N) return RB_EINVAL;
+  return gemm_f32_impl(stream, X, ldx, W, ldw, b, nullptr, N, M, N, K, act, nullptr, 0, OutMap{rows, out, d_out});
+}
+
+rb_status rb_k_gemm_head(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
+                         int32_t M, int32_t K, int32_t act, const rb_k_row* rows, const void* w_head, float b_head,
+                         int32_t head_act, float* out) {
+  if (M < 0 || K <= 0 || (K % G16_KALIGN) || ldx < K || ldw < K || (ldx & 7) || (ldw & 7)) return RB_EINVAL;
+  if (!X || !W || !b || !rows || !w_head || !out || ((uintptr_t)w_head & 15)) return RB_EINVAL;
+  if ((int64_t)ldx * 512 >= ((int64_t)1 << 31) || (int64_t)ldw * 512 >= ((int64_t)1 << 31)) return RB_EINVAL;
+  if (act != RB_ACT_NONE && act != RB_ACT_RELU && act != RB_ACT_SIGMOID) return RB_EINVAL;
+  if (head_act != RB_ACT_NONE && head_act != RB_ACT_SIGMOID) return RB_EINVAL;
+  if (M == 0) return RB_OK;
+  // 128 x 256 tiles (every row's 256 outputs in one workgroup), 8 waves of
+  // 64 x 64 (two per SIMD: 4 waves of 64 x 128 measured 16% slower), k-step
+  // 64, 3 stages; XCD-contiguous order (W is 256 x K bf16). With fewer such
+  // tiles than half the compute units (a launch of a few batches, bound by
+  // its k-loop's latency), 64 x 256 tiles of 8 waves of 64 x 32.
+  const bool small = (int64_t)(M + 127) / 128 < std::max<int64_t>(device_cus() / 2, 1);
+  const unsigned g = (unsigned)(small ? (M + 63) / 64 : (M + 127) / 128);
+  const HeadArgs ha{rows, (const bf16_t*)w_head, b_head, out};
+  hipStream_t s = (hipStream_t)stream;
+#define RB_GH(A, H)                                                                                                    \
+  do {                                                                                                                 \
+    if (small)                                                                                                         \
+      hipLaunchKernelGGL((k_gemm_head<64, 256, 64, 32, 512, 128, 3, 1, A, H>), dim3(g), dim3(512), 0, s,             \
+                         (const bf16_t*)X, ldx, (const bf16_t*)W, ldw, b, M, K, ha);                                   \
+    else                                                                                                               \
+      hipLaunchKernelGGL((k_gemm_head<128, 256, 64, 64, 512, 128, 3, 1, A, H>), dim3(g), dim3(512), 0, s,            \
+                         (const bf16_t*)X, ldx, (const bf16_t*)W, ldw, b, M, K, ha);                                   \
+  } while (0)
+  if (head_act == RB_ACT_SIGMOID) {
+    if (act == RB_ACT_RELU) RB_GH(RB_ACT_RELU, RB_ACT_SIGMOID);
+    else if (act == RB_ACT_SIGMOID) RB_GH(RB_ACT_SIGMOID, RB_ACT_SIGMOID);
+    else RB_GH(RB_ACT_NONE, RB_ACT_SIGMOID);
+  } else {
+    if (act == RB_ACT_RELU) RB_GH(RB_ACT_RELU, RB_ACT_NONE);
+    else if (act == RB_ACT_SIGMOID) RB_GH(RB_ACT_SIGMOID, RB_ACT_NONE);
+    else RB_GH(RB_ACT_NONE, RB_ACT_NONE);
+  }
+#undef RB_GH
+  return launch_status();
+}
+
+}  // extern "C"

@@ -26,61 +26,11 @@
 // Every row is computed the same way whatever batch it sits in (one tile
 // shape and k order per layer, no row-count-dependent split of the sum), so a
 // request's result does not depend on how its batch was composed.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include <type_traits>
-#include <algorithm>
-#include <atomic>
 #include <mutex>
 
-#include "../../include/rb.h"
+#include "device.h"
 
 namespace {
-
-typedef uint16_t bf16_t;
-typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8_t;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ bf16_t f2bf(float f) {
-  // round to nearest even on the 16 dropped bits; NaN stays a (quiet) NaN
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 16); }
-
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-  return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
-}
-
-template <int ACT>
-__device__ __forceinline__ float act_fn(float z) {
-  if (ACT == RB_ACT_RELU) return z > 0.f ? z : 0.f;
-  if (ACT == RB_ACT_SIGMOID) return 1.f / (1.f + expf(-z));
-  return z;
-}
-
-// Workgroups are handed to the 8 XCDs round-robin (block i runs on XCD i % 8)
-// and each XCD has its own L2. Remap so that XCD x gets a contiguous range of
-// tiles: with tiles ordered row-block-major, the tiles sharing an A row-block
-// then run on the same XCD and re-read it from that XCD's L2.
-__device__ __forceinline__ int xcd_tile(int bid, int nb) {
-  const int nb8 = nb & ~7;
-  return bid < nb8 ? (bid & 7) * (nb8 >> 3) + (bid >> 3) : bid;
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 
 // ---------------------------------------------------------------- route
 
@@ -816,577 +766,24 @@ __global__ __launch_bounds__(DD_NT) void k_embbag_dedup(const rb_k_row* __restri
   }
 }
 
-// ---------------------------------------------------------------- GEMM (bf16 and fp32)
-
-// value of v in lane l ^ 2 / l ^ 1 of the same quad (DPP quad permutations:
-// plain VALU moves, no LDS traffic)
-__device__ __forceinline__ float quad_xor2(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));  // [2,3,0,1]
-}
-__device__ __forceinline__ float quad_xor1(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));  // [1,0,3,2]
-}
-
-// 4 x 4 transpose across the four lanes of a quad: lane 4q + i holding x[k] =
-// element (k, i) ends up holding x[j] = element (i, j), where element (k, c)
-// is the value lane 4q + c held in x[k]. Two exchange rounds (lane xor 2, then
-// lane xor 1), each sending two values and keeping two, with selects only.
-__device__ __forceinline__ void quad_transpose4(float (&x)[4], int lane) {
-  const bool b1 = lane & 2, b0 = lane & 1;
-  float r0 = quad_xor2(b1 ? x[0] : x[2]), r1 = quad_xor2(b1 ? x[1] : x[3]);
-  const float y0 = b1 ? r0 : x[0], y1 = b1 ? r1 : x[1], y2 = b1 ? x[2] : r0, y3 = b1 ? x[3] : r1;
-  r0 = quad_xor1(b0 ? y0 : y1);
-  r1 = quad_xor1(b0 ? y2 : y3);
-  x[0] = b0 ? r0 : y0;
-  x[1] = b0 ? y1 : r0;
-  x[2] = b0 ? r1 : y2;
-  x[3] = b0 ? y3 : r1;
-}
-
-// two floats rounded to bf16 (round to nearest even, v_cvt_pk_bf16_f32),
-// the first in the low half
-__device__ __forceinline__ uint32_t pack2_rne(float a, float b) {
-  typedef __bf16 bf16x2_hw __attribute__((ext_vector_type(2)));
-  typedef float float2_hw __attribute__((ext_vector_type(2)));
-  const float2_hw f = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_hw));
-}
-
-// s_waitcnt vmcnt(N) lgkmcnt(0) (gfx9 encoding: vmcnt[3:0], expcnt[6:4],
-// lgkmcnt[11:8], vmcnt[5:4] in bits 15:14): at most N vector memory
-// operations of this wave in flight and every LDS read of it returned.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt_lds() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
-
-template <int I>
-using ic = std::integral_constant<int, I>;
-
-// f(ic<0>{}), f(ic<1>{}), ..., f(ic<N - 1>{}), unrolled at compile time
-template <int... I, class F>
-__device__ __forceinline__ void for_each_ic(std::integer_sequence<int, I...>, F&& f) {
-  (f(ic<I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  for_each_ic(std::make_integer_sequence<int, N>{}, f);
-}
-
-// LDS byte address of a __shared__ object.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
-
-// Buffer resource (gfx9 layout: base address, stride 0, no range limit) for
-// a wave-uniform base address.
-__device__ __forceinline__ i32x4_t buffer_rsrc(const void* base) {
-  const uint64_t p = (uint64_t)(uintptr_t)base;
-  i32x4_t r;
-  r.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
-  r.y = __builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xffffu));
-  r.z = -1;
-  r.w = 0x00020000;
-  return r;
-}
-
-// One 16-byte-per-lane buffer -> LDS load (buffer_load_dwordx4 ... lds) of the
-// bytes at base + voff + soff: lane l's 16 bytes land at LDS byte lds + 16 l.
-// Issued as inline assembly so that the compiler does not add its own
-// conservative waits for it: the kernel waits with explicit vmcnt counts and
-// a barrier before the data is read.
-__device__ __forceinline__ void buffer_to_lds(i32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
-               "s"(soff)
-               : "memory", "m0");
-}
-
-// Y = act(X W^T + b): X [M, K] and W [N, K] of element type TI (bf16 or
-// fp32), K contiguous; fp32 accumulation with v_mfma_f32_32x32x16_bf16 or
-// v_mfma_f32_32x32x2f32.
-//
-// Workgroup tile BM x BN, k-step of RB bytes per row (64 or 128: 32 or 64
-// bf16, 16 or 32 fp32), NT/64 waves each owning a WM x WN sub-tile
-// ((WM/32) x (WN/32) accumulators). Operand tiles go straight from global
-// memory into a ring of S >= 2 LDS stages (global_load_lds: each wave load
-// instruction fills 1 KB of consecutive LDS rows; no register staging).
-// K-step kt reads stage kt % S while the stage of k-step kt - 1 is refilled
-// with k-step kt - 1 + S, its loads spread one every few MFMAs over the step
-// (over its first half when S = 2, where that refill is the next k-step):
-// issued back to back they stall the wave on the texture path with no MFMA in
-// flight. A sub-step covers 32 bytes of every row (16 bf16 or 8 fp32 k values)
-// and its MFMAs have the next sub-step's fragment reads between them. In the
-// last sub-step, after half of its MFMAs (three quarters with S = 2), the wave
-// waits for its loads of the next k-step and for its LDS reads, and all waves
-// meet at one barrier: the next stage has landed and nobody reads the current
-// one again. The rest of the sub-step then runs with the next k-step's first
-// fragment reads between the MFMAs. The order of MFMAs, LDS reads and loads
-// within a step is fixed with scheduling barriers.
-//
-// A fragment is 16 bytes of one row: lane l holds row l % 32 and chunk
-// 2 kk + l / 32 of sub-step kk. bf16: one 32x32x16 MFMA per accumulator and
-// sub-step. fp32: chunk c holds k = 4c .. 4c + 3, and MFMA t (t = 0..3) of the
-// sub-step takes dword t, so it adds the products of k = 8 kk + t (lanes
-// 0..31) and k = 8 kk + 4 + t (lanes 32..63); the MFMAs of a sub-step run
-// t-major over the accumulators, so two MFMAs into one accumulator are NM
-// instructions apart.
-//
-// LDS rows hold RB/16 16-byte chunks; chunk c of row r sits at chunk
-// c ^ ((r / (16 / (RB/16))) % (RB/16)), so the 16 rows one fragment read
-// serves per LDS cycle hit 16 distinct bank groups (64 banks).
-//
-// Every tile shape, k-step, stage count and tile order accumulates each output
-// element in the same k order with the same instructions, so results do not
-// depend on them, nor on which rows share a tile.
-//
-// skip_rows (sequence layout, slot e owning rows [e skip_T, (e + 1) skip_T),
-// skip_T a multiple of BM): a workgroup whose rows are all padding tokens
-// (at or past its slot's length, or in a padding slot) returns at once.
-constexpr int G16_KALIGN = 64;  // K multiple the bf16 entry point accepts
-constexpr int G32_KALIGN = 32;  // K multiple the fp32 entry point accepts
-constexpr int G32_BM = 64;      // fp32 tile height (the padding-token skip granularity)
-
-// A narrow head applied in the epilogue instead of storing the layer's
-// output (HEAD >= 0, the head's activation): the layer's bf16 outputs of
-// the tile (all N = BN columns of its rows) go to LDS, and row r's head
-// output act(w . y_r + b) is written to out[rows[r].out] when that is >= 0.
-struct HeadArgs {
-  const rb_k_row* rows;
-  const bf16_t* w;  // BN bf16 weights, 16-byte aligned
-  float b;
-  float* out;
-};
-
-// fp32 outputs written through a row map instead of to Y (rows != nullptr):
-// row r's first d_out columns go to out[rows[r].out ...] when that is >= 0
-// (the merged run's split fused into its last layer); padding rows and
-// columns past d_out are dropped.
-struct OutMap {
-  const rb_k_row* rows;
-  float* out;
-  int d_out;
-};
-
-template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, bool OUT_F32,
-          bool PERSIST, int HEAD = -1>
-__device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, const TI* __restrict__ W, int ldw,
-                                          const float* __restrict__ bias, void* __restrict__ Y, int ldy, int M,
-                                          int N, int K, const rb_k_row* __restrict__ skip_rows, int skip_T,
-                                          const HeadArgs ha = HeadArgs{}, const OutMap om = OutMap{}) {
-  constexpr bool F32 = sizeof(TI) == 4;
-  constexpr int ES = sizeof(TI);  // bytes per element
-  constexpr int BK = RB / ES;     // k values per k-step
-  constexpr int NW = NT / 64;
-  static_assert((BM / WM) * (BN / WN) == NW, "one wave per sub-tile");
-  static_assert(RB == 64 || RB == 128, "k-step of 64 or 128 bytes per row");
-  static_assert(S >= 2 && S <= 4, "2..4 stages");
-  constexpr int CPR = RB / 16;   // 16-byte chunks per LDS row
-  constexpr int RPI = 64 / CPR;  // rows filled per wave load instruction
-  constexpr int SWZ = 16 / CPR;  // rows sharing one swizzle pattern
-  constexpr int EPC = 16 / ES;   // elements per chunk
-  constexpr int TM = WM / 32, TN = WN / 32;
-  static_assert(TM % 2 == 0 || F32, "the last sub-step splits the A fragments in halves");
-  constexpr int SA = BM / RPI / NW, SB = BN / RPI / NW;  // load instructions per wave per stage
-  static_assert(SA * NW * RPI == BM && SB * NW * RPI == BN, "loads cover the tile");
-  constexpr int OPS = SA + SB;
-  constexpr int KK = RB / 32;    // MFMA sub-steps per k-step
-  constexpr int NM = TM * TN;    // accumulators
-  constexpr int MPF = F32 ? 4 : 1;  // MFMAs per accumulator and sub-step
-  constexpr int NU = NM * MPF;   // MFMAs per sub-step
-  constexpr int NR = TM + TN;    // fragment reads per sub-step
-  // the last sub-step's MFMAs before the barrier: half of them, three quarters
-  // with two stages (more time for the loads of the next k-step to land)
-  constexpr int UB = S == 2 ? NU * 3 / 4 : NU / 2;
-  constexpr int PRE = (KK - 1) * NU + UB;  // MFMAs of a step before its barrier
-  // MFMA slots the refill loads are spread over: with two stages the stage
-  // refilled during a step is the one the next step reads, so its loads go in
-  // the first half of the step to land before the barrier
-  constexpr int LPOS = S == 2 ? PRE / 2 : PRE;
-  // fragment read slot -> fragment (A fragments q < TM, then B). With two
-  // stages (bf16) in the order the next sub-step's MFMAs consume them (A0, B0
-  // .. B(TN-1), A1 .. A(TM-1)), so the fragment needed first is read first;
-  // otherwise A0 .. A(TM-1), B0 .. B(TN-1).
-  auto qmap = [](auto sc) {
-    constexpr int q = decltype(sc)::value;
-    if constexpr (S != 2 || F32 || q == 0)
-      return ic<q>{};
-    else if constexpr (q <= TN)
-      return ic<TM + q - 1>{};
-    else
-      return ic<q - TN>{};
-  };
-  __shared__ u32x4_t sA[S][BM * CPR];
-  __shared__ u32x4_t sB[S][BN * CPR];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wid / (BN / WN), wn = wid % (BN / WN);
-  const int tiles_n = N / BN;
-  const int ntiles = ((M + BM - 1) / BM) * tiles_n;
-  // v: this workgroup's index in the tile sequence (blockIdx.x, then + gridDim.x
-  // per tile when persistent; gridDim.x is a multiple of 8, so v % 8 stays the
-  // XCD the workgroup runs on)
-  int v = blockIdx.x;
-  auto tile_origin = [&](int vv, int& m0_, int& n0_) {
-    const int tile = ORDER ? xcd_tile(vv, ntiles) : vv;
-    const int bm = tile / tiles_n;
-    m0_ = bm * BM;
-    n0_ = (tile - bm * tiles_n) * BN;
-  };
-  int m0, n0;
-  tile_origin(v, m0, n0);
-  if (skip_rows) {  // uniform per workgroup
-    const int e = m0 / skip_T;
-    const rb_k_row rw = skip_rows[e];
-    if (rw.src < 0 || m0 - e * skip_T >= rw.aux) return;
+// The arena offset of every packed token row, one wave per sequence slot:
+// token t of slot e is packed row rows[e].lens + t and starts at element
+// rows[e].src + t d_in of the dense arena. The checks are k_assemble_seq's; a
+// sequence that fails them sets *err and leaves its entries as they are (the
+// layer that reads them checks each against the arena).
+__global__ __launch_bounds__(256) void k_token_rows(const rb_k_row* __restrict__ rows, int n_slots, int T,
+                                                    int64_t dense_len, int d_in, int64_t* __restrict__ src,
+                                                    int64_t n_src, int* __restrict__ err) {
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (e >= n_slots) return;
+  const rb_k_row rw = rows[e];
+  if (rw.src < 0 || rw.aux <= 0) return;
+  const int64_t L = rw.aux;
+  if (L > T || rw.src + L * d_in > dense_len || rw.lens < 0 || rw.lens + L > n_src) {
+    if ((threadIdx.x & 63) == 0) *err = 1;
+    return;
   }
-
-  // lane l of a load instruction fills LDS row l / CPR (of its RPI), chunk l % CPR
-  const int lr = lane / CPR, lc = lane % CPR;
-  // byte offsets from the tile's first row (buffer resources based there; the
-  // k-step's byte offset goes in the scalar offset)
-  auto a_offsets = [&](int m0_, uint32_t (&va_)[SA]) {
-#pragma unroll
-    for (int i = 0; i < SA; ++i) {
-      const int row = (wid * SA + i) * RPI + lr;
-      const int ra = min(row, M - 1 - m0_);  // rows past M are computed on a copy and never stored
-      va_[i] = (uint32_t)(ra * ldx + (lc ^ ((row / SWZ) % CPR)) * EPC) * (uint32_t)ES;
-    }
-  };
-  i32x4_t rA = buffer_rsrc(X + (int64_t)m0 * ldx), rB = buffer_rsrc(W + (int64_t)n0 * ldw);
-  uint32_t va[SA], vb[SB];
-  a_offsets(m0, va);
-#pragma unroll
-  for (int i = 0; i < SB; ++i) {
-    const int row = (wid * SB + i) * RPI + lr;
-    vb[i] = (uint32_t)(row * ldw + (lc ^ ((row / SWZ) % CPR)) * EPC) * (uint32_t)ES;
-  }
-  // persistent: the next tile's origin, resources and A offsets (a copy of the
-  // current tile's when there is none)
-  int m0n = m0, n0n = n0;
-  bool has_next = false;
-  i32x4_t rAn = rA, rBn = rB;
-  uint32_t van[SA];
-#pragma unroll
-  for (int i = 0; i < SA; ++i) van[i] = va[i];
-  auto next_tile = [&]() {
-    has_next = v + (int)gridDim.x < ntiles;
-    if (has_next) {
-      tile_origin(v + (int)gridDim.x, m0n, n0n);
-      rAn = buffer_rsrc(X + (int64_t)m0n * ldx);
-      rBn = buffer_rsrc(W + (int64_t)n0n * ldw);
-      a_offsets(m0n, van);
-    } else {
-      m0n = m0;
-      n0n = n0;
-      rAn = rA;
-      rBn = rB;
-#pragma unroll
-      for (int i = 0; i < SA; ++i) van[i] = va[i];
-    }
-  };
-  if constexpr (PERSIST) next_tile();
-
-  floatx16_t acc[TM][TN];
-  auto zero_acc = [&]() {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  };
-  zero_acc();
-
-  const int nk = K / BK;
-  // load instruction o (A rows for o < SA, then B rows) of k-step kt into
-  // stage st. K-steps past the end reload the last one into a stage that is
-  // never read again, so every step runs the same branch-free code; when
-  // persistent, they are the next tile's first k-steps instead (the load stream
-  // runs on across tiles, so the next tile's operands are in flight during this
-  // tile's last steps and epilogue).
-  auto issue_one = [&](int kt, auto stc, auto oc) {
-    constexpr int st = decltype(stc)::value, o = decltype(oc)::value;
-    if constexpr (PERSIST) {
-      const bool nx = kt >= nk;  // uniform
-      const uint32_t kb = (uint32_t)((nx ? (has_next ? kt - nk : nk - 1) : kt) * RB);
-      if constexpr (o < SA)
-        buffer_to_lds(nx ? rAn : rA, nx ? van[o] : va[o], kb, lds_addr(&sA[st][0]) + (wid * SA + o) * 1024);
-      else
-        buffer_to_lds(nx ? rBn : rB, vb[o - SA], kb, lds_addr(&sB[st][0]) + (wid * SB + o - SA) * 1024);
-    } else {
-      const uint32_t kb = (uint32_t)(min(kt, nk - 1) * RB);
-      if constexpr (o < SA)
-        buffer_to_lds(rA, va[o], kb, lds_addr(&sA[st][0]) + (wid * SA + o) * 1024);
-      else
-        buffer_to_lds(rB, vb[o - SA], kb, lds_addr(&sB[st][0]) + (wid * SB + o - SA) * 1024);
-    }
-  };
-  u32x4_t fa[2][TM], fb[2][TN];
-  // fragment read q (A fragment q for q < TM, then B) of sub-step kk of stage st
-  auto read_one = [&](auto stc, int kk, auto qc, auto bufc) {
-    constexpr int st = decltype(stc)::value, q = decltype(qc)::value, bf = decltype(bufc)::value;
-    // lane l holds row l % 32, chunk 2 kk + l / 32
-    const int ch = kk * 2 + (lane >> 5);
-    if constexpr (q < TM) {
-      const int r = wm * WM + q * 32 + (lane & 31);
-      fa[bf][q] = sA[st][r * CPR + (ch ^ ((r / SWZ) % CPR))];
-    } else {
-      const int r = wn * WN + (q - TM) * 32 + (lane & 31);
-      fb[bf][q - TM] = sB[st][r * CPR + (ch ^ ((r / SWZ) % CPR))];
-    }
-  };
-  // k-step kt: stage stc, next stage nstc, refilled stage rstc (k-step kt - 1's)
-  auto step = [&](int kt, auto stc, auto nstc, auto rstc) {
-    static_for<KK>([&](auto kkc) {
-      constexpr int kk = decltype(kkc)::value;
-      constexpr bool last = kk == KK - 1;
-      constexpr int cur = kk & 1, nxt = (kk + 1) & 1;
-      static_for<NU>([&](auto uc) {
-        constexpr int u = decltype(uc)::value;
-        constexpr int m = u % NM, t = u / NM;
-        if constexpr (last && u == UB) {
-          wait_vmcnt_lds<(S - 2) * OPS>();
-          lds_barrier();
-        }
-        if constexpr (F32)
-          acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-              __uint_as_float(fa[cur][m / TN][t]), __uint_as_float(fb[cur][m % TN][t]), acc[m / TN][m % TN], 0, 0, 0);
-        else
-          acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8_t, fa[cur][m / TN]), __builtin_bit_cast(bf16x8_t, fb[cur][m % TN]),
-              acc[m / TN][m % TN], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<NR>([&](auto qc) {
-          constexpr int q = decltype(qc)::value;
-          if constexpr (!last) {
-            if constexpr (q * NU / NR == u) read_one(stc, kk + 1, qmap(qc), ic<nxt>{});
-          } else if constexpr (u >= UB) {
-            if constexpr (UB + q * (NU - UB) / NR == u) read_one(nstc, 0, qmap(qc), ic<0>{});
-          }
-        });
-        constexpr int pos = kk * NU + u;
-        static_for<OPS>([&](auto oc) {
-          constexpr int o = decltype(oc)::value;
-          if constexpr (o * LPOS / OPS == pos) issue_one(kt - 1 + S, rstc, oc);
-        });
-        __builtin_amdgcn_sched_barrier(0);
-      });
-    });
-  };
-  static_for<S - 1>([&](auto sc) { static_for<OPS>([&](auto oc) { issue_one(decltype(sc)::value, sc, oc); }); });
-  wait_vmcnt_lds<(S - 2) * OPS>();
-  lds_barrier();
-  static_for<NR>([&](auto qc) { read_one(ic<0>{}, 0, qmap(qc), ic<0>{}); });
-  auto group = [&](int kt) {  // S k-steps from a multiple of S
-    step(kt, ic<0>{}, ic<1>{}, ic<S - 1>{});
-    step(kt + 1, ic<1>{}, ic<2 % S>{}, ic<0>{});
-    if constexpr (S > 2) step(kt + 2, ic<2 % S>{}, ic<3 % S>{}, ic<1>{});
-    if constexpr (S > 3) step(kt + 3, ic<3>{}, ic<0>{}, ic<2>{});
-  };
-
-  // accumulator (i, j) register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4,
-  // column l%32 of its 32 x 32 block. Bias and activation are applied per
-  // column; then each group of four registers (four consecutive rows) is
-  // transposed across the four lanes of a quad, so that a lane holds four
-  // consecutive columns of one row and stores them at once (8 bytes bf16, 16
-  // bytes fp32) instead of four single elements.
-  auto epilogue = [&]() {
-  // with an output row map: the output offsets of this lane's rows, loaded
-  // all at once before any is needed
-  const bool mapped = OUT_F32 && om.rows != nullptr;  // uniform
-  int64_t ro[TM][4];
-  if (mapped) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int r = m0 + wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
-        ro[i][g] = r < M ? om.rows[r].out : -1;
-      }
-  }
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const float bb = bias[n0 + wn * WN + j * 32 + (lane & 31)];
-    const int colq = n0 + wn * WN + j * 32 + (lane & 28);  // first column of this lane's quad
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float q[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = act_fn<ACT>(acc[i][j][4 * g + k] + bb);
-        quad_transpose4(q, lane);
-        const int row = m0 + wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
-        // streaming (nontemporal) stores: the whole chip writes its tiles'
-        // outputs at about the same time, and these drain faster than
-        // stores that allocate in L2
-        if constexpr (OUT_F32) {
-          if (mapped) {
-            const int64_t o = ro[i][g];
-            if (o >= 0) {
-              float* dst = om.out + o + colq;
-              if (colq + 3 < om.d_out && ((uintptr_t)dst & 15) == 0) {
-                const f32x4_t v = {q[0], q[1], q[2], q[3]};
-                __builtin_nontemporal_store(v, (f32x4_t*)dst);
-              } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                  if (colq + k < om.d_out) dst[k] = q[k];
-              }
-            }
-            continue;
-          }
-        }
-        if (row < M) {
-          if (OUT_F32) {
-            const f32x4_t o = {q[0], q[1], q[2], q[3]};
-            __builtin_nontemporal_store(o, (f32x4_t*)((float*)Y + (int64_t)row * ldy + colq));
-          } else {
-            const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
-            __builtin_nontemporal_store(o, (u32x2_t*)((bf16_t*)Y + (int64_t)row * ldy + colq));
-          }
-        }
-      }
-  }
-  };
-
-  // The head instead of the store: the tile's outputs, rounded to bf16 exactly
-  // as the store would round them, into LDS rows of HLD bytes (over the
-  // operand stages, once every wave is done with them); then 16 lanes per row
-  // sum w . y in the order of k_head (lane l: elements 8 l .. 8 l + 7 of every
-  // 128, then a 16-lane butterfly), so the results equal the separate layer and
-  // head bit for bit.
-  auto head_epilogue = [&]() {
-    if constexpr (HEAD >= 0) {
-    constexpr int RPP = NT / 16;  // rows per pass of the head (16 lanes each)
-    static_assert(!F32 && !OUT_F32 && BN == 256 && BM % RPP == 0, "bf16 layer of 256 outputs");
-    constexpr int HLD = BN * 2 + 16;
-    static_assert(BM * HLD <= S * BN * CPR * 16, "the output tile fits over the B stages");
-    unsigned char* hb = (unsigned char*)&sB[0][0];
-    // the output offsets of this thread's rows and its head weights, loaded
-    // before the tile goes to LDS so that their latency overlaps it
-    const int l = tid & 15;
-    int64_t outs[BM / RPP];
-#pragma unroll
-    for (int p = 0; p < BM / RPP; ++p) {
-      const int r = m0 + p * RPP + (tid >> 4);
-      outs[p] = r < M ? ha.rows[r].out : -1;
-    }
-    const u32x4_t w0 = *(const u32x4_t*)(ha.w + l * 8), w1 = *(const u32x4_t*)(ha.w + 128 + l * 8);
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const float bb = bias[n0 + wn * WN + j * 32 + (lane & 31)];
-      const int colq = wn * WN + j * 32 + (lane & 28);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float q[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) q[k] = act_fn<ACT>(acc[i][j][4 * g + k] + bb);
-          quad_transpose4(q, lane);
-          const int rl = wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
-          const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
-          *(u32x2_t*)(hb + rl * HLD + colq * 2) = o;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < BM / RPP; ++p) {
-      const int rl = p * RPP + (tid >> 4);
-      float sum = 0.f;
-      const int64_t o = outs[p];
-      {
-        if (o >= 0) {
-#pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            const u32x4_t hv = *(const u32x4_t*)(hb + rl * HLD + (c * 128 + l * 8) * 2), wv = c ? w1 : w0;
-            sum += bf2f(hv.x & 0xffffu) * bf2f(wv.x & 0xffffu);
-            sum += bf2f(hv.x >> 16) * bf2f(wv.x >> 16);
-            sum += bf2f(hv.y & 0xffffu) * bf2f(wv.y & 0xffffu);
-            sum += bf2f(hv.y >> 16) * bf2f(wv.y >> 16);
-            sum += bf2f(hv.z & 0xffffu) * bf2f(wv.z & 0xffffu);
-            sum += bf2f(hv.z >> 16) * bf2f(wv.z >> 16);
-            sum += bf2f(hv.w & 0xffffu) * bf2f(wv.w & 0xffffu);
-            sum += bf2f(hv.w >> 16) * bf2f(wv.w >> 16);
-          }
-        }
-      }
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      sum += __shfl_xor(sum, 4);
-      sum += __shfl_xor(sum, 8);
-      if (l == 0 && o >= 0) ha.out[o] = act_fn<HEAD>(sum + ha.b);
-    }
-    }
-  };
-
-  if constexpr (PERSIST) {
-    // K a multiple of S k-steps (so every tile starts at stage 0) and at least
-    // S k-steps (so the loads of a tile's last steps reach only the next tile)
-    for (;;) {
-      for (int kt = 0; kt < nk; kt += S) group(kt);
-      epilogue();
-      if (!has_next) break;
-      v += gridDim.x;
-      m0 = m0n;
-      n0 = n0n;
-      rA = rAn;
-      rB = rBn;
-#pragma unroll
-      for (int i = 0; i < SA; ++i) va[i] = van[i];
-      next_tile();
-      zero_acc();
-    }
-    // no load into LDS may still be in flight when the wave ends
-    wait_vmcnt_lds<0>();
-  } else {
-    int kt = 0;
-    for (; kt + S <= nk; kt += S) group(kt);
-    if (kt < nk) step(kt, ic<0>{}, ic<1>{}, ic<S - 1>{});
-    if (kt + 1 < nk) step(kt + 1, ic<1>{}, ic<2 % S>{}, ic<0>{});
-    if constexpr (S > 3)
-      if (kt + 2 < nk) step(kt + 2, ic<2 % S>{}, ic<3 % S>{}, ic<1>{});
-    // no load into LDS may still be in flight when the wave ends
-    wait_vmcnt_lds<0>();
-    if constexpr (HEAD >= 0)
-      head_epilogue();
-    else
-      epilogue();
-  }
-}
-
-// The two operand types as separately named kernels (so that traces and
-// counters tell them apart).
-template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, bool OUT_F32, bool PERSIST>
-__global__ __launch_bounds__(NT) void k_gemm_bf16(const bf16_t* __restrict__ X, int ldx,
-                                                  const bf16_t* __restrict__ W, int ldw,
-                                                  const float* __restrict__ bias, void* __restrict__ Y, int ldy,
-                                                  int M, int N, int K, OutMap om) {
-  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, OUT_F32, PERSIST>(X, ldx, W, ldw, bias, Y, ldy, M, N, K,
-                                                                            nullptr, 0, HeadArgs{}, om);
-}
-// A bf16 layer of 256 outputs with a narrow head in its epilogue (HEAD: the
-// head's activation); the layer's outputs never leave the workgroup.
-template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, int HEAD>
-__global__ __launch_bounds__(NT) void k_gemm_head(const bf16_t* __restrict__ X, int ldx,
-                                                  const bf16_t* __restrict__ W, int ldw,
-                                                  const float* __restrict__ bias, int M, int K, HeadArgs ha) {
-  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, false, false, HEAD>(X, ldx, W, ldw, bias, nullptr, BN, M,
-                                                                             BN, K, nullptr, 0, ha);
-}
-template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT>
-__global__ __launch_bounds__(NT) void k_gemm_f32(const float* __restrict__ X, int ldx, const float* __restrict__ W,
-                                                 int ldw, const float* __restrict__ bias, void* __restrict__ Y,
-                                                 int ldy, int M, int N, int K,
-                                                 const rb_k_row* __restrict__ skip_rows, int skip_T, OutMap om) {
-  gemm_mfma<float, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, true, false>(X, ldx, W, ldw, bias, Y, ldy, M, N, K,
-                                                                       skip_rows, skip_T, HeadArgs{}, om);
+  for (int t = threadIdx.x & 63; t < L; t += 64) src[rw.lens + t] = rw.src + (int64_t)t * d_in;
 }
 
 // ---------------------------------------------------------------- heads and split
@@ -1777,71 +1174,19 @@ __global__ __launch_bounds__(256) void k_split(const rb_k_row* __restrict__ rows
   }
 }
 
-inline rb_status launch_status() {
-  return hipGetLastError() == hipSuccess ? RB_OK : RB_EDEVICE;
-}
-
 inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
 
 }  // namespace
 
-namespace {
-
-// PERSIST: a grid of at most `cap` workgroups (a multiple of 8), each taking
-// every cap-th tile
-template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, bool PERSIST = false>
-void launch_gemm(hipStream_t s, const TI* x, int ldx, const TI* w, int ldw, const float* b, void* Y, int ldy,
-                 int M, int N, int K, int act, bool out_f32, const rb_k_row* skip_rows, int skip_T,
-                 unsigned cap = 0, OutMap om = OutMap{}) {
-  const unsigned tiles = (unsigned)(((M + BM - 1) / BM) * (N / BN));
-  const unsigned g = PERSIST ? std::min(tiles, cap) : tiles;
-  if constexpr (sizeof(TI) == 4) {
-#define RB_G(A)                                                                                                     \
-  hipLaunchKernelGGL((k_gemm_f32<BM, BN, WM, WN, NT, RB, S, ORDER, A>), dim3(g), dim3(NT), 0, s, x, ldx, w, ldw, b, \
-                     Y, ldy, M, N, K, skip_rows, skip_T, om)
-    if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU);
-    else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID);
-    else RB_G(RB_ACT_NONE);
-#undef RB_G
-  } else {
-#define RB_G(A, F)                                                                                             \
-  hipLaunchKernelGGL((k_gemm_bf16<BM, BN, WM, WN, NT, RB, S, ORDER, A, F, PERSIST>), dim3(g), dim3(NT), 0, s, x, ldx, w, \
-                     ldw, b, Y, ldy, M, N, K, om)
-    if (out_f32) {
-      if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU, true);
-      else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID, true);
-      else RB_G(RB_ACT_NONE, true);
-    } else {
-      if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU, false);
-      else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID, false);
-      else RB_G(RB_ACT_NONE, false);
-    }
-#undef RB_G
-  }
+// Runtime support (not part of the C ABI): the arena offset of every packed
+// token row of a sequence group.
+rb_status rb_token_rows(hipStream_t s, const rb_k_row* rows, int n_slots, int T, int64_t dense_len, int d_in,
+                        int64_t* src, int64_t n_src, int* err) {
+  if (n_slots < 1) return RB_OK;
+  hipLaunchKernelGGL(k_token_rows, dim3((unsigned)((n_slots + 3) / 4)), dim3(256), 0, s, rows, n_slots, T, dense_len, d_in,
+                     src, n_src, err);
+  return launch_status();
 }
-
-// bf16 operands, k-step BK bf16 values
-template <int BM, int BN, int WM, int WN, int NT, int BK, int S, int ORDER, bool PERSIST>
-void launch_gemm_bf16(hipStream_t s, const bf16_t* x, int ldx, const bf16_t* w, int ldw, const float* b, void* Y,
-                      int ldy, int M, int N, int K, int act, int out_f32, unsigned cap, OutMap om) {
-  launch_gemm<bf16_t, BM, BN, WM, WN, NT, BK * 2, S, ORDER, PERSIST>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act,
-                                                                    out_f32 != 0, nullptr, 0, cap, om);
-}
-
-// compute units of the current device (cached per device)
-unsigned device_cus() {
-  static std::atomic<int> cus[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  int c = cus[dev].load(std::memory_order_relaxed);
-  if (c <= 0) {
-    if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || c <= 0) c = 256;
-    cus[dev].store(c, std::memory_order_relaxed);
-  }
-  return (unsigned)c;
-}
-
-}  // namespace
 
 // ---------------------------------------------------------------- row map fill
 
@@ -2016,140 +1361,6 @@ rb_status rb_k_embbag(void* stream, const rb_k_row* rows, int32_t n_rows_total, 
   return launch_status();
 }
 
-namespace {
-rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
-                         void* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act, int32_t out_f32,
-                         OutMap om) {
-  if (M < 0 || N <= 0 || K <= 0 || (N % 128) || (K % G16_KALIGN) || ldx < K || ldw < K) return RB_EINVAL;
-  if ((ldx & 7) || (ldw & 7) || !X || !W || !b) return RB_EINVAL;
-  // operand byte offsets within a 256-row tile are 32-bit
-  if ((int64_t)ldx * 512 >= ((int64_t)1 << 31) || (int64_t)ldw * 512 >= ((int64_t)1 << 31)) return RB_EINVAL;
-  if (act != RB_ACT_NONE && act != RB_ACT_RELU && act != RB_ACT_SIGMOID) return RB_EINVAL;
-  if (M == 0) return RB_OK;
-  hipStream_t s = (hipStream_t)stream;
-  const bf16_t* x = (const bf16_t*)X;
-  const bf16_t* w = (const bf16_t*)W;
-  // Tile shape, k-step, stage count and tile order only change speed: every
-  // choice accumulates each output in the same k order with the same
-  // instruction (identical bits). The largest tile that still gives every CU a
-  // tile: 256 x 256 (k-step 64, 2 stages, 128 KB LDS, every row's k-step a
-  // whole 128-byte line) as 4 waves of 128 x 128 when there are at least two
-  // tiles per CU (half the fragment reads per flop of 8 waves of 64 x 128), as
-  // 8 waves of 64 x 128 when fewer (two waves per SIMD hide more of the single
-  // round's start and end), else 256 x 128 (8 waves of 64 x 64, k-step
-  // 64, 3 stages, 144 KB), else
-  // 128 x 128 (8 waves of 64 x 32, k-step 64, 4 stages, 128 KB), 128 x 64 (4
-  // waves of 64 x 32, 96 KB) or 64 x 64 (2 waves of 64 x 32, 64 KB). XCD-contiguous
-  // tile order when all of W fits in one XCD's L2 (each XCD then keeps its A
-  // row-blocks and W in its own L2); plain order otherwise (contiguous ranges
-  // would stream all of W through every XCD).
-  //
-  // With more 256 x 128 tiles than compute units, the grid is persistent (one
-  // workgroup per CU, each taking every CU-count-th tile) when K is a multiple of the
-  // stage count in k-steps: the operand loads then run on across tile
-  // boundaries, so a tile's first k-steps load during the previous tile's last
-  // steps and epilogue.
-  const int64_t rows256 = (M + 255) / 256;
-  const bool xcd = (int64_t)N * K * 2 <= (4 << 20);
-  const unsigned cus = device_cus() & ~7u;
-#define RB_PICK(BM, BN, WM, WN, NT, BK, S, P)                                                                   \
-  do {                                                                                                          \
-    if (xcd)                                                                                                    \
-      launch_gemm_bf16<BM, BN, WM, WN, NT, BK, S, 1, P>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act, out_f32, cus, om); \
-    else                                                                                                        \
-      launch_gemm_bf16<BM, BN, WM, WN, NT, BK, S, 0, P>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act, out_f32, cus, om); \
-  } while (0)
-  auto persist = [&](int bm, int bn, int bk, int st) {
-    const int64_t tiles = ((M + bm - 1) / bm) * (int64_t)(N / bn);
-    const int nk = K / bk;
-    return cus >= 8 && tiles > (int64_t)cus && nk >= st && nk % st == 0;
-  };
-  if (N % 256 == 0 && rows256 * (N / 256) >= 256) {
-    if (rows256 * (N / 256) >= 2 * (int64_t)cus)
-      RB_PICK(256, 256, 128, 128, 256, 64, 2, false);
-    else
-      RB_PICK(256, 256, 64, 128, 512, 64, 2, false);
-  } else if (rows256 * (N / 128) >= 256) {
-    if (persist(256, 128, 64, 3))
-      RB_PICK(256, 128, 64, 64, 512, 64, 3, true);
-    else
-      RB_PICK(256, 128, 64, 64, 512, 64, 3, false);
-  } else {
-    // fewer tiles than that: the k-loop's latency bounds a launch of a few
-    // batches, so the largest of 128 x 128, 128 x 64 and 64 x 64 tiles that
-    // still gives half the compute units a tile (512 x 1024 x 1728: 12.5 ->
-    // 8.7 us with 64 x 64; 2816 x 512 x 1024: 9.7 -> 7.3 us with 128 x 64)
-    const int64_t rows128 = (M + 127) / 128, half = std::max<int64_t>(cus / 2, 1);
-    if (rows128 * (N / 128) >= half)
-      RB_PICK(128, 128, 64, 32, 512, 64, 4, false);
-    else if (rows128 * (N / 64) >= half)
-      RB_PICK(128, 64, 64, 32, 256, 64, 4, false);
-    else
-      RB_PICK(64, 64, 64, 32, 128, 64, 4, false);
-  }
-#undef RB_PICK
-  return launch_status();
-}
-}  // namespace
-
-rb_status rb_k_gemm_bf16(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
-                         void* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act, int32_t out_f32) {
-  if (ldy < N || (ldy & 7) || ((uintptr_t)Y & 15) || !Y) return RB_EINVAL;
-  return gemm_bf16_impl(stream, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, out_f32, OutMap{});
-}
-
-rb_status rb_k_gemm_bf16_rows(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
-                              int32_t M, int32_t N, int32_t K, int32_t act, const rb_k_row* rows, int32_t d_out,
-                              float* out) {
-  if (!rows || !out || d_out < 1 || d_out > N) return RB_EINVAL;
-  return gemm_bf16_impl(stream, X, ldx, W, ldw, b, nullptr, N, M, N, K, act, 1, OutMap{rows, out, d_out});
-}
-
-namespace {
-rb_status gemm_f32_impl(void* stream, const float* X, int32_t ldx, const float* W, int32_t ldw, const float* b,
-                        float* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act,
-                        const rb_k_row* skip_rows, int32_t skip_T, OutMap om) {
-  if (M < 0 || N <= 0 || K <= 0 || (N % 64) || (K % G32_KALIGN) || ldx < K || ldw < K) return RB_EINVAL;
-  if ((ldx & 3) || (ldw & 3) || !X || !W || !b) return RB_EINVAL;
-  if (((uintptr_t)X & 15) || ((uintptr_t)W & 15)) return RB_EINVAL;
-  // operand byte offsets within a 64-row tile are 32-bit
-  if ((int64_t)ldx * 4 * G32_BM >= ((int64_t)1 << 31) || (int64_t)ldw * 4 * 64 >= ((int64_t)1 << 31)) return RB_EINVAL;
-  if (act != RB_ACT_NONE && act != RB_ACT_RELU && act != RB_ACT_SIGMOID) return RB_EINVAL;
-  if (skip_rows && (skip_T <= 0 || skip_T % G32_BM)) return RB_EINVAL;
-  if (M == 0) return RB_OK;
-  hipStream_t s = (hipStream_t)stream;
-  // 64 x 64 tiles (64 rows: the padding-token skip granularity), 4 waves of
-  // 32 x 32, k-step 16, 3 stages (24 KB LDS, six workgroups per CU). Small
-  // wave tiles keep the work per wave small, so the CUs stay evenly loaded when
-  // padding-token blocks leave holes in the grid (64 x 64 wave tiles measured
-  // up to 1.5x slower there). XCD-contiguous tile order when W fits in one
-  // XCD's L2 (each XCD then reads its X rows once; plain order measured 1.5x
-  // slower on sequence groups).
-  const bool xcd = (int64_t)N * K * 4 <= (4 << 20);
-  if (xcd)
-    launch_gemm<float, G32_BM, 64, 32, 32, 256, 64, 3, 1>(s, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, true, skip_rows,
-                                                          skip_T, 0, om);
-  else
-    launch_gemm<float, G32_BM, 64, 32, 32, 256, 64, 3, 0>(s, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, true, skip_rows,
-                                                          skip_T, 0, om);
-  return launch_status();
-}
-}  // namespace
-
-rb_status rb_k_gemm_f32(void* stream, const float* X, int32_t ldx, const float* W, int32_t ldw, const float* b,
-                        float* Y, int32_t ldy, int32_t M, int32_t N, int32_t K, int32_t act,
-                        const rb_k_row* skip_rows, int32_t skip_T) {
-  if (ldy < N || (ldy & 3) || ((uintptr_t)Y & 15) || !Y) return RB_EINVAL;
-  return gemm_f32_impl(stream, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, skip_rows, skip_T, OutMap{});
-}
-
-rb_status rb_k_gemm_f32_rows(void* stream, const float* X, int32_t ldx, const float* W, int32_t ldw, const float* b,
-                             int32_t M, int32_t N, int32_t K, int32_t act, const rb_k_row* rows, int32_t d_out,
-                             float* out) {
-  if (!rows || !out || d_out < 1 || d_out > N) return RB_EINVAL;
-  return gemm_f32_impl(stream, X, ldx, W, ldw, b, nullptr, N, M, N, K, act, nullptr, 0, OutMap{rows, out, d_out});
-}
-
 rb_status rb_k_head(void* stream, const rb_k_row* rows, int32_t n_rows_total, const void* H, int32_t ldh,
                     const void* w, float b, int32_t K, int32_t act, float* out) {
   if (n_rows_total < 0 || K < 1 || ldh < K || !rows || !H || !w || !out) return RB_EINVAL;
@@ -2164,46 +1375,6 @@ rb_status rb_k_head(void* stream, const rb_k_row* rows, int32_t n_rows_total, co
   else
     hipLaunchKernelGGL(k_head<RB_ACT_NONE>, dim3(g), dim3(256), 0, (hipStream_t)stream, rows, n_rows_total,
                        (const bf16_t*)H, ldh, (const bf16_t*)w, b, K, vec, out);
-  return launch_status();
-}
-
-rb_status rb_k_gemm_head(void* stream, const void* X, int32_t ldx, const void* W, int32_t ldw, const float* b,
-                         int32_t M, int32_t K, int32_t act, const rb_k_row* rows, const void* w_head, float b_head,
-                         int32_t head_act, float* out) {
-  if (M < 0 || K <= 0 || (K % G16_KALIGN) || ldx < K || ldw < K || (ldx & 7) || (ldw & 7)) return RB_EINVAL;
-  if (!X || !W || !b || !rows || !w_head || !out || ((uintptr_t)w_head & 15)) return RB_EINVAL;
-  if ((int64_t)ldx * 512 >= ((int64_t)1 << 31) || (int64_t)ldw * 512 >= ((int64_t)1 << 31)) return RB_EINVAL;
-  if (act != RB_ACT_NONE && act != RB_ACT_RELU && act != RB_ACT_SIGMOID) return RB_EINVAL;
-  if (head_act != RB_ACT_NONE && head_act != RB_ACT_SIGMOID) return RB_EINVAL;
-  if (M == 0) return RB_OK;
-  // 128 x 256 tiles (every row's 256 outputs in one workgroup), 8 waves of
-  // 64 x 64 (two per SIMD: 4 waves of 64 x 128 measured 16% slower), k-step
-  // 64, 3 stages; XCD-contiguous order (W is 256 x K bf16). With fewer such
-  // tiles than half the compute units (a launch of a few batches, bound by
-  // its k-loop's latency), 64 x 256 tiles of 8 waves of 64 x 32.
-  const bool small = (int64_t)(M + 127) / 128 < std::max<int64_t>(device_cus() / 2, 1);
-  const unsigned g = (unsigned)(small ? (M + 63) / 64 : (M + 127) / 128);
-  const HeadArgs ha{rows, (const bf16_t*)w_head, b_head, out};
-  hipStream_t s = (hipStream_t)stream;
-#define RB_GH(A, H)                                                                                                    \
-  do {                                                                                                                 \
-    if (small)                                                                                                         \
-      hipLaunchKernelGGL((k_gemm_head<64, 256, 64, 32, 512, 128, 3, 1, A, H>), dim3(g), dim3(512), 0, s,             \
-                         (const bf16_t*)X, ldx, (const bf16_t*)W, ldw, b, M, K, ha);                                   \
-    else                                                                                                               \
-      hipLaunchKernelGGL((k_gemm_head<128, 256, 64, 64, 512, 128, 3, 1, A, H>), dim3(g), dim3(512), 0, s,            \
-                         (const bf16_t*)X, ldx, (const bf16_t*)W, ldw, b, M, K, ha);                                   \
-  } while (0)
-  if (head_act == RB_ACT_SIGMOID) {
-    if (act == RB_ACT_RELU) RB_GH(RB_ACT_RELU, RB_ACT_SIGMOID);
-    else if (act == RB_ACT_SIGMOID) RB_GH(RB_ACT_SIGMOID, RB_ACT_SIGMOID);
-    else RB_GH(RB_ACT_NONE, RB_ACT_SIGMOID);
-  } else {
-    if (act == RB_ACT_RELU) RB_GH(RB_ACT_RELU, RB_ACT_NONE);
-    else if (act == RB_ACT_SIGMOID) RB_GH(RB_ACT_SIGMOID, RB_ACT_NONE);
-    else RB_GH(RB_ACT_NONE, RB_ACT_NONE);
-  }
-#undef RB_GH
   return launch_status();
 }
 

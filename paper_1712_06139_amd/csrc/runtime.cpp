@@ -44,6 +44,15 @@
 void rb_scrub_caches(hipStream_t stream, const void* buf, size_t bytes, unsigned* sink);
 // kernels.hip: sets n row-map entries to padding
 void rb_fill_padding_rows(hipStream_t stream, rb_k_row* rows, int64_t n);
+// kernels.hip: one layer of an fp32 model on split weights (X's rows gathered when src is given; the output
+// through the row map when out_rows is)
+rb_status rb_gemm_f32_split(hipStream_t s, const float* X, int ldx, const int64_t* src, int src_stride,
+                            int64_t src_len, int* err, const void* Wp, const float* b, float* Y, int ldy, int M, int N,
+                            int K, int act, const rb_k_row* skip_rows, int skip_T, const rb_k_row* out_rows, int d_out,
+                            float* out);
+// kernels.hip: the arena offset of every packed token row
+rb_status rb_token_rows(hipStream_t s, const rb_k_row* rows, int n_slots, int T, int64_t dense_len, int d_in,
+                        int64_t* src, int64_t n_src, int* err);
 // kernels.hip: the per-device address of the static scratch array (set up once
 // per device; nullptr before that succeeded)
 rb_status rb_static_scratch_setup(int device);
@@ -91,7 +100,7 @@ struct rb_ctx {
 
 struct DevLayer {
   int K = 0, N = 0, Kp = 0, Np = 0, act = 0;
-  void* w = nullptr;   // [Np, Kp] bf16 or fp32, zero padded
+  void* w = nullptr;   // [Np, Kp] zero padded: bf16, or fp32 split into bf16 parts in fragment order
   float* b = nullptr;  // [Np] zero padded
 };
 
@@ -328,10 +337,27 @@ rb_status upload_layer(rb_model* m, const rb_layer_desc& L, DevLayer& d, bool bf
     if ((st = dev_alloc(m, n * 2, &d.w)) != RB_OK) return st;
     if (!copy_h2d(m, d.w, h.data(), n * 2)) return RB_EDEVICE;
   } else {
-    std::vector<float> h(n, 0.f);
-    for (int j = 0; j < d.N; ++j) std::memcpy(&h[(size_t)j * d.Kp], L.w + (size_t)j * d.K, sizeof(float) * d.K);
-    if ((st = dev_alloc(m, n * 4, &d.w)) != RB_OK) return st;
-    if (!copy_h2d(m, d.w, h.data(), n * 4)) return RB_EDEVICE;
+    // each element as three bf16 parts that sum to it exactly (its first part
+    // is not rounded up to infinity); per 32 rows and 16 k values the parts one
+    // after another, in the order of a wave's 32 x 16 fragment
+    std::vector<uint16_t> h(n * 3, 0);
+    for (int j = 0; j < d.N; ++j)
+      for (int k = 0; k < d.K; ++k) {
+        uint16_t* e = &h[((size_t)(j / 32) * (d.Kp / 16) + k / 16) * 1536 + ((k / 8 % 2) * 32 + j % 32) * 8 + k % 8];
+        float r = L.w[(size_t)j * d.K + k];
+        for (int p = 0; p < 3; ++p) {
+          uint16_t v = host_f2bf(r);
+          if ((v & 0x7fff) == 0x7f80 && std::isfinite(r)) v = (uint16_t)(v - 1);
+          e[p * 512] = v;
+          if ((v & 0x7f80) == 0x7f80) break;
+          uint32_t u = (uint32_t)v << 16;
+          float f;
+          std::memcpy(&f, &u, 4);
+          r -= f;
+        }
+      }
+    if ((st = dev_alloc(m, n * 6, &d.w)) != RB_OK) return st;
+    if (!copy_h2d(m, d.w, h.data(), n * 6)) return RB_EDEVICE;
   }
   std::vector<float> hb(d.Np, 0.f);
   std::memcpy(hb.data(), L.b, sizeof(float) * d.N);
@@ -691,7 +717,17 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
   const bool pack = m->kind == RB_MODEL_SEQPOOL && s->opts.seq_pack && !bf16;
   const bool seq_skip = m->kind == RB_MODEL_SEQPOOL && !pack && q->bucket % 64 == 0;
   const int64_t Ml = pack ? tokens : M;  // rows of the layers
-  if (m->kind == RB_MODEL_RANKING) {
+  // fp32 models whose rows need no zero columns: the first layer reads the
+  // requests' rows (packed tokens through a map of their arena offsets, kept
+  // where the assembled rows would be) and nothing is assembled
+  const bool gather = !bf16 && m->kind != RB_MODEL_RANKING && m->d_in == Kp0 && (pack || m->kind == RB_MODEL_MLP);
+  const int64_t* src = nullptr;
+  if (gather) {
+    src = pack ? (const int64_t*)w->X : &w->rows->src;
+    if (pack)
+      RB_LAUNCH(s, st_h, "assemble", rb_token_rows(st_h, w->rows, (int)slots, q->bucket, dense_len, m->d_in,
+                                                   (int64_t*)w->X, Ml, s->err_dev));
+  } else  if (m->kind == RB_MODEL_RANKING) {
     auto emb = s->opts.emb_dedup ? rb_k_embbag_dedup : rb_k_embbag;
     RB_LAUNCH(s, st_h, "embbag", emb(hs, w->rows, (int)slots, lens, ids, ids_len, (const void* const*)m->tables_dev,
                                      m->n_tables, m->table_rows, m->emb_dim, dense, m->n_dense, w->X, Kp0, pad,
@@ -711,8 +747,17 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
   // a chain that ends in the split writes its last layer straight into the
   // requests' output rows (bit-identical to the layer and the split)
   const bool rows_out = !m->head_last && m->kind != RB_MODEL_SEQPOOL;
-  void* h = w->X;
+  const void* h = gather ? (const void*)dense : w->X;
   int ldh = Kp0;
+  // layer i of an fp32 model, to y or (null) to the requests' rows
+  auto gemm_f32 = [&](size_t i, const DevLayer& L, float* y) {
+    const bool g = gather && i == 0;
+    return rb_gemm_f32_split(st_h, (const float*)h, ldh, g ? src : nullptr,
+                             pack ? 1 : (int)(sizeof(rb_k_row) / sizeof(int64_t)), dense_len,
+                             g && !pack ? s->err_dev : nullptr, L.w, L.b, y, L.Np, (int)Ml, L.Np, L.Kp, L.act,
+                             seq_skip ? w->rows : nullptr, seq_skip ? q->bucket : 0, y ? nullptr : w->rows, m->d_out,
+                             out);
+  };
   for (size_t i = 0; i < nL - (tail ? 2 : 0) - (ghead ? 1 : 0); ++i) {
     const DevLayer& L = m->layers[i];
     const bool last = (i + 1 == nL) && !m->head_last;
@@ -722,15 +767,12 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
         RB_LAUNCH(s, st_h, "gemm_bf16", rb_k_gemm_bf16_rows(hs, h, ldh, L.w, L.Kp, L.b, (int)Ml, L.Np, L.Kp, L.act,
                                                             w->rows, m->d_out, out));
       else
-        RB_LAUNCH(s, st_h, "gemm_f32", rb_k_gemm_f32_rows(hs, (const float*)h, ldh, (const float*)L.w, L.Kp, L.b,
-                                                          (int)Ml, L.Np, L.Kp, L.act, w->rows, m->d_out, out));
+        RB_LAUNCH(s, st_h, "gemm_f32", gemm_f32(i, L, nullptr));
     } else if (bf16) {
       RB_LAUNCH(s, st_h, "gemm_bf16", rb_k_gemm_bf16(hs, h, ldh, L.w, L.Kp, L.b, y, L.Np, (int)Ml, L.Np, L.Kp, L.act,
                                                last ? 1 : 0));
     } else {
-      RB_LAUNCH(s, st_h, "gemm_f32", rb_k_gemm_f32(hs, (const float*)h, ldh, (const float*)L.w, L.Kp, L.b, (float*)y,
-                                             L.Np, (int)Ml, L.Np, L.Kp, L.act, seq_skip ? w->rows : nullptr,
-                                             seq_skip ? q->bucket : 0));
+      RB_LAUNCH(s, st_h, "gemm_f32", gemm_f32(i, L, (float*)y));
     }
     h = y;
     ldh = L.Np;

@@ -1,0 +1,144 @@
+"""fp32 model layers (bf16 matrix cores on exactly split operands) through
+rb_run_group, against fp64: every tile shape and its ragged edges, rows read
+from the request arena at any alignment, and infinite, NaN and huge values."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1712_06139_amd import rb
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = rb.Ctx(0)
+    yield c
+    c.destroy()
+
+
+def _layers(rng, dims):
+    ls = []
+    for i, (fi, fo) in enumerate(zip(dims[:-1], dims[1:])):
+        W = (rng.standard_normal((fo, fi)) / np.sqrt(fi)).astype(np.float32)
+        ls.append((W, rng.uniform(-0.5, 0.5, fo).astype(np.float32), "relu" if i + 2 < len(dims) else "none"))
+    return ls
+
+
+def _run(ctx, layers, X, shift=0, dense_len=None, pad=0.0, allowed=()):
+    """One group of single-row-block requests (64 rows each, batches of up to
+    4096 rows); `shift`: floats before the first row in the arena."""
+    M, d_in = X.shape
+    d_out = layers[-1][0].shape[0]
+    m = rb.Model(ctx, "mlp", "f32", layers)
+    s = rb.Sched(ctx, pad_value=pad)
+    q = rb.Queue(s, m, 4096, allowed)
+    first = np.arange(0, M, 64)
+    kr = np.zeros(len(first), rb.K_REQ_DTYPE)
+    kr["n_rows"] = np.minimum(64, M - first)
+    kr["dense_off"] = shift + first * d_in
+    kr["dense_end"] = kr["dense_off"] + kr["n_rows"] * d_in
+    kr["out_off"] = first * d_out
+    nb = (M + 4095) // 4096
+    kb = np.zeros(nb, rb.K_BATCH_DTYPE)
+    for b in range(nb):
+        real = min(4096, M - b * 4096)
+        kb[b] = (b * 64, (real + 63) // 64, b * 4096, min([a for a in allowed if a >= real], default=real), real, 0)
+    slots = int(kb["row_base"][-1] + kb["padded"][-1])
+    dense = torch.zeros(shift + M * d_in, device=DEV)
+    dense[shift:] = torch.from_numpy(X.reshape(-1)).to(DEV)
+    out = torch.full((M * d_out,), -7.0, device=DEV)
+    up = [torch.from_numpy(a.view(np.uint8)).to(DEV) for a in (kb, kr)]
+    torch.cuda.synchronize()
+    q.run_group(0, up[0], nb, up[1], len(kr), slots, 0, dense, dense.numel() if dense_len is None else dense_len, None,
+                0, None, 0, out, out.numel())
+    status = rb.lib().rb_sync(s.h)
+    y = out.cpu().numpy().reshape(M, d_out)
+    q.destroy()
+    s.destroy()
+    m.destroy()
+    return y, status
+
+
+def _ref(layers, X):
+    x = X.astype(np.float64)
+    with np.errstate(all="ignore"):
+        for i, (W, b, act) in enumerate(layers):
+            x = x @ W.astype(np.float64).T + b
+            x = (np.where(x > 0, x, 0) if act == "relu" else x).astype(np.float32).astype(np.float64)
+    return x
+
+
+def _err(y, ref):
+    return np.max(np.abs(y - ref) / np.maximum(np.abs(ref).max(axis=1, keepdims=True), 1e-30))
+
+
+# rows around the 32-, 64- and 128-row tiles; widths for each tile (N a multiple
+# of 64, 128, 256); 33000 rows x 512 and 66000 x 256 take the 128 x 256 tile on
+# 256 compute units, 8256 x 256 the 64 x 128 one. d_in not a multiple of 64 is
+# assembled first, the others are read from the arena, aligned or not.
+@pytest.mark.parametrize("M,dims,shift", [
+    (1, (64, 128, 16), 0), (31, (64, 64), 1), (33, (128, 40, 3), 2), (65, (100, 300, 70), 3), (127, (256, 1024, 32), 0),
+    (129, (320, 192), 1), (8256, (64, 256, 128), 3), (33000, (64, 512, 256), 1), (66000, (128, 256), 0)])
+def test_f32_layers_match_fp64(ctx, M, dims, shift):
+    rng = np.random.default_rng(M)
+    layers, X = _layers(rng, dims), rng.standard_normal((M, dims[0])).astype(np.float32)
+    y, status = _run(ctx, layers, X, shift)
+    assert status == rb.RB_OK
+    assert _err(y, _ref(layers, X)) <= 1e-5
+    # a row's bits do not depend on the rows it runs with, nor on its alignment
+    for r0, n in ((0, 1), (M // 2, min(40, M - M // 2)), (M - 1, 1)):
+        part, _ = _run(ctx, layers, X[r0:r0 + n], (shift + 1) % 4)
+        assert np.array_equal(part, y[r0:r0 + n])
+
+
+def test_f32_layer_exact_products(ctx):
+    # one-hot rows return weights exactly: no bits of an operand are lost
+    W = np.random.default_rng(1).standard_normal((64, 64)).astype(np.float32)
+    W[:, 5] *= np.float32(1e-30)
+    W[:, 6] *= np.float32(1e30)
+    y, _ = _run(ctx, [(W, np.zeros(64, np.float32), "none")], np.eye(64, dtype=np.float32))
+    assert np.array_equal(y, W.T)
+
+
+@pytest.mark.parametrize("M", [40, 33000])
+def test_f32_layers_non_finite_and_huge(ctx, M):
+    # rows with infinities, NaN and values whose products or bf16 roundings
+    # overflow give what fp32 arithmetic gives; their neighbours keep their bits
+    rng = np.random.default_rng(3)
+    W = np.abs(rng.standard_normal((512, 64))).astype(np.float32)
+    W[7, 3] = np.float32(3.4e38)
+    W[9, 2] = np.inf
+    layers = [(W, np.zeros(512, np.float32), "none")]
+    X = np.abs(rng.standard_normal((M, 64))).astype(np.float32)
+    X[:, 2:4] = np.float32(0.25)
+    base, _ = _run(ctx, layers, X)
+    X2 = X.copy()
+    X2[3, 10], X2[5, 11], X2[9, 12], X2[11, 0] = np.inf, np.nan, np.float32(3.4e38), np.float32(-np.inf)
+    X2[13, :] = np.float32(1e38)
+    y, _ = _run(ctx, layers, X2)
+    same = np.setdiff1d(np.arange(M), [3, 5, 9, 11, 13])
+    assert np.array_equal(y[same], base[same], equal_nan=True)
+    with np.errstate(all="ignore"):
+        ref = X2[:16].astype(np.float64) @ W.astype(np.float64).T
+        ref32 = ref.astype(np.float32)
+    fin = np.isfinite(ref32) & (np.abs(ref) < 1e38)
+    assert np.max(np.abs(y[:16][fin] - ref[fin]) / np.abs(ref[fin])) <= 1e-5
+    assert np.array_equal(np.isnan(y[:16]), np.isnan(ref32))
+    big = np.abs(ref) > 1e39
+    assert np.array_equal(y[:16][big], ref32[big])
+
+
+def test_f32_layers_rows_outside_the_arena(ctx):
+    # the last request's rows end past the declared arena: reported, and they
+    # contribute zeros; other rows are unchanged. NaN padding reaches nothing.
+    rng = np.random.default_rng(5)
+    layers, X = _layers(rng, (64, 128, 16)), rng.standard_normal((150, 64)).astype(np.float32)
+    good, status = _run(ctx, layers, X, pad=float("nan"), allowed=(256, 4096))
+    assert status == rb.RB_OK and np.isfinite(good).all()
+    y, status = _run(ctx, layers, X, dense_len=149 * 64 + 10)
+    assert status == rb.RB_ERANGE
+    assert np.array_equal(y[:149], good[:149])
+    assert _err(y[149:], _ref(layers, np.zeros((1, 64), np.float32))) <= 1e-5
