@@ -156,12 +156,14 @@ typedef struct {
    * Each model keeps one stream, assigned in order of first use, so its
    * chains stay in order; outputs do not depend on this setting. */
   int32_t n_streams;
-  /* Device mode, fp32 seqpool models: 1 packs the real tokens of a launch
-   * group's sequences into consecutive rows (no time padding) for the
-   * token-wise layers, then pools each sequence from its own rows (the
+  /* Device mode, fp32 seqpool models: the real tokens of a launch group's
+   * sequences are packed into consecutive rows (no time padding) for the
+   * token-wise layers, then each sequence is pooled from its own rows (the
    * sub-graph batching the paper's Batch/Unbatch operations allow, section on
-   * batching); 0 pads every sequence to its queue's bucket. Outputs are
-   * identical either way. */
+   * batching). Replays and the serving calls always do so. For rb_run_group
+   * and rb_run_group_static, whose callers name the packed rows, 1 does so and
+   * 0 pads every sequence to its queue's bucket. Outputs are identical either
+   * way. */
   int32_t seq_pack;
   /* Device mode, rb_sim_run: 0 runs the trace as a backlogged device would
    * (every launch window holds window_batches consecutive dispatched batches,
