@@ -8,7 +8,8 @@
 //
 //   route     per-batch exclusive prefix scans: which request row (or padding)
 //             every row is, where its input and output live (the paper's
-//             concatenation of input tensors, section 2.2.1, as an index map)
+//             concatenation of input tensors, section 2.2.1, as an index map),
+//             and where each of its embedding bags ends
 //   assemble  gather request rows into the padded batch tensor (optional
 //             fp32 -> bf16 cast), or
 //   embbag    sum-pool each row's embedding bags (ranking models)
@@ -35,91 +36,153 @@ namespace {
 // ---------------------------------------------------------------- route
 
 constexpr int ROUTE_MAX_ROWS = 4096;  // rows (sequence slots) per batch
+constexpr int ROUTE_NT = 512;         // threads per batch
 
-// Block-wide exclusive scan of one value per thread (256 threads); returns
-// the exclusive prefix and writes the block total to *total.
-__device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t* s_w, int64_t* total) {
+// Block-wide exclusive scan of one value per thread (ROUTE_NT threads);
+// returns the exclusive prefix and writes the block total to *total.
+template <typename T>
+__device__ __forceinline__ T block_exclusive_scan(T v, T* s_w, T* total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int64_t incl = v;
+  T incl = v;
   for (int o = 1; o < 64; o <<= 1) {
-    const int64_t u = __shfl_up(incl, o);
+    const T u = __shfl_up(incl, o);
     if (lane >= o) incl += u;
   }
   if (lane == 63) s_w[wid] = incl;
   __syncthreads();
-  int64_t off = 0;
-  for (int w = 0; w < wid; ++w) off += s_w[w];
-  *total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+  T off = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < ROUTE_NT / 64; ++w) {
+    if (w < wid) off += s_w[w];
+    tot += s_w[w];
+  }
+  *total = tot;
   __syncthreads();
   return off + incl - v;
 }
 
-// One workgroup per batch, all steps parallel over requests or rows:
+// Whether a batch's rows and requests lie inside the row map and the request
+// table (its rows are otherwise not written).
+__device__ __forceinline__ bool batch_in_range(const rb_k_batch& b, int max_rows, int n_rows_total, int n_reqs) {
+  return b.padded <= max_rows && b.n_req <= b.padded && b.real <= b.padded && b.padded >= 0 && b.n_req >= 0 &&
+         b.row_base >= 0 && (int64_t)b.row_base + b.padded <= n_rows_total && b.req_begin >= 0 &&
+         (int64_t)b.req_begin + b.n_req <= n_reqs;
+}
+
+// One workgroup per batch, all steps parallel over requests or rows. A launch
+// waits for one chain of dependent loads (the batch, its requests' row counts,
+// a row's request, its lengths), so:
 //  1. exclusive scan of the requests' row counts -> each request's first row
 //     (the concatenation offsets), and a row -> request map in LDS;
-//  2. per real row, its id count (ranking: sum of its bag lengths) or token
-//     count (seqpool: its sequence length), loaded in parallel;
+//  2. per real row, its request's descriptor, kept in registers for the first
+//     ROUTE_NT rows, and its id count (ranking: sum of its bag lengths) or token
+//     count (seqpool: its sequence length). The lengths are loaded 16 bytes at a
+//     time, 8 loads in flight (one length per load touched 64 lines 26 times
+//     a wave). When `ends` is given, ends[f n_rows_total + row] is the end of the
+//     row's bag f among its ids, so that the embedding kernel finds a bag with
+//     two loads;
 //  3. exclusive scan of those counts over the batch's rows; a row's first id
 //     (token) is its request's base plus the scan difference to the request's
 //     first row; each request is checked against its payload extent;
 //  4. the row map entries, then padding rows. A sequence's entry also names
 //     the row of its first token when the group's real tokens are packed
 //     (its request's first packed row, set by the host, plus the scan).
-__global__ __launch_bounds__(256) void k_route(int kind, const rb_k_batch* __restrict__ batches,
-                                               const rb_k_req* __restrict__ reqs, int n_reqs,
-                                               const int32_t* __restrict__ lens, int64_t lens_len, int d_in,
-                                               int d_out, int n_tables, rb_k_row* __restrict__ rows,
-                                               int n_rows_total, int64_t out_len, int* __restrict__ err) {
+// MAXR: the largest batch (512 rows take 7 KB of LDS, so that the workgroups
+// find a place beside another stream's GEMM; 4096 take 54). Beside other
+// streams' kernels 64 batches of 512 rows take 11.1 us at least, against 12.4
+// without the ends; with a GEMM's worth of LDS for coalesced staging of the
+// lengths it was 16.8.
+// fill: the rows that no batch in range covers are set to padding too: each
+// batch's workgroup sets those from its end to the next batch's start (the
+// first one also those before it; without any, the first workgroup all).
+template <int MAXR>
+__global__ __launch_bounds__(ROUTE_NT) void k_route(int kind, const rb_k_batch* __restrict__ batches, int n_batches,
+                                                    const rb_k_req* __restrict__ reqs, int n_reqs,
+                                                    const int32_t* __restrict__ lens, int64_t lens_len, int d_in,
+                                                    int d_out, int n_tables, rb_k_row* __restrict__ rows,
+                                                    int n_rows_total, int64_t out_len, int32_t* __restrict__ ends,
+                                                    int fill, int* __restrict__ err) {
   const rb_k_batch b = batches[blockIdx.x];
   const int tid = threadIdx.x;
-  __shared__ int s_first[ROUTE_MAX_ROWS + 1];   // first row of request i (batch-relative)
-  __shared__ int s_req[ROUTE_MAX_ROWS];         // request of row p
-  __shared__ int64_t s_ex[ROUTE_MAX_ROWS + 1];  // exclusive scan of per-row id/token counts
-  __shared__ unsigned char s_bad[ROUTE_MAX_ROWS];
-  __shared__ int64_t s_w[4];
-  // the batch's rows and requests must lie inside the row map and the
-  // request table (its rows are then left as they are)
-  if (b.padded > ROUTE_MAX_ROWS || b.n_req > b.padded || b.real > b.padded || b.padded < 0 || b.n_req < 0 ||
-      b.row_base < 0 || (int64_t)b.row_base + b.padded > n_rows_total || b.req_begin < 0 ||
-      (int64_t)b.req_begin + b.n_req > n_reqs) {
-    if (tid == 0) *err = 1;
-    return;
+  __shared__ uint16_t s_first[MAXR + 1];   // first row of request i (batch-relative)
+  __shared__ uint16_t s_req[MAXR];         // request of row p
+  __shared__ int64_t s_ex[MAXR + 1];       // exclusive scan of per-row id/token counts
+  __shared__ unsigned char s_bad[MAXR];
+  __shared__ int64_t s_w[ROUTE_NT / 64];
+  __shared__ int s_w32[ROUTE_NT / 64];
+  __shared__ int s_desc_bad, s_next, s_prev;
+  const rb_k_row none = {-1, 0, -1, -1};
+  const bool in_range = batch_in_range(b, MAXR, n_rows_total, n_reqs);  // uniform
+  if (tid == 0) {
+    s_desc_bad = 0;
+    s_next = n_rows_total;
+    s_prev = 0;
+    if (!in_range) *err = 1;
   }
-  // 1. request offsets
-  __shared__ int s_desc_bad;
-  if (tid == 0) s_desc_bad = 0;
   __syncthreads();
-  int64_t carry = 0;
-  for (int base = 0; base < b.n_req; base += 256) {
+  if (fill) {
+    // s_next: where the rows that another batch covers or fills start after
+    // this one's end (of empty batches at one row the last in the list fills);
+    // s_prev: whether any batch in range comes before it
+    const int end = in_range ? b.row_base + b.padded : 0;
+    for (int i = tid; i < n_batches; i += ROUTE_NT) {
+      const rb_k_batch o = batches[i];
+      if (i == (int)blockIdx.x || !batch_in_range(o, MAXR, n_rows_total, n_reqs)) continue;
+      if (o.row_base > end || (o.row_base == end && (o.padded > 0 || i > (int)blockIdx.x)))
+        atomicMin(&s_next, o.row_base);
+      else if (o.row_base < end && o.row_base + o.padded > end)
+        atomicMin(&s_next, end);
+      if (o.row_base < b.row_base || (o.row_base == b.row_base && i < (int)blockIdx.x) || !in_range) s_prev = 1;
+    }
+    __syncthreads();
+    if (in_range) {
+      for (int r = end + tid; r < s_next; r += ROUTE_NT) rows[r] = none;
+      if (!s_prev)
+        for (int r = tid; r < b.row_base; r += ROUTE_NT) rows[r] = none;
+    } else if (!s_prev && blockIdx.x == 0) {
+      for (int r = tid; r < n_rows_total; r += ROUTE_NT) rows[r] = none;
+    }
+  }
+  if (!in_range) return;
+  // 1. request offsets
+  int s = 0;
+  for (int base = 0; base < b.n_req; base += ROUTE_NT) {
     const int i = base + tid;
-    const int n = i < b.n_req ? reqs[b.req_begin + i].n_rows : 0;
-    if (i < b.n_req && n < 1) s_desc_bad = 1;  // every request has >= 1 row
-    int64_t tot;
-    const int64_t ex = block_exclusive_scan(n, s_w, &tot);
-    if (i < b.n_req) {
-      s_first[i] = (int)(carry + ex);
+    int n = i < b.n_req ? reqs[b.req_begin + i].n_rows : 0;
+    if (i < b.n_req && (n < 1 || n > MAXR)) {  // every request has >= 1 row
+      s_desc_bad = 1;
+      n = 0;
+    }
+    int tot;
+    const int ex = block_exclusive_scan(n, s_w32, &tot);
+    if (i < b.n_req && s + ex <= MAXR) {
+      s_first[i] = (uint16_t)(s + ex);
       s_bad[i] = 0;
     }
-    carry += tot;
+    s += tot;
   }
-  if (tid == 0) s_first[b.n_req] = (int)carry;
   __syncthreads();
-  const int s = (int)carry;
-  if (s > b.padded || s_desc_bad) {
+  if (s > b.padded || s_desc_bad) {  // uniform
     if (tid == 0) *err = 1;
+    if (fill)
+      for (int p = tid; p < b.padded; p += ROUTE_NT) rows[b.row_base + p] = none;
     return;
   }
-  for (int i = tid; i < b.n_req; i += 256)
-    for (int p = s_first[i]; p < s_first[i + 1]; ++p) s_req[p] = i;
+  if (tid == 0) s_first[b.n_req] = (uint16_t)s;
+  __syncthreads();
+  for (int i = tid; i < b.n_req; i += ROUTE_NT)
+    for (int p = s_first[i]; p < s_first[i + 1]; ++p) s_req[p] = (uint16_t)i;
   __syncthreads();
   // 2 + 3. per-row counts and their scan
-  carry = 0;
-  for (int base = 0; base < s; base += 256) {
+  rb_k_req rq0 = {};  // the descriptor of row tid's request
+  int64_t carry = 0;
+  for (int base = 0; base < s; base += ROUTE_NT) {
     const int p = base + tid;
     int64_t c = 0;
     if (p < s) {
       const int i = s_req[p];
-      const rb_k_req& rq = reqs[b.req_begin + i];
+      const rb_k_req rq = reqs[b.req_begin + i];
+      if (base == 0) rq0 = rq;
       const int e = p - s_first[i];
       // a request whose output rows would lie outside the output, or whose bag
       // or sequence lengths outside the lens arena, is rejected
@@ -129,25 +192,39 @@ __global__ __launch_bounds__(256) void k_route(int kind, const rb_k_batch* __res
                             (nl == 0 || (rq.lens_off >= 0 && rq.lens_off + nl <= lens_len));
       if (!in_arena) {
         s_bad[i] = 1;
-      } else if (kind == RB_MODEL_MLP) {
       } else if (kind == RB_MODEL_RANKING) {
+        typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
         const int32_t* l = lens + rq.lens_off + (int64_t)e * n_tables;
-        // the flag is kept in a register so that the unrolled loads are all
-        // issued before the first one is used
+        int32_t* en = ends ? ends + b.row_base + p : nullptr;
         bool neg = false;
-#pragma unroll 8
-        for (int f = 0; f < n_tables; ++f) {
-          const int v = l[f];
-          neg |= v < 0;
-          c += v;
+        for (int f0 = 0; f0 < n_tables; f0 += 32) {
+          int v[32];
+#pragma unroll
+          for (int u = 0; u < 32; u += 4) {
+            const int f = f0 + u;
+            if (f + 4 <= n_tables) {
+              const i32x4_any q = *(const i32x4_any*)(l + f);
+              v[u] = q[0]; v[u + 1] = q[1]; v[u + 2] = q[2]; v[u + 3] = q[3];
+            } else {
+#pragma unroll
+              for (int k = 0; k < 4; ++k) v[u + k] = f + k < n_tables ? l[f + k] : 0;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 32; ++u) {
+            neg |= v[u] < 0;
+            c += v[u];
+            if (en && f0 + u < n_tables) en[(int64_t)(f0 + u) * n_rows_total] = (int32_t)c;
+          }
         }
-        if (neg) s_bad[i] = 1;
-      } else {
+        if (neg || c > INT32_MAX) s_bad[i] = 1;
+      } else if (kind == RB_MODEL_SEQPOOL) {
         const int v = lens[rq.lens_off + e];
         if (v < 1 || v > b.seq_T) s_bad[i] = 1;
         c = v;
       }
     }
+    if (kind == RB_MODEL_MLP) continue;
     int64_t tot;
     const int64_t ex = block_exclusive_scan(c, s_w, &tot);
     if (p < s) s_ex[p] = carry + ex;
@@ -155,27 +232,19 @@ __global__ __launch_bounds__(256) void k_route(int kind, const rb_k_batch* __res
   }
   if (tid == 0) s_ex[s] = carry;
   __syncthreads();
-  for (int i = tid; i < b.n_req; i += 256) {
-    const rb_k_req& rq = reqs[b.req_begin + i];
-    const int n = s_first[i + 1] - s_first[i];
-    const int64_t cnt = s_ex[s_first[i + 1]] - s_ex[s_first[i]];
-    bool ok = !s_bad[i] && n == rq.n_rows;
-    if (kind == RB_MODEL_SEQPOOL) ok = ok && cnt * d_in == rq.dense_end - rq.dense_off;
-    else ok = ok && (int64_t)n * d_in == rq.dense_end - rq.dense_off;
-    if (kind == RB_MODEL_RANKING) ok = ok && cnt == rq.ids_end - rq.ids_off;
-    if (!ok) *err = 1;
-    s_bad[i] = ok ? 0 : 1;
-  }
-  __syncthreads();
   // 4. row entries
-  for (int p = tid; p < b.padded; p += 256) {
-    rb_k_row rw;
+  for (int p = tid; p < b.padded; p += ROUTE_NT) {
+    rb_k_row rw = none;
     if (p < s) {
-      const int i = s_req[p];
-      const rb_k_req& rq = reqs[b.req_begin + i];
-      const int e = p - s_first[i];
-      const bool ok = !s_bad[i];
-      const int64_t within = s_ex[p] - s_ex[s_first[i]];
+      const int i = s_req[p], p0 = s_first[i], p1 = s_first[i + 1];
+      const rb_k_req rq = p == tid ? rq0 : reqs[b.req_begin + i];
+      const int e = p - p0;
+      const int64_t cnt = kind == RB_MODEL_MLP ? 0 : s_ex[p1] - s_ex[p0];
+      const int64_t within = kind == RB_MODEL_MLP ? 0 : s_ex[p] - s_ex[p0];
+      bool ok = !s_bad[i];
+      ok = ok && (kind == RB_MODEL_SEQPOOL ? cnt : (int64_t)(p1 - p0)) * d_in == rq.dense_end - rq.dense_off;
+      if (kind == RB_MODEL_RANKING) ok = ok && cnt == rq.ids_end - rq.ids_off;
+      if (!ok) *err = 1;
       if (kind == RB_MODEL_SEQPOOL) {
         rw.src = ok ? rq.dense_off + within * d_in : -1;
         rw.aux = ok ? s_ex[p + 1] - s_ex[p] : 0;
@@ -186,11 +255,6 @@ __global__ __launch_bounds__(256) void k_route(int kind, const rb_k_batch* __res
         rw.lens = (kind == RB_MODEL_RANKING && ok) ? rq.lens_off + (int64_t)e * n_tables : -1;
       }
       rw.out = ok ? rq.out_off + (int64_t)e * d_out : -1;  // a rejected request's rows are not returned
-    } else {
-      rw.src = -1;
-      rw.aux = 0;
-      rw.lens = -1;
-      rw.out = -1;
     }
     rows[b.row_base + p] = rw;
   }
@@ -337,172 +401,227 @@ __global__ __launch_bounds__(256) void k_assemble(const rb_k_row* __restrict__ r
 
 constexpr int EMB_DIM = 64;       // one table row = 128 bytes of bf16
 constexpr int MAX_TABLES = 64;
-constexpr int EMB_SLICES = MAX_TABLES;  // table slices: one table each (up to MAX_TABLES)
-constexpr int EMB_CHUNK = 8;      // ids loaded (one per lane of a group) and gathers issued per round
-static_assert(EMB_CHUNK <= 8, "each of a group's 8 lanes loads one id of a chunk");
-// (4 ids per round measured 4% slower; 16 or 24, two or three per lane, 1.5x
-// and 1.7x slower; fewer workgroups per CU, capped through LDS, 1.25x to 2.8x
-// slower: the gather wants every load in flight the registers can hold)
+constexpr int EMB_CHUNK = 8;      // ids loaded (one per lane of a group) per round
 
-// One 8-lane group per (row, bag); lane l8 owns dims [8 l8, 8 l8 + 8) of the
-// 64-dim table rows. The grid is slice-major: workgroups [x nrb, (x + 1) nrb)
-// serve table slice x (tables x, x + n_slices, ...; with one table per slice,
-// table x) for rpw consecutive rows each, so at any time the whole chip
+// One 8-lane group per bag; lane l8 owns dims [8 l8, 8 l8 + 8) of the 64-dim
+// table rows. The grid is table-major: workgroups [t nrb, (t + 1) nrb) serve
+// table t for 32 ROUNDS consecutive rows each, so at any time the whole chip
 // gathers from one or two tables and every XCD's L2 and the Infinity Cache
-// hold their hot rows (all tables at once per row measured 1.5x slower, 4 or
-// 8 slices 1.2x slower).
-// A group finds its bag in the row's flat id list (bag after bag) with an
-// 8-lane sum of the preceding bag lengths; the row-map entry takes one round
-// trip and all the lengths one more (loaded one after another, as a loop that
-// adds each length as it arrives compiles, they took up to five: the kernel
-// was 4-5% slower on one box). The workgroup's 32 bags are then
-// ranked by length through LDS and the group of rank p walks the bag of rank
-// p, so the 8 bags of a wave have similar lengths and its gather instructions
-// keep most lanes busy (uniform 1..20-id bags: 50 gather instructions per
-// workgroup instead of 73; 2-3% faster). A bag is walked EMB_CHUNK ids at a
-// time: lane i loads id c + i, the ids are broadcast within the group and all
-// EMB_CHUNK gathers are issued before any is added. Sums are fp32 in id order
-// (a fixed order that depends on the bag only), stored as bf16. The workgroups
-// of slice 0 also write the rows' dense features and zero tails.
-// Reads stay inside the ids arena and the tables: an id position past the
-// arena or an id outside its table sets *err = 1 and contributes nothing.
-__global__ __launch_bounds__(256) void k_embbag(const rb_k_row* __restrict__ rows, int n_rows,
-                                                const int32_t* __restrict__ lens,
-                                                const int32_t* __restrict__ ids, int64_t ids_len,
-                                                const bf16_t* const* __restrict__ tables, int n_tables,
-                                                int64_t table_rows, const float* __restrict__ dense,
-                                                int n_dense, bf16_t* __restrict__ X, int ldx, int n_slices,
-                                                int gpr, int rpw, float pad, int* __restrict__ err) {
-  const int nrb = gridDim.x / n_slices;  // row blocks per slice
-  const int x = blockIdx.x / nrb;
-  const int r0 = (blockIdx.x - x * nrb) * rpw;
-  const int tid = threadIdx.x, g = tid >> 3, l8 = tid & 7;
-  const int gbase = (tid & 63) & ~7;  // this group's first lane in the wave
-  const int demb = n_tables * EMB_DIM;
-  // 1. group g's own bag: its length (-1: no bag, -2: a padding row) and its
-  //    first id's position in the ids arena
-  __shared__ int s_key[32];
-  __shared__ int s_bag[32], s_len[32];
-  __shared__ int64_t s_id0[32];
+// hold their hot rows (all tables at once per row measured 1.5x slower, 4 or 8
+// tables 1.2x slower).
+//
+// The kernel is bound by its chains of dependent loads and its instructions
+// before memory: with every id the same row (all gathers in L1) a workgroup per
+// 32 bags, ranked through LDS, took 104 us of the 140 us it took on Zipf ids
+// (32768 rows x 26 bags of 1..20 ids; 64 bytes a clock and compute unit, what L1
+// and L2 return to 32 waves of 8 gathers each, would be 37 us). Now 105 us on
+// Zipf ids and 63 us on one row, at 7 waves per SIMD (72 registers; at 5 waves
+// 115 us).
+// A wave takes the bags of 8 ROUNDS rows, bag i in lane i first:
+//  - a bag's place among its row's ids comes from the routing step (`ends`:
+//    two loads per bag; without it, from an 8-lane sum of the preceding bag
+//    lengths);
+//  - the lanes rank the bags by length (six ballots on a capped key) and the
+//    wave walks 8 of them at a time, longest first: the bags of a round then have
+//    similar lengths, and the longest bounds the round's loop;
+//  - lane i of a group loads and checks id c + i of a chunk and turns it into a
+//    byte offset into the table, out of range for an id that is invalid or past
+//    the bag; the offset is broadcast and a buffer load returns zeros for it
+//    (BIG: tables of 4 GiB or more, with 64-bit addresses and a predicate). The
+//    next chunk's or round's ids load during a chunk's gathers;
+//  - a chunk that the longest bag ends in gathers 4, 2 and 1 ids.
+// Sums are fp32 in id order (a fixed order that depends on the bag only),
+// stored as bf16. The workgroups of table 0 also write the rows' dense features
+// and zero tails. Reads stay inside the ids arena and the tables: an id
+// position outside the arena or an id outside its table sets *err = 1 and
+// contributes nothing.
+template <int ROUNDS, bool BIG>
+__global__ __launch_bounds__(256, ROUNDS == 1 ? 8 : 7) void k_embbag(const rb_k_row* __restrict__ rows, int n_rows,
+                                                   const int32_t* __restrict__ lens,
+                                                   const int32_t* __restrict__ ends,
+                                                   const int32_t* __restrict__ ids, int64_t ids_len,
+                                                   const bf16_t* const* __restrict__ tables, int n_tables,
+                                                   int64_t table_rows, const float* __restrict__ dense,
+                                                   int n_dense, bf16_t* __restrict__ X, int ldx, float pad,
+                                                   int* __restrict__ err) {
+  constexpr int NB = 8 * ROUNDS;         // bags per wave
+  const int nrb = gridDim.x / n_tables;  // row blocks per table
+  const int t = blockIdx.x / nrb;
+  const int rb0 = (blockIdx.x - t * nrb) * 4 * NB;  // the workgroup's first row
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 3, l8 = lane & 7;
+  const int r0 = __builtin_amdgcn_readfirstlane(rb0 + (tid >> 6) * NB);
+  auto from = [](int v, int src_lane) { return __builtin_amdgcn_ds_bpermute(src_lane * 4, v); };
+  // a position in the ids arena (one outside it stays outside for the whole bag)
+  typedef typename std::conditional<BIG, int64_t, uint32_t>::type pos_t;
+  const pos_t n_ids = (pos_t)ids_len;
+  auto to_pos = [&](int64_t p) { return BIG ? (pos_t)p : (p >= 0 && p <= ids_len ? (pos_t)p : (pos_t)n_ids); };
+  // 1. lane i: bag i's length (-1: no bag, -2: a padding row) and its first
+  //    id's position in the ids arena
   int L = -1;
-  int64_t id0 = 0;
-  {
-    const int row = r0 + g / gpr, t = x + n_slices * (g % gpr);
-    if (g < rpw * gpr && row < n_rows && t < n_tables) {
-      // the 32-byte entry as two 16-byte loads issued together (the empty asm
-      // uses the second half here, so that its load is not moved after the
-      // test of the first half and waited for separately)
-      const u32x4_t* re = (const u32x4_t*)(rows + row);
-      const u32x4_t e0 = re[0], e1 = re[1];
-      asm volatile("" ::"v"(e1.x), "v"(e1.y));
-      rb_k_row rw;
-      rw.src = (int64_t)((uint64_t)e0.x | ((uint64_t)e0.y << 32));
-      rw.aux = (int64_t)((uint64_t)e0.z | ((uint64_t)e0.w << 32));
-      rw.lens = (int64_t)((uint64_t)e1.x | ((uint64_t)e1.y << 32));
-      if (rw.src < 0) {
-        L = -2;
-      } else {
-        // lane l8 loads the lengths of tables l8, l8 + 8, ... below t and
-        // the bag's own length, all issued before any is used (a loop that
-        // adds each length as it arrives waits for every load in turn)
-        int v[MAX_TABLES / 8];
-#pragma unroll
-        for (int u = 0; u < MAX_TABLES / 8; ++u) {
-          const int f = l8 + 8 * u;
-          v[u] = f < t ? lens[rw.lens + f] : 0;
-        }
-        L = lens[rw.lens + t];
-        int pre = 0;
-#pragma unroll
-        for (int u = 0; u < MAX_TABLES / 8; ++u) pre += v[u];
-        pre += __shfl_xor(pre, 1);
-        pre += __shfl_xor(pre, 2);
-        pre += __shfl_xor(pre, 4);
-        id0 = rw.aux + pre;
-      }
+  pos_t pos = 0;
+  if (ends) {
+    if (lane < NB && r0 + lane < n_rows) {
+      const int row = r0 + lane;
+      const int e1 = ends[(int64_t)t * n_rows + row], e0 = t ? ends[(int64_t)(t - 1) * n_rows + row] : 0;
+      const int64_t src = rows[row].src, aux = rows[row].aux;
+      L = src < 0 ? -2 : e1 - e0;
+      pos = to_pos(aux + e0);
     }
-  }
-  // 2. the workgroup's 32 bags ranked longest first (ties by group), and
-  //    group p takes the bag of rank p: the 8 bags of a wave then have
-  //    similar lengths, so its gather instructions keep most lanes busy
-  if (l8 == 0) s_key[g] = L;
-  __syncthreads();
-  {
-    int rank = 0;
-    for (int h = l8; h < 32; h += 8) {
-      const int k = s_key[h];
-      rank += (k > L || (k == L && h < g)) ? 1 : 0;
-    }
-    rank += __shfl_xor(rank, 1);
-    rank += __shfl_xor(rank, 2);
-    rank += __shfl_xor(rank, 4);
-    if (l8 == 0) {
-      s_bag[rank] = g;
-      s_len[rank] = L;
-      s_id0[rank] = id0;
-    }
-  }
-  __syncthreads();
-  const int b = s_bag[g];
-  L = s_len[g];
-  id0 = s_id0[g];
-  // 3. the bag's walk
-  if (L != -1) {
-    const int row = r0 + b / gpr, t = x + n_slices * (b % gpr);
-    u32x4_t o;
-    if (L == -2) {
-      const uint32_t p = f2bf(pad);
-      o = (u32x4_t){p | (p << 16), p | (p << 16), p | (p << 16), p | (p << 16)};
-    } else {
-      const bf16_t* tab = tables[t];
-      float acc[8];
+  } else {
+    for (int i = 0; i < ROUNDS; ++i) {
+      const int row = r0 + 8 * i + g;
+      int len = -1;
+      pos_t p = 0;
+      if (row < n_rows) {
+        const rb_k_row rw = rows[row];
+        if (rw.src < 0) {
+          len = -2;
+        } else {
+          // lane l8 loads the lengths of tables l8, l8 + 8, ... below t and
+          // the bag's own length, all issued before any is used
+          int v[MAX_TABLES / 8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-      // lane i's id of chunk c (-1: past the bag or outside the ids arena)
-      auto chunk_id = [&](int c) {
-        const int64_t pos = id0 + c + l8;
-        return (c + l8 < L && pos >= 0 && pos < ids_len) ? ids[pos] : -1;
-      };
-      int nxt = chunk_id(0);
-      for (int c = 0; c < L; c += EMB_CHUNK) {
-        const int my = nxt;
-        nxt = chunk_id(c + EMB_CHUNK);  // the next chunk's ids load during this chunk's gathers
-        u32x4_t q[EMB_CHUNK];
-#pragma unroll
-        for (int u = 0; u < EMB_CHUNK; ++u) {
-          const int id = __shfl(my, gbase + u);
-          q[u] = (u32x4_t){0u, 0u, 0u, 0u};
-          if (c + u < L) {
-            if ((uint64_t)(int64_t)id < (uint64_t)table_rows)
-              q[u] = *(const u32x4_t*)(tab + (int64_t)id * EMB_DIM + l8 * 8);
-            else
-              *err = 1;
+          for (int u = 0; u < MAX_TABLES / 8; ++u) {
+            const int f = l8 + 8 * u;
+            v[u] = f < t ? lens[rw.lens + f] : 0;
           }
-        }
+          len = lens[rw.lens + t];
+          int pre = 0;
 #pragma unroll
-        for (int u = 0; u < EMB_CHUNK; ++u) {
-          acc[0] += bf2f(q[u].x & 0xffffu); acc[1] += bf2f(q[u].x >> 16);
-          acc[2] += bf2f(q[u].y & 0xffffu); acc[3] += bf2f(q[u].y >> 16);
-          acc[4] += bf2f(q[u].z & 0xffffu); acc[5] += bf2f(q[u].z >> 16);
-          acc[6] += bf2f(q[u].w & 0xffffu); acc[7] += bf2f(q[u].w >> 16);
+          for (int u = 0; u < MAX_TABLES / 8; ++u) pre += v[u];
+          pre += __shfl_xor(pre, 1);
+          pre += __shfl_xor(pre, 2);
+          pre += __shfl_xor(pre, 4);
+          p = to_pos(rw.aux + pre);
         }
       }
-      o.x = pack2(acc[0], acc[1]);
-      o.y = pack2(acc[2], acc[3]);
-      o.z = pack2(acc[4], acc[5]);
-      o.w = pack2(acc[6], acc[7]);
+      const int a = __shfl(len, l8 * 8);
+      const pos_t b = __shfl(p, l8 * 8);
+      if (g == i) {
+        L = a;
+        pos = b;
+      }
     }
-    *(u32x4_t*)(X + (int64_t)row * ldx + t * EMB_DIM + l8 * 8) = o;
   }
-  if (x == 0) {
-    // the dense features and zero tail (columns demb .. ldx, a multiple of 8
+  // 2. ranked longest first (ties by row; lengths past 60 count as equal): bag
+  //    of rank p in lane p
+  int row_of = lane;
+  if (ROUNDS > 1) {
+    const int key = min(L, 60) + 2;
+    uint32_t gt = 0, eq = NB < 32 ? (1u << (NB & 31)) - 1u : 0xffffffffu;
+#pragma unroll
+    for (int bit = 5; bit >= 0; --bit) {
+      const bool one = (key >> bit) & 1;
+      const uint32_t b = (uint32_t)__ballot(one);
+      if (!one) gt |= eq & b;
+      eq &= one ? b : ~b;
+    }
+    const int to = 4 * (lane < NB ? __popc(gt) + __popc(eq & ((1u << (lane & 31)) - 1u)) : lane);
+    L = __builtin_amdgcn_ds_permute(to, L);
+    row_of = __builtin_amdgcn_ds_permute(to, lane);
+    if constexpr (BIG)
+      pos = (pos_t)(((uint64_t)(uint32_t)__builtin_amdgcn_ds_permute(to, (int)((uint64_t)pos >> 32)) << 32) |
+                    (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)pos));
+    else
+      pos = (pos_t)__builtin_amdgcn_ds_permute(to, (int)pos);
+  }
+  // 3. the walks
+  const bf16_t* tab = tables[t];
+  constexpr uint32_t NONE = 0xffffff00u;  // past every table that is not BIG
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)tab, 0, BIG ? 0 : (int)(uint32_t)(table_rows * EMB_DIM * 2),
+                                                      0x00020000);
+  const auto irsrc = __builtin_amdgcn_make_buffer_rsrc((void*)ids, 0, BIG ? 0 : (int)(uint32_t)(ids_len * 4), 0x00020000);
+  const int gsel = (lane & ~7) * 4;  // this group's first lane, as a permute address
+  // this lane's id of chunk c of a bag as a byte offset into the table (BIG:
+  // the id, or -1)
+  auto chunk_off = [&](int bL, pos_t bpos, int c) -> uint32_t {
+    const int j = c + l8;
+    uint32_t o = BIG ? 0xffffffffu : NONE;
+    if (j < bL) {
+      const pos_t p = bpos + (pos_t)j;
+      int id = -1;
+      if constexpr (BIG) {
+        if (p >= 0 && p < n_ids) id = ids[p];
+      } else {
+        if (p < n_ids) id = (int)__builtin_amdgcn_raw_buffer_load_b32(irsrc, (int)(p * 4), 0, 0);
+      }
+      if (BIG ? (uint64_t)(int64_t)id < (uint64_t)table_rows : (uint32_t)id < (uint32_t)table_rows)
+        o = BIG ? (uint32_t)id : (uint32_t)id * (EMB_DIM * 2);
+      else
+        *err = 1;
+    }
+    return o;
+  };
+  int bL = __shfl(L, g);
+  pos_t bpos = __shfl(pos, g);
+  uint32_t nxt = chunk_off(bL, bpos, 0);
+  for (int i = 0; i < ROUNDS; ++i) {
+    int Lw = bL;  // the round's longest bag
+    Lw = max(Lw, __shfl_xor(Lw, 8));
+    Lw = max(Lw, __shfl_xor(Lw, 16));
+    Lw = __builtin_amdgcn_readfirstlane(max(Lw, __shfl_xor(Lw, 32)));
+    const int brow = from(row_of, i * 8 + g), myL = bL;
+    float acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0.f;
+    auto gather = [&](auto nc, uint32_t my, int u0) {  // ids u0 .. u0 + n - 1 of a chunk
+      constexpr int n = decltype(nc)::value;
+      u32x4_t q[n];
+#pragma unroll
+      for (int u = 0; u < n; ++u) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_ds_bpermute(gsel + (u0 + u) * 4, (int)my);
+        if constexpr (BIG) {
+          q[u] = (u32x4_t){0u, 0u, 0u, 0u};
+          if (o != 0xffffffffu) q[u] = *(const u32x4_t*)((const char*)tab + (int64_t)o * (EMB_DIM * 2) + l8 * 16);
+        } else {
+          q[u] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(o + l8 * 16), 0, 0));
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < n; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          acc[2 * k] += __uint_as_float(q[u][k] << 16);
+          acc[2 * k + 1] += __uint_as_float(q[u][k] & 0xffff0000u);
+        }
+    };
+    int c = 0;
+    do {
+      const uint32_t my = nxt;
+      const int rem = Lw - c;  // uniform
+      c += EMB_CHUNK;
+      if (rem <= EMB_CHUNK) {  // on to the next round's bag (after the last round: none)
+        bL = i + 1 < ROUNDS ? __shfl(L, i * 8 + 8 + g) : -1;
+        bpos = __shfl(pos, i * 8 + 8 + g);
+      }
+      nxt = chunk_off(bL, bpos, rem <= EMB_CHUNK ? 0 : c);
+      if (rem >= EMB_CHUNK) {
+        gather(ic<8>{}, my, 0);
+      } else if (rem > 0) {
+        if (rem & 4) gather(ic<4>{}, my, 0);
+        if (rem & 2) gather(ic<2>{}, my, rem & 4);
+        if (rem & 1) gather(ic<1>{}, my, rem & 6);
+      }
+    } while (c < Lw);
+    if (myL != -1) {
+      u32x4_t o = {pack2_rne(acc[0], acc[1]), pack2_rne(acc[2], acc[3]), pack2_rne(acc[4], acc[5]),
+                   pack2_rne(acc[6], acc[7])};
+      if (myL == -2) {
+        const uint32_t p = f2bf(pad);
+        o = (u32x4_t){p | (p << 16), p | (p << 16), p | (p << 16), p | (p << 16)};
+      }
+      *(u32x4_t*)(X + (int64_t)(r0 + brow) * ldx + t * EMB_DIM + l8 * 8) = o;
+    }
+  }
+  if (t == 0) {
+    // the dense features and zero tail (columns n_tables EMB_DIM .. ldx, a multiple of 8
     // wide): one 8-column chunk, a 16-byte store, per thread and pass, so that
     // the loads of all the block's rows are in flight at once
-    const int cpr = (ldx - demb) >> 3;
-    for (int e = tid; e < rpw * cpr; e += 256) {
+    const int demb = n_tables * EMB_DIM, cpr = (ldx - demb) >> 3;
+    for (int e = tid; e < 4 * NB * cpr; e += 256) {
       const int i = e / cpr, c = e - i * cpr;
-      if (r0 + i >= n_rows) break;
-      const rb_k_row rw = rows[r0 + i];
+      if (rb0 + i >= n_rows) break;
+      const rb_k_row rw = rows[rb0 + i];
       uint32_t h[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -510,7 +629,7 @@ __global__ __launch_bounds__(256) void k_embbag(const rb_k_row* __restrict__ row
         h[k] = d < n_dense ? (uint32_t)f2bf(rw.src < 0 ? pad : dense[rw.src + d]) : 0u;
       }
       const u32x4_t o = {h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-      *(u32x4_t*)(X + (int64_t)(r0 + i) * ldx + demb + 8 * c) = o;
+      *(u32x4_t*)(X + (int64_t)(rb0 + i) * ldx + demb + 8 * c) = o;
     }
   }
 }
@@ -1188,23 +1307,6 @@ rb_status rb_token_rows(hipStream_t s, const rb_k_row* rows, int n_slots, int T,
   return launch_status();
 }
 
-// ---------------------------------------------------------------- row map fill
-
-namespace {
-// Every entry of a row map set to padding (no input, no output).
-__global__ __launch_bounds__(256) void k_fill_padding_rows(rb_k_row* __restrict__ rows, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) rows[i] = rb_k_row{-1, 0, -1, -1};
-}
-}  // namespace
-
-// Runtime support (not part of the C ABI): a row map whose batches come from
-// a caller's descriptors starts as padding, so that rows no valid batch
-// covers are neither computed from nor returned.
-void rb_fill_padding_rows(hipStream_t stream, rb_k_row* rows, int64_t n) {
-  if (n > 0) hipLaunchKernelGGL(k_fill_padding_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, rows, n);
-}
-
 // ---------------------------------------------------------------- static scratch
 
 namespace {
@@ -1269,10 +1371,13 @@ void rb_scrub_caches(hipStream_t stream, const void* buf, size_t bytes, unsigned
 
 extern "C" {
 
-rb_status rb_k_route(void* stream, int32_t kind, const rb_k_batch* batches, int32_t n_batches,
-                     const rb_k_req* reqs, int32_t n_reqs, const int32_t* lens, int64_t lens_len, int32_t d_in,
-                     int32_t d_out, int32_t n_tables, rb_k_row* rows, int32_t n_rows_total, int64_t out_len,
-                     int32_t* err) {
+// rb_k_route (runtime support, not part of the C ABI): with `ends` also the end
+// of every bag among its row's ids, table after table; with `fill` the rows that
+// no batch covers become padding; max_rows: the most rows a batch has.
+rb_status rb_route_bags(void* stream, int32_t kind, const rb_k_batch* batches, int32_t n_batches,
+                        const rb_k_req* reqs, int32_t n_reqs, const int32_t* lens, int64_t lens_len, int32_t d_in,
+                        int32_t d_out, int32_t n_tables, rb_k_row* rows, int32_t n_rows_total, int64_t out_len,
+                        int32_t* ends, int32_t fill, int32_t max_rows, int32_t* err) {
   if (n_batches < 0 || n_reqs < 0 || n_rows_total < 0 || lens_len < 0 || out_len < 0 || !batches || !rows ||
       !err || d_in < 1 || d_out < 1)
     return RB_EINVAL;
@@ -1281,9 +1386,21 @@ rb_status rb_k_route(void* stream, int32_t kind, const rb_k_batch* batches, int3
   if (kind != RB_MODEL_MLP && !lens) return RB_EINVAL;
   if (kind == RB_MODEL_RANKING && (n_tables < 1 || n_tables > MAX_TABLES)) return RB_EINVAL;
   if (n_batches == 0) return RB_OK;
-  hipLaunchKernelGGL(k_route, dim3(n_batches), dim3(256), 0, (hipStream_t)stream, kind, batches, reqs, n_reqs, lens,
-                     lens_len, d_in, d_out, n_tables, rows, n_rows_total, out_len, err);
+#define RB_R(MAXR)                                                                                                    \
+  hipLaunchKernelGGL(k_route<MAXR>, dim3(n_batches), dim3(ROUTE_NT), 0, (hipStream_t)stream, kind, batches, n_batches, \
+                     reqs, n_reqs, lens, lens_len, d_in, d_out, n_tables, rows, n_rows_total, out_len, ends, fill, err)
+  if (max_rows <= 512) RB_R(512);
+  else RB_R(ROUTE_MAX_ROWS);
+#undef RB_R
   return launch_status();
+}
+
+rb_status rb_k_route(void* stream, int32_t kind, const rb_k_batch* batches, int32_t n_batches,
+                     const rb_k_req* reqs, int32_t n_reqs, const int32_t* lens, int64_t lens_len, int32_t d_in,
+                     int32_t d_out, int32_t n_tables, rb_k_row* rows, int32_t n_rows_total, int64_t out_len,
+                     int32_t* err) {
+  return rb_route_bags(stream, kind, batches, n_batches, reqs, n_reqs, lens, lens_len, d_in, d_out, n_tables, rows,
+                       n_rows_total, out_len, nullptr, 0, ROUTE_MAX_ROWS, err);
 }
 
 rb_status rb_k_assemble(void* stream, const rb_k_row* rows, int32_t n_rows_total, int32_t seq_T,
@@ -1341,24 +1458,44 @@ rb_status rb_k_embbag_dedup(void* stream, const rb_k_row* rows, int32_t n_rows_t
   return launch_status();
 }
 
-rb_status rb_k_embbag(void* stream, const rb_k_row* rows, int32_t n_rows_total, const int32_t* lens,
-                      const int32_t* ids, int64_t ids_len, const void* const* tables, int32_t n_tables,
-                      int64_t table_rows, int32_t emb_dim, const float* dense, int32_t n_dense, void* X, int32_t ldx,
-                      float pad, int32_t* err) {
+// rb_k_embbag with the bags' ends from rb_route_bags (runtime support, not
+// part of the C ABI; nullptr: from the lengths).
+rb_status rb_embbag_ends(void* stream, const rb_k_row* rows, int32_t n_rows_total, const int32_t* lens,
+                         const int32_t* ends, const int32_t* ids, int64_t ids_len, const void* const* tables,
+                         int32_t n_tables, int64_t table_rows, int32_t emb_dim, const float* dense, int32_t n_dense,
+                         void* X, int32_t ldx, float pad, int32_t* err) {
   if (emb_dim != EMB_DIM || n_tables < 1 || n_tables > MAX_TABLES || n_dense < 0 || n_dense > 256 ||
       table_rows < 1 || ids_len < 0)
     return RB_EINVAL;
   if (n_rows_total < 0 || ldx < n_tables * EMB_DIM + n_dense || (ldx & 7) || !rows || !X || !err || !tables)
     return RB_EINVAL;
   if (n_rows_total == 0) return RB_OK;
-  const int n_slices = std::min(EMB_SLICES, (int)n_tables);
-  const int gpr = (n_tables + n_slices - 1) / n_slices;  // groups per row (bags of one slice)
-  const int rpw = 32 / gpr;                              // rows per workgroup (32 groups)
-  const unsigned grid = (unsigned)((n_rows_total + rpw - 1) / rpw) * n_slices;
-  hipLaunchKernelGGL(k_embbag, dim3(grid), dim3(256), 0, (hipStream_t)stream, rows, n_rows_total, lens, ids, ids_len,
-                     (const bf16_t* const*)tables, n_tables, table_rows, dense, n_dense, (bf16_t*)X, ldx, n_slices,
-                     gpr, rpw, pad, err);
+  // 32-bit byte offsets into the ids and into a table, with room for one that
+  // is out of range
+  const bool big = table_rows > 0xffffff00ll / (EMB_DIM * 2) || ids_len > 0xffffff00ll / 4;
+  // bags per wave: 32 once that gives every compute unit 48 waves, 16 from 24
+  // waves on, else 8 (26 bags a row: 32768 rows 105 us with 32, 110 with 16, 121
+  // with 8; 4096 rows 24, 17 and 17; 64 rows 11, 8.7 and 5.7)
+  const int64_t bags = (int64_t)n_rows_total * n_tables, cus = device_cus();
+  const int rounds = bags >= 32 * 48 * cus ? 4 : (bags >= 16 * 24 * cus ? 2 : 1);
+#define RB_E(R, B)                                                                                                   \
+  hipLaunchKernelGGL((k_embbag<R, B>), dim3((unsigned)((n_rows_total + 32 * R - 1) / (32 * R)) * n_tables), dim3(256), 0, \
+                     (hipStream_t)stream, rows, n_rows_total, lens, ends, ids, ids_len, (const bf16_t* const*)tables, \
+                     n_tables, table_rows, dense, n_dense, (bf16_t*)X, ldx, pad, err)
+  if (big) RB_E(4, true);
+  else if (rounds == 4) RB_E(4, false);
+  else if (rounds == 2) RB_E(2, false);
+  else RB_E(1, false);
+#undef RB_E
   return launch_status();
+}
+
+rb_status rb_k_embbag(void* stream, const rb_k_row* rows, int32_t n_rows_total, const int32_t* lens,
+                      const int32_t* ids, int64_t ids_len, const void* const* tables, int32_t n_tables,
+                      int64_t table_rows, int32_t emb_dim, const float* dense, int32_t n_dense, void* X, int32_t ldx,
+                      float pad, int32_t* err) {
+  return rb_embbag_ends(stream, rows, n_rows_total, lens, nullptr, ids, ids_len, tables, n_tables, table_rows, emb_dim,
+                        dense, n_dense, X, ldx, pad, err);
 }
 
 rb_status rb_k_head(void* stream, const rb_k_row* rows, int32_t n_rows_total, const void* H, int32_t ldh,

@@ -42,14 +42,21 @@
 
 // kernels.hip: reads a buffer on the stream, leaving only its clean lines in the caches
 void rb_scrub_caches(hipStream_t stream, const void* buf, size_t bytes, unsigned* sink);
-// kernels.hip: sets n row-map entries to padding
-void rb_fill_padding_rows(hipStream_t stream, rb_k_row* rows, int64_t n);
 // kernels.hip: one layer of an fp32 model on split weights (X's rows gathered when src is given; the output
 // through the row map when out_rows is)
 rb_status rb_gemm_f32_split(hipStream_t s, const float* X, int ldx, const int64_t* src, int src_stride,
                             int64_t src_len, int* err, const void* Wp, const float* b, float* Y, int ldy, int M, int N,
                             int K, int act, const rb_k_row* skip_rows, int skip_T, const rb_k_row* out_rows, int d_out,
                             float* out);
+// kernels.hip: rb_k_route and rb_k_embbag, with the ends of every row's bags passed from one to the other
+extern "C" rb_status rb_route_bags(void* stream, int32_t kind, const rb_k_batch* batches, int32_t n_batches,
+                                   const rb_k_req* reqs, int32_t n_reqs, const int32_t* lens, int64_t lens_len,
+                                   int32_t d_in, int32_t d_out, int32_t n_tables, rb_k_row* rows, int32_t n_rows_total,
+                                   int64_t out_len, int32_t* ends, int32_t fill, int32_t max_rows, int32_t* err);
+extern "C" rb_status rb_embbag_ends(void* stream, const rb_k_row* rows, int32_t n_rows_total, const int32_t* lens,
+                                    const int32_t* ends, const int32_t* ids, int64_t ids_len,
+                                    const void* const* tables, int32_t n_tables, int64_t table_rows, int32_t emb_dim,
+                                    const float* dense, int32_t n_dense, void* X, int32_t ldx, float pad, int32_t* err);
 // kernels.hip: the arena offset of every packed token row
 rb_status rb_token_rows(hipStream_t s, const rb_k_row* rows, int n_slots, int T, int64_t dense_len, int d_in,
                         int64_t* src, int64_t n_src, int* err);
@@ -695,8 +702,8 @@ bool gemm_head(const rb_model* m) {
 // padded rows (sequence slots) and `tokens` real tokens (seqpool), with work
 // buffers w large enough for it; `timed`: HIP events around every launch when
 // the scheduler profiles.
-// Descriptors not built by this library start from a row map of padding
-// (fill_rows).
+// Descriptors not built by this library need not cover every row: the rest
+// becomes padding (fill_rows).
 rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batches, int n_reqs, int64_t slots,
                     int64_t tokens, const Work* w, bool timed, bool fill_rows, const rb_k_batch* d_batches,
                     const rb_k_req* d_reqs, const float* dense, int64_t dense_len, const int32_t* lens,
@@ -705,9 +712,13 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
   const int64_t M = group_rows(m, q, slots);
   void* hs = (void*)st_h;
   const float pad = s->opts.pad_value;
-  if (fill_rows) rb_fill_padding_rows(st_h, w->rows, slots);
-  RB_LAUNCH(s, st_h, "route", rb_k_route(hs, m->kind, d_batches, n_batches, d_reqs, n_reqs, lens, lens_len, m->d_in,
-                                         m->d_out, m->n_tables, w->rows, (int)slots, out_len, s->err_dev));
+  // the ends of every row's bags, n_tables of 4 bytes a row, where the second
+  // layer's output (at least 128 values of 2 bytes a row) goes later
+  int32_t* ends = m->kind == RB_MODEL_RANKING && !s->opts.emb_dedup ? (int32_t*)w->B : nullptr;
+  RB_LAUNCH(s, st_h, "route", rb_route_bags(hs, m->kind, d_batches, n_batches, d_reqs, n_reqs, lens, lens_len, m->d_in,
+                                            m->d_out, m->n_tables, w->rows, (int)slots, out_len, ends, fill_rows,
+                                            fill_rows ? (int)std::min<int64_t>(slots, RB_MAX_BATCH_ROWS) : q->B,
+                                            s->err_dev));
   const bool bf16 = m->dtype == RB_DT_BF16;
   const int Kp0 = m->layers[0].Kp;
   // sequence groups of an fp32 model: the real tokens take `tokens` consecutive
@@ -731,10 +742,14 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
       RB_LAUNCH(s, st_h, "assemble", rb_token_rows(st_h, w->rows, (int)slots, q->bucket, dense_len, m->d_in,
                                                    (int64_t*)w->X, Ml, s->err_dev));
   } else  if (m->kind == RB_MODEL_RANKING) {
-    auto emb = s->opts.emb_dedup ? rb_k_embbag_dedup : rb_k_embbag;
-    RB_LAUNCH(s, st_h, "embbag", emb(hs, w->rows, (int)slots, lens, ids, ids_len, (const void* const*)m->tables_dev,
-                                     m->n_tables, m->table_rows, m->emb_dim, dense, m->n_dense, w->X, Kp0, pad,
-                                     s->err_dev));
+    if (ends)
+      RB_LAUNCH(s, st_h, "embbag", rb_embbag_ends(hs, w->rows, (int)slots, lens, ends, ids, ids_len,
+                                                  (const void* const*)m->tables_dev, m->n_tables, m->table_rows,
+                                                  m->emb_dim, dense, m->n_dense, w->X, Kp0, pad, s->err_dev));
+    else
+      RB_LAUNCH(s, st_h, "embbag", rb_k_embbag_dedup(hs, w->rows, (int)slots, lens, ids, ids_len,
+                                                     (const void* const*)m->tables_dev, m->n_tables, m->table_rows,
+                                                     m->emb_dim, dense, m->n_dense, w->X, Kp0, pad, s->err_dev));
   } else {
     RB_LAUNCH(s, st_h, "assemble", rb_k_assemble(hs, w->rows, (int)M, m->kind == RB_MODEL_SEQPOOL ? q->bucket : 0,
                                            pack ? 2 : (seq_skip ? 1 : 0), dense, dense_len, m->d_in, w->X, Kp0,

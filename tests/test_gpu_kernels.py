@@ -834,3 +834,131 @@ def test_split_vector_and_scalar_paths(d_out, ldy):
         if out_idx[r] >= 0:
             want[out_idx[r]:out_idx[r] + d_out] = Y[r, :d_out]
     assert np.array_equal(o, want)
+
+
+@pytest.mark.parametrize("nt", [1, 26, 64])
+@pytest.mark.parametrize("rows", [1, 8, 9, 33, 70, 3900, 16400])
+def test_embbag_waves_of_8_16_and_32_bags(rows, nt):
+    # every number of bags per wave (8, 16 and 32, by rows x tables), at its row
+    # edges: the sums of exactly representable table rows match integer sums bit
+    # for bit, whatever the bag's rank (lengths with ties, zeros and more than
+    # the 60 that rank as equal), and the last row's bags are whole
+    g = torch.Generator(device=DEV).manual_seed(rows * nt)
+    tr = 50
+    tabs = torch.randint(0, 2, (nt, tr, 64), device=DEV, generator=g).to(torch.bfloat16)
+    ptrs = torch.tensor([tabs[t].data_ptr() for t in range(nt)], dtype=torch.int64, device=DEV)
+    lens = torch.randint(0, 6, (rows, nt), device=DEV, generator=g)
+    lens[torch.rand((rows, nt), device=DEV, generator=g) < 0.02] = 70
+    lens[-1] = 61
+    ids = torch.randint(0, tr, (int(lens.sum()),), device=DEV, generator=g).to(torch.int32)
+    first = (torch.cumsum(lens.sum(1), 0) - lens.sum(1)).cpu().numpy()
+    rm = np.zeros(rows, rb.K_ROW_DTYPE)
+    rm["src"], rm["aux"], rm["lens"], rm["out"] = np.arange(rows), first, np.arange(rows) * nt, 0
+    rows_d, ldx = _dev(rm.view(np.uint8)), nt * 64 + 8
+    dense = torch.randn(rows, device=DEV, generator=g)
+    X = torch.full((rows + 1, ldx), -9.0, device=DEV, dtype=torch.bfloat16)
+    l32, err = lens.to(torch.int32).reshape(-1).contiguous(), _err()
+    rb.check(rb.lib().rb_k_embbag(_stream(), rb.dptr(rows_d), rows, rb.dptr(l32), rb.dptr(ids), ids.numel(),
+                                  rb.dptr(ptrs), nt, tr, 64, rb.dptr(dense), 1, rb.dptr(X), ldx, 0.0, rb.dptr(err)),
+             "embbag")
+    bag = torch.repeat_interleave(torch.arange(rows * nt, device=DEV), lens.reshape(-1))
+    ref = torch.zeros(rows * nt, 64, device=DEV)
+    ref.index_add_(0, bag, tabs.float()[bag % nt, ids.long()])  # sums of at most 70 ones: exact in fp32 and bf16
+    assert torch.equal(X[:rows, :nt * 64].float(), ref.reshape(rows, -1))
+    assert torch.equal(X[:rows, nt * 64], dense.to(torch.bfloat16)) and not X[:rows, nt * 64 + 1:].any()
+    assert bool((X[rows] == -9.0).all()) and int(err) == 0
+
+
+def test_embbag_table_past_32_bit_offsets():
+    # a table of more than 2^32 bytes: rows beyond the 32-bit byte offsets are
+    # gathered from the right place, ids outside are reported and contribute nothing
+    tr = (1 << 25) + 3
+    tab = torch.zeros((tr, 64), dtype=torch.bfloat16, device=DEV)
+    hot = torch.tensor([0, 1 << 24, (1 << 25) - 2, (1 << 25) + 2], device=DEV)
+    tab[hot] = torch.arange(1, 5, device=DEV, dtype=torch.bfloat16)[:, None].expand(4, 64)
+    ptrs = torch.tensor([tab.data_ptr()], dtype=torch.int64, device=DEV)
+    ids = torch.cat([hot, torch.tensor([tr, -1], device=DEV)]).to(torch.int32)
+    rm = np.zeros(2, rb.K_ROW_DTYPE)
+    rm["src"], rm["aux"], rm["lens"] = [0, 0], [0, 4], [0, 1]
+    rows_d, lens, err = _dev(rm.view(np.uint8)), torch.tensor([4, 2], dtype=torch.int32, device=DEV), _err()
+    X = torch.empty((2, 64), device=DEV, dtype=torch.bfloat16)
+    rb.check(rb.lib().rb_k_embbag(_stream(), rb.dptr(rows_d), 2, rb.dptr(lens), rb.dptr(ids), 6, rb.dptr(ptrs), 1, tr,
+                                  64, None, 0, rb.dptr(X), 64, 0.0, rb.dptr(err)), "embbag")
+    assert bool((X[0] == 10).all()) and bool((X[1] == 0).all()) and int(err) == 1
+
+
+@pytest.mark.parametrize("max_rows", [512, 4096])
+@pytest.mark.parametrize("layout", ["gaps", "unsorted", "empty_batches", "overlap", "one_bad", "all_bad"])
+def test_route_fills_rows_no_batch_covers(layout, max_rows):
+    # every row outside a batch in range is set to padding, whatever the order
+    # of the batches; a batch that is refused for its requests too
+    bad = (0, 1, 100_000, 8, 1, 0)
+    kb = {"gaps": [(0, 1, 5, 4, 3, 0), (1, 1, 40, 64, 3, 0), (2, 1, 200, 3, 3, 0)],
+          "unsorted": [(2, 1, 600, 9, 3, 0), (0, 1, 5, 4, 3, 0), (1, 1, 40, 64, 3, 0)],
+          "empty_batches": [(0, 0, 20, 0, 0, 0), (1, 1, 20, 4, 3, 0), (0, 0, 300, 0, 0, 0), (0, 0, 300, 0, 0, 0)],
+          "overlap": [(0, 1, 5, 40, 3, 0), (1, 1, 30, 40, 3, 0), (2, 1, 10, 4, 3, 0)],
+          "one_bad": [bad, (1, 1, 40, 64, 3, 0), (0, 2, 300, 4, 3, 0)],  # the last holds 6 rows of 4
+          "all_bad": [bad, bad]}[layout]
+    n_rows, kba = 700, np.array(kb, rb.K_BATCH_DTYPE)
+    kr = np.zeros(3, rb.K_REQ_DTYPE)
+    kr["n_rows"], kr["dense_off"], kr["out_off"] = 3, np.arange(3) * 6, np.arange(3) * 3
+    kr["dense_end"] = kr["dense_off"] + 6
+    rows = torch.full((n_rows, 4), 77, dtype=torch.int64, device=DEV)
+    err, b_d, r_d = _err(), _dev(kba.view(np.uint8)), _dev(kr.view(np.uint8))
+    f = rb.lib().rb_route_bags
+    f.argtypes = rb.lib().rb_k_route.argtypes[:-1] + [rb.C.c_void_p, rb.C.c_int32, rb.C.c_int32, rb.C.c_void_p]
+    f.restype = rb.C.c_int32
+    rb.check(f(_stream(), rb.RB_MODEL_MLP, rb.dptr(b_d), len(kb), rb.dptr(r_d), 3, None, 0, 2, 1, 0, rb.dptr(rows),
+               n_rows, 9, None, 1, max_rows, rb.dptr(err)), "route")
+    got = rows.cpu().numpy()
+    assert not (got == 77).any()
+    assert int(err) == ("bad" in layout)
+    covered = np.zeros(n_rows, bool)
+    for begin, n_req, base, padded, real, _ in kb:
+        if padded < 1 or base + padded > n_rows or n_req * 3 > padded:
+            continue
+        covered[base:base + padded] = True
+        if layout != "overlap":
+            want = np.full((padded, 4), -1)
+            want[:, 1] = 0
+            want[:3, 0], want[:3, 3] = begin * 6 + np.arange(3) * 2, begin * 3 + np.arange(3)
+            assert np.array_equal(got[base:base + padded], want)
+    assert np.array_equal(got[~covered], np.tile([-1, 0, -1, -1], (int((~covered).sum()), 1)))
+
+
+@pytest.mark.parametrize("nt", [1, 3, 26, 33, 64])
+def test_route_ends_of_bags(nt):
+    # 16-byte loads of the lengths at every alignment and tail, and the running
+    # sums per table, over batches of one, several and more rows than threads
+    rng = np.random.default_rng(nt)
+    sizes, reqs_per = [1, 70, 1500], []
+    kb, kr, base, lo = [], [], 0, 1
+    lens = [np.zeros(1, np.int32)]
+    for n in sizes:
+        begin = len(kr)
+        left = n
+        while left:
+            k = int(min(left, rng.integers(1, 40)))
+            ln = rng.integers(0, 9, (k, nt)).astype(np.int32)
+            kr.append((0, k, lo, 1000 * len(kr), 1000 * len(kr) + int(ln.sum()), 0, k, 0))
+            lens.append(ln.reshape(-1))
+            lo += k * nt
+            left -= k
+        kb.append((begin, len(kr) - begin, base, n + 2, n, 0))
+        base += n + 2
+    kba, kra, L = np.array(kb, rb.K_BATCH_DTYPE), np.array(kr, rb.K_REQ_DTYPE), np.concatenate(lens)
+    rows, ends = torch.zeros((base, 4), dtype=torch.int64, device=DEV), torch.full((nt, base), -5, dtype=torch.int32, device=DEV)
+    err, b_d, r_d, l_d = _err(), _dev(kba.view(np.uint8)), _dev(kra.view(np.uint8)), _dev(L)
+    f = rb.lib().rb_route_bags
+    f.argtypes = rb.lib().rb_k_route.argtypes[:-1] + [rb.C.c_void_p, rb.C.c_int32, rb.C.c_int32, rb.C.c_void_p]
+    f.restype = rb.C.c_int32
+    rb.check(f(_stream(), rb.RB_MODEL_RANKING, rb.dptr(b_d), len(kb), rb.dptr(r_d), len(kr), rb.dptr(l_d), L.size, 1, 1,
+               nt, rb.dptr(rows), base, 1 << 40, rb.dptr(ends), 0, 4096, rb.dptr(err)), "route")
+    got, e = rows.cpu().numpy(), ends.cpu().numpy()
+    at = 1
+    for begin, n_req, b0, padded, real, _ in kb:
+        assert (got[b0 + real:b0 + padded, 0] == -1).all() and (e[:, b0 + real:b0 + padded] == -5).all()
+        ln = L[at:at + real * nt].reshape(real, nt)
+        at += real * nt
+        assert np.array_equal(e[:, b0:b0 + real], np.cumsum(ln, 1).T)
+    assert int(err) == 0
