@@ -1189,19 +1189,25 @@ __global__ __launch_bounds__(MT_NT) void k_mlp_tail(const bf16_t* __restrict__ H
 
 constexpr int POOL_MAX_D = 1024, POOL_MAX_OUT = 16;
 
-// One workgroup per sequence slot. Wave w sums the slot's real tokens
-// [w L / 4, (w + 1) L / 4) (tokens past L are never read, so padding cannot
-// reach the mean), each lane owning float4 columns and keeping four token
-// loads in flight while adding them in token order; the four partial sums are
-// added in wave order and divided by L (a fixed order, so the result depends
-// on the sequence only). The block then computes the head logits with
-// fixed-order reductions and thread 0 applies the softmax and writes the
-// request's output row.
-__global__ __launch_bounds__(256) void k_seqpool(const rb_k_row* __restrict__ rows, int n_seqs, int T,
-                                                 int64_t packed_rows, const float* __restrict__ H, int ldh, int D,
-                                                 const float* __restrict__ Wh,
-                                                 const float* __restrict__ bh, int n_out, int act,
-                                                 float* __restrict__ out) {
+// One workgroup per sequence slot. The slot's real tokens are summed in
+// POOL_PARTS consecutive parts (part p: tokens [p L / 16, (p + 1) L / 16); tokens
+// past L are never read, so padding cannot reach the mean), each in token
+// order; the partial sums are added in part order and divided by L: a fixed
+// order, so the result depends on the sequence only, not on NW. A wave sums
+// POOL_PARTS / NW parts side by side, each lane owning float4 columns, with 8
+// token loads in flight; a launch waits for one wave's chain of round trips,
+// so 16 waves take a sequence when there are few (60 sequences of up to 512
+// tokens: 20.4 us with 4 waves of one part and 4 loads each, now 12.8), and 4
+// otherwise. The first 256 threads
+// then compute the head logits with fixed-order reductions and thread 0 applies
+// the softmax and writes the request's output row.
+constexpr int POOL_PARTS = 16, POOL_COLS = 512;
+template <int NW>
+__global__ __launch_bounds__(NW * 64) void k_seqpool(const rb_k_row* __restrict__ rows, int n_seqs, int T,
+                                                     int64_t packed_rows, const float* __restrict__ H, int ldh, int D,
+                                                     const float* __restrict__ Wh,
+                                                     const float* __restrict__ bh, int n_out, int act,
+                                                     float* __restrict__ out) {
   const int r = blockIdx.x;
   const rb_k_row rw = rows[r];
   if (rw.out < 0) return;
@@ -1209,42 +1215,64 @@ __global__ __launch_bounds__(256) void k_seqpool(const rb_k_row* __restrict__ ro
   // packed tokens: the sequence's rows [rows[r].lens, + L) of packed_rows
   if (packed_rows > 0 && (rw.lens < 0 || rw.lens + L > packed_rows)) L = 0;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  __shared__ float psum[4][POOL_MAX_D];
-  __shared__ float pooled[POOL_MAX_D];
+  extern __shared__ float pool_lds[];  // partial sums of up to POOL_COLS columns, then the pooled row
+  const int ld = min(D, POOL_COLS);
+  float* pooled = pool_lds + POOL_PARTS * ld;
   __shared__ float part[4][POOL_MAX_OUT];
   const float* h = H + (packed_rows > 0 ? rw.lens : (int64_t)r * T) * ldh;
-  const int t0 = (int)((int64_t)L * wid / 4), t1 = (int)((int64_t)L * (wid + 1) / 4);
-  if ((D & 3) == 0 && (ldh & 3) == 0) {
-    for (int c = lane * 4; c < D; c += 256) {
-      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-      int t = t0;
-      for (; t + 4 <= t1; t += 4) {
-        float4 v[4];
+  constexpr int PP = POOL_PARTS / NW, U = 8 / PP;  // parts per wave, tokens in flight per part
+  int t0[PP], t1[PP], longest = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = *(const float4*)(h + (int64_t)(t + u) * ldh + c);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w;
-        }
-      }
-      for (; t < t1; ++t) {
-        const float4 v = *(const float4*)(h + (int64_t)t * ldh + c);
-        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-      }
-      *(float4*)&psum[wid][c] = s;
-    }
-  } else {
-    for (int c = lane; c < D; c += 64) {
-      float s = 0.f;
-      for (int t = t0; t < t1; ++t) s += h[(int64_t)t * ldh + c];
-      psum[wid][c] = s;
-    }
+  for (int i = 0; i < PP; ++i) {
+    const int p = wid * PP + i;
+    t0[i] = (int)((int64_t)L * p / POOL_PARTS);
+    t1[i] = (int)((int64_t)L * (p + 1) / POOL_PARTS);
+    longest = max(longest, t1[i] - t0[i]);
   }
-  __syncthreads();
   const float inv = 1.f / (float)max(L, 1);
-  for (int c = tid; c < D; c += 256) pooled[c] = (((psum[0][c] + psum[1][c]) + psum[2][c]) + psum[3][c]) * inv;
-  __syncthreads();
-  for (int j = 0; j < n_out; ++j) {
+  for (int c0 = 0; c0 < D; c0 += POOL_COLS) {
+    const int n = min(D - c0, POOL_COLS);
+    const float* hc = h + c0;
+    if ((D & 3) == 0 && (ldh & 3) == 0) {
+      for (int c = lane * 4; c < n; c += 256) {
+        f32x4_t s[PP];
+#pragma unroll
+        for (int i = 0; i < PP; ++i) s[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < longest; k += U) {
+          f32x4_t v[PP][U];
+#pragma unroll
+          for (int i = 0; i < PP; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (t0[i] + k + u < t1[i]) v[i][u] = *(const f32x4_t*)(hc + (int64_t)(t0[i] + k + u) * ldh + c);
+#pragma unroll
+          for (int i = 0; i < PP; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (t0[i] + k + u < t1[i]) s[i] += v[i][u];
+        }
+#pragma unroll
+        for (int i = 0; i < PP; ++i) *(f32x4_t*)&pool_lds[(wid * PP + i) * ld + c] = s[i];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < PP; ++i)
+        for (int c = lane; c < n; c += 64) {
+          float s = 0.f;
+          for (int t = t0[i]; t < t1[i]; ++t) s += hc[(int64_t)t * ldh + c];
+          pool_lds[(wid * PP + i) * ld + c] = s;
+        }
+    }
+    __syncthreads();
+    for (int c = tid; c < n; c += NW * 64) {
+      float s = 0.f;
+#pragma unroll
+      for (int p = 0; p < POOL_PARTS; ++p) s += pool_lds[p * ld + c];
+      pooled[c0 + c] = s * inv;
+    }
+    __syncthreads();
+  }
+  for (int j = 0; j < n_out && tid < 256; ++j) {
     float s = 0.f;
     for (int c = tid; c < D; c += 256) s += Wh[(int64_t)j * D + c] * pooled[c];
     s = wave_sum(s);
@@ -1545,8 +1573,13 @@ rb_status rb_k_seqpool(void* stream, const rb_k_row* rows, int32_t n_seqs, int32
   if (act != RB_ACT_NONE && act != RB_ACT_SOFTMAX) return RB_EINVAL;
   if (!rows || !H || !Wh || !bh || !out) return RB_EINVAL;
   if (n_seqs == 0) return RB_OK;
-  hipLaunchKernelGGL(k_seqpool, dim3(n_seqs), dim3(256), 0, (hipStream_t)stream, rows, n_seqs, seq_T, packed_rows, H,
-                     ldh, D, Wh, bh, n_out, act, out);
+  const size_t lds = ((size_t)POOL_PARTS * std::min(D, POOL_COLS) + D) * sizeof(float);
+  if (n_seqs < (int)device_cus())  // fewer workgroups than compute units: a launch takes as long as one of them
+    hipLaunchKernelGGL(k_seqpool<16>, dim3(n_seqs), dim3(1024), lds, (hipStream_t)stream, rows, n_seqs, seq_T,
+                       packed_rows, H, ldh, D, Wh, bh, n_out, act, out);
+  else
+    hipLaunchKernelGGL(k_seqpool<4>, dim3(n_seqs), dim3(256), lds, (hipStream_t)stream, rows, n_seqs, seq_T, packed_rows,
+                       H, ldh, D, Wh, bh, n_out, act, out);
   return launch_status();
 }
 
