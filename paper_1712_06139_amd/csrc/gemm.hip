@@ -50,11 +50,11 @@ constexpr int G16_KALIGN = 64;  // K multiple the bf16 entry point accepts
 constexpr int G32_KALIGN = 32;  // K multiple the fp32 entry point accepts
 constexpr int G32_BM = 64;      // fp32 tile height (the padding-token skip granularity)
 
-template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, bool OUT_F32,
+template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, int ACT, bool OUT_F32,
           bool PERSIST, int HEAD = -1>
 __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, const TI* __restrict__ W, int ldw,
                                           const float* __restrict__ bias, void* __restrict__ Y, int ldy, int M,
-                                          int N, int K, const rb_k_row* __restrict__ skip_rows, int skip_T,
+                                          int N, int K, int xcd_order, const rb_k_row* __restrict__ skip_rows, int skip_T,
                                           const HeadArgs ha = HeadArgs{}, const OutMap om = OutMap{}) {
   constexpr bool F32 = sizeof(TI) == 4;
   constexpr int ES = sizeof(TI);  // bytes per element
@@ -62,13 +62,12 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   constexpr int NW = NT / 64;
   static_assert((BM / WM) * (BN / WN) == NW, "one wave per sub-tile");
   static_assert(RB == 64 || RB == 128, "k-step of 64 or 128 bytes per row");
-  static_assert(S >= 2 && S <= 4, "2..4 stages");
+  static_assert(S >= 2 && S <= 8, "2..8 stages");
   constexpr int CPR = RB / 16;   // 16-byte chunks per LDS row
   constexpr int RPI = 64 / CPR;  // rows filled per wave load instruction
   constexpr int SWZ = 16 / CPR;  // rows sharing one swizzle pattern
   constexpr int EPC = 16 / ES;   // elements per chunk
   constexpr int TM = WM / 32, TN = WN / 32;
-  static_assert(TM % 2 == 0 || F32, "the last sub-step splits the A fragments in halves");
   constexpr int SA = BM / RPI / NW, SB = BN / RPI / NW;  // load instructions per wave per stage
   static_assert(SA * NW * RPI == BM && SB * NW * RPI == BN, "loads cover the tile");
   constexpr int OPS = SA + SB;
@@ -111,7 +110,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   // XCD the workgroup runs on)
   int v = blockIdx.x;
   auto tile_origin = [&](int vv, int& m0_, int& n0_) {
-    const int tile = ORDER ? xcd_tile(vv, ntiles) : vv;
+    const int tile = xcd_order ? xcd_tile(vv, ntiles) : vv;
     const int bm = tile / tiles_n;
     m0_ = bm * BM;
     n0_ = (tile - bm * tiles_n) * BN;
@@ -262,10 +261,10 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   lds_barrier();
   static_for<NR>([&](auto qc) { read_one(ic<0>{}, 0, qmap(qc), ic<0>{}); });
   auto group = [&](int kt) {  // S k-steps from a multiple of S
-    step(kt, ic<0>{}, ic<1>{}, ic<S - 1>{});
-    step(kt + 1, ic<1>{}, ic<2 % S>{}, ic<0>{});
-    if constexpr (S > 2) step(kt + 2, ic<2 % S>{}, ic<3 % S>{}, ic<1>{});
-    if constexpr (S > 3) step(kt + 3, ic<3>{}, ic<0>{}, ic<2>{});
+    static_for<S>([&](auto ic_) {
+      constexpr int i = decltype(ic_)::value;
+      step(kt + i, ic<i>{}, ic<(i + 1) % S>{}, ic<(i + S - 1) % S>{});
+    });
   };
 
   // accumulator (i, j) register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4,
@@ -428,10 +427,10 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   } else {
     int kt = 0;
     for (; kt + S <= nk; kt += S) group(kt);
-    if (kt < nk) step(kt, ic<0>{}, ic<1>{}, ic<S - 1>{});
-    if (kt + 1 < nk) step(kt + 1, ic<1>{}, ic<2 % S>{}, ic<0>{});
-    if constexpr (S > 3)
-      if (kt + 2 < nk) step(kt + 2, ic<2 % S>{}, ic<3 % S>{}, ic<1>{});
+    static_for<S - 1>([&](auto ic_) {
+      constexpr int i = decltype(ic_)::value;
+      if (kt + i < nk) step(kt + i, ic<i>{}, ic<(i + 1) % S>{}, ic<(i + S - 1) % S>{});
+    });
     // no load into LDS may still be in flight when the wave ends
     wait_vmcnt_lds<0>();
     if constexpr (HEAD >= 0)
@@ -443,52 +442,52 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
 
 // The two operand types as separately named kernels (so that traces and
 // counters tell them apart).
-template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, bool OUT_F32, bool PERSIST>
+template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ACT, bool OUT_F32, bool PERSIST>
 __global__ __launch_bounds__(NT) void k_gemm_bf16(const bf16_t* __restrict__ X, int ldx,
                                                   const bf16_t* __restrict__ W, int ldw,
                                                   const float* __restrict__ bias, void* __restrict__ Y, int ldy,
-                                                  int M, int N, int K, OutMap om) {
-  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, OUT_F32, PERSIST>(X, ldx, W, ldw, bias, Y, ldy, M, N, K,
-                                                                            nullptr, 0, HeadArgs{}, om);
+                                                  int M, int N, int K, int xcd_order, OutMap om) {
+  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ACT, OUT_F32, PERSIST>(X, ldx, W, ldw, bias, Y, ldy, M, N, K, xcd_order,
+                                                                     nullptr, 0, HeadArgs{}, om);
 }
 // A bf16 layer of 256 outputs with a narrow head in its epilogue (HEAD: the
 // head's activation); the layer's outputs never leave the workgroup.
-template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT, int HEAD>
+template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ACT, int HEAD>
 __global__ __launch_bounds__(NT) void k_gemm_head(const bf16_t* __restrict__ X, int ldx,
                                                   const bf16_t* __restrict__ W, int ldw,
                                                   const float* __restrict__ bias, int M, int K, HeadArgs ha) {
-  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, false, false, HEAD>(X, ldx, W, ldw, bias, nullptr, BN, M,
-                                                                             BN, K, nullptr, 0, ha);
+  gemm_mfma<bf16_t, BM, BN, WM, WN, NT, RB, S, ACT, false, false, HEAD>(X, ldx, W, ldw, bias, nullptr, BN, M,
+                                                                       BN, K, 1, nullptr, 0, ha);
 }
-template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, int ACT>
+template <int BM, int BN, int WM, int WN, int NT, int RB, int S, int ACT>
 __global__ __launch_bounds__(NT) void k_gemm_f32(const float* __restrict__ X, int ldx, const float* __restrict__ W,
                                                  int ldw, const float* __restrict__ bias, void* __restrict__ Y,
-                                                 int ldy, int M, int N, int K,
+                                                 int ldy, int M, int N, int K, int xcd_order,
                                                  const rb_k_row* __restrict__ skip_rows, int skip_T, OutMap om) {
-  gemm_mfma<float, BM, BN, WM, WN, NT, RB, S, ORDER, ACT, true, false>(X, ldx, W, ldw, bias, Y, ldy, M, N, K,
-                                                                       skip_rows, skip_T, HeadArgs{}, om);
+  gemm_mfma<float, BM, BN, WM, WN, NT, RB, S, ACT, true, false>(X, ldx, W, ldw, bias, Y, ldy, M, N, K, xcd_order,
+                                                               skip_rows, skip_T, HeadArgs{}, om);
 }
 
 // PERSIST: a grid of at most `cap` workgroups (a multiple of 8), each taking
 // every cap-th tile
-template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, int ORDER, bool PERSIST = false>
+template <typename TI, int BM, int BN, int WM, int WN, int NT, int RB, int S, bool PERSIST = false>
 void launch_gemm(hipStream_t s, const TI* x, int ldx, const TI* w, int ldw, const float* b, void* Y, int ldy,
-                 int M, int N, int K, int act, bool out_f32, const rb_k_row* skip_rows, int skip_T,
+                 int M, int N, int K, int act, bool out_f32, int xcd, const rb_k_row* skip_rows, int skip_T,
                  unsigned cap = 0, OutMap om = OutMap{}) {
   const unsigned tiles = (unsigned)(((M + BM - 1) / BM) * (N / BN));
   const unsigned g = PERSIST ? std::min(tiles, cap) : tiles;
   if constexpr (sizeof(TI) == 4) {
 #define RB_G(A)                                                                                                     \
-  hipLaunchKernelGGL((k_gemm_f32<BM, BN, WM, WN, NT, RB, S, ORDER, A>), dim3(g), dim3(NT), 0, s, x, ldx, w, ldw, b, \
-                     Y, ldy, M, N, K, skip_rows, skip_T, om)
+  hipLaunchKernelGGL((k_gemm_f32<BM, BN, WM, WN, NT, RB, S, A>), dim3(g), dim3(NT), 0, s, x, ldx, w, ldw, b, \
+                     Y, ldy, M, N, K, xcd, skip_rows, skip_T, om)
     if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU);
     else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID);
     else RB_G(RB_ACT_NONE);
 #undef RB_G
   } else {
 #define RB_G(A, F)                                                                                             \
-  hipLaunchKernelGGL((k_gemm_bf16<BM, BN, WM, WN, NT, RB, S, ORDER, A, F, PERSIST>), dim3(g), dim3(NT), 0, s, x, ldx, w, \
-                     ldw, b, Y, ldy, M, N, K, om)
+  hipLaunchKernelGGL((k_gemm_bf16<BM, BN, WM, WN, NT, RB, S, A, F, PERSIST>), dim3(g), dim3(NT), 0, s, x, ldx, w, \
+                     ldw, b, Y, ldy, M, N, K, xcd, om)
     if (out_f32) {
       if (act == RB_ACT_RELU) RB_G(RB_ACT_RELU, true);
       else if (act == RB_ACT_SIGMOID) RB_G(RB_ACT_SIGMOID, true);
@@ -500,14 +499,6 @@ void launch_gemm(hipStream_t s, const TI* x, int ldx, const TI* w, int ldw, cons
     }
 #undef RB_G
   }
-}
-
-// bf16 operands, k-step BK bf16 values
-template <int BM, int BN, int WM, int WN, int NT, int BK, int S, int ORDER, bool PERSIST>
-void launch_gemm_bf16(hipStream_t s, const bf16_t* x, int ldx, const bf16_t* w, int ldw, const float* b, void* Y,
-                      int ldy, int M, int N, int K, int act, int out_f32, unsigned cap, OutMap om) {
-  launch_gemm<bf16_t, BM, BN, WM, WN, NT, BK * 2, S, ORDER, PERSIST>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act,
-                                                                    out_f32 != 0, nullptr, 0, cap, om);
 }
 
 }  // namespace
@@ -536,8 +527,8 @@ rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W
   // 8 waves of 64 x 128 when fewer (two waves per SIMD hide more of the single
   // round's start and end), else 256 x 128 (8 waves of 64 x 64, k-step
   // 64, 3 stages, 144 KB), else
-  // 128 x 128 (8 waves of 64 x 32, k-step 64, 4 stages, 128 KB), 128 x 64 (4
-  // waves of 64 x 32, 96 KB) or 64 x 64 (2 waves of 64 x 32, 64 KB). XCD-contiguous
+  // 128 x 128 (8 waves of 64 x 32, k-step 64, 4 stages, 128 KB) or smaller ones
+  // for launches of few rows. XCD-contiguous
   // tile order when all of W fits in one XCD's L2 (each XCD then keeps its A
   // row-blocks and W in its own L2); plain order otherwise (contiguous ranges
   // would stream all of W through every XCD).
@@ -550,13 +541,9 @@ rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W
   const int64_t rows256 = (M + 255) / 256;
   const bool xcd = (int64_t)N * K * 2 <= (4 << 20);
   const unsigned cus = device_cus() & ~7u;
-#define RB_PICK(BM, BN, WM, WN, NT, BK, S, P)                                                                   \
-  do {                                                                                                          \
-    if (xcd)                                                                                                    \
-      launch_gemm_bf16<BM, BN, WM, WN, NT, BK, S, 1, P>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act, out_f32, cus, om); \
-    else                                                                                                        \
-      launch_gemm_bf16<BM, BN, WM, WN, NT, BK, S, 0, P>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act, out_f32, cus, om); \
-  } while (0)
+#define RB_PICK(BM, BN, WM, WN, NT, BK, S, P)                                                                      \
+  launch_gemm<bf16_t, BM, BN, WM, WN, NT, BK * 2, S, P>(s, x, ldx, w, ldw, b, Y, ldy, M, N, K, act, out_f32 != 0, xcd, \
+                                                        nullptr, 0, cus, om)
   auto persist = [&](int bm, int bn, int bk, int st) {
     const int64_t tiles = ((M + bm - 1) / bm) * (int64_t)(N / bn);
     const int nk = K / bk;
@@ -573,17 +560,31 @@ rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W
     else
       RB_PICK(256, 128, 64, 64, 512, 64, 3, false);
   } else {
-    // fewer tiles than that: the k-loop's latency bounds a launch of a few
-    // batches, so the largest of 128 x 128, 128 x 64 and 64 x 64 tiles that
-    // still gives half the compute units a tile (512 x 1024 x 1728: 12.5 ->
-    // 8.7 us with 64 x 64; 2816 x 512 x 1024: 9.7 -> 7.3 us with 128 x 64)
-    const int64_t rows128 = (M + 127) / 128, half = std::max<int64_t>(cus / 2, 1);
-    if (rows128 * (N / 128) >= half)
-      RB_PICK(128, 128, 64, 32, 512, 64, 4, false);
-    else if (rows128 * (N / 64) >= half)
-      RB_PICK(128, 64, 64, 32, 256, 64, 4, false);
-    else
+    // fewer tiles than that. A wave issues its loads, LDS reads and MFMAs one
+    // after another, and a compute unit's loads enter at 64 bytes a clock, so a
+    // launch of few rows takes as long as one tile's k-loop: the smallest tiles
+    // that still leave one (or two) to a compute unit. Cold weights, us:
+    //                     32 x 32  64 x 32  64 x 64  128 x 64  128 x 128
+    //   64 x 1024 x 1728      6.9      7.1      8.1
+    //   512 x 1024 x 1728     7.5      7.2      8.0                12.5
+    //   128 x 4096 x 8192      33       31       39
+    //   128 x 8192 x 8192      83       68       47        56
+    //   256 x 8192 x 8192     141      124       65        77
+    //   512 x 8192 x 4096                        58                  42
+    //   2816 x 1024 x 1728                       23                  14
+    // (64 x 64 tiles with 4 waves of 32 x 32 in one round, 2 of 64 x 32 in two:
+    // 47 against 47, 65 against 72)
+    const int64_t rows64 = (M + 63) / 64, rows32 = (M + 31) / 32;
+    if (rows32 * (N / 32) <= (int64_t)cus)
+      RB_PICK(32, 32, 32, 32, 64, 64, 6, false);
+    else if (rows64 * (N / 32) <= (int64_t)cus)
+      RB_PICK(64, 32, 32, 32, 128, 64, 8, false);
+    else if (rows64 * (N / 64) <= (int64_t)cus)
+      RB_PICK(64, 64, 32, 32, 256, 64, 4, false);
+    else if (rows64 * (N / 64) <= 2 * (int64_t)cus)
       RB_PICK(64, 64, 64, 32, 128, 64, 4, false);
+    else
+      RB_PICK(128, 128, 64, 32, 512, 64, 4, false);
   }
 #undef RB_PICK
   return launch_status();
@@ -624,12 +625,8 @@ rb_status gemm_f32_impl(void* stream, const float* X, int32_t ldx, const float* 
   // XCD's L2 (each XCD then reads its X rows once; plain order measured 1.5x
   // slower on sequence groups).
   const bool xcd = (int64_t)N * K * 4 <= (4 << 20);
-  if (xcd)
-    launch_gemm<float, G32_BM, 64, 32, 32, 256, 64, 3, 1>(s, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, true, skip_rows,
-                                                          skip_T, 0, om);
-  else
-    launch_gemm<float, G32_BM, 64, 32, 32, 256, 64, 3, 0>(s, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, true, skip_rows,
-                                                          skip_T, 0, om);
+  launch_gemm<float, G32_BM, 64, 32, 32, 256, 64, 3>(s, X, ldx, W, ldw, b, Y, ldy, M, N, K, act, true, xcd, skip_rows,
+                                                     skip_T, 0, om);
   return launch_status();
 }
 }  // namespace
@@ -669,10 +666,10 @@ rb_status rb_k_gemm_head(void* stream, const void* X, int32_t ldx, const void* W
 #define RB_GH(A, H)                                                                                                    \
   do {                                                                                                                 \
     if (small)                                                                                                         \
-      hipLaunchKernelGGL((k_gemm_head<64, 256, 64, 32, 512, 128, 3, 1, A, H>), dim3(g), dim3(512), 0, s,             \
+      hipLaunchKernelGGL((k_gemm_head<64, 256, 64, 32, 512, 128, 3, A, H>), dim3(g), dim3(512), 0, s,             \
                          (const bf16_t*)X, ldx, (const bf16_t*)W, ldw, b, M, K, ha);                                   \
     else                                                                                                               \
-      hipLaunchKernelGGL((k_gemm_head<128, 256, 64, 64, 512, 128, 3, 1, A, H>), dim3(g), dim3(512), 0, s,            \
+      hipLaunchKernelGGL((k_gemm_head<128, 256, 64, 64, 512, 128, 3, A, H>), dim3(g), dim3(512), 0, s,            \
                          (const bf16_t*)X, ldx, (const bf16_t*)W, ldw, b, M, K, ha);                                   \
   } while (0)
   if (head_act == RB_ACT_SIGMOID) {

@@ -962,3 +962,50 @@ def test_route_ends_of_bags(nt):
         at += real * nt
         assert np.array_equal(e[:, b0:b0 + real], np.cumsum(ln, 1).T)
     assert int(err) == 0
+
+
+@pytest.mark.parametrize("n,T,D,ldh", [(3, 512, 256, 256), (3, 40, 1000, 1000), (2, 70, 517, 520), (2, 33, 513, 513),
+                                       (600, 40, 256, 256), (600, 17, 6, 7)])
+def test_seqpool_parts_and_wave_counts(n, T, D, ldh):
+    # sequences shorter than the 16 parts and longer, with 16 waves (few
+    # sequences) and 4 (many), widths over one pass of columns and not multiples
+    # of 4; a sequence's bits are the same with either wave count
+    rng = np.random.default_rng(n + D)
+    L = np.concatenate([[1, T], rng.integers(1, T + 1, n - 2)])
+    rows = _rows_dev(np.zeros(n), L, np.arange(n) * 2)
+    H = rng.standard_normal((n * T, ldh)).astype(np.float32)
+    Wh, bh = rng.standard_normal((2, D)).astype(np.float32), rng.standard_normal(2).astype(np.float32)
+    Hd, Wd, bd = _dev(H), _dev(Wh), _dev(bh)
+    out = torch.zeros(2 * n, device=DEV)
+    call = lambda o, k: rb.check(rb.lib().rb_k_seqpool(_stream(), rb.dptr(rows), k, T, 0, rb.dptr(Hd), ldh, D,  # noqa: E731
+                                                       rb.dptr(Wd), rb.dptr(bd), 2, rb.RB_ACT_NONE, rb.dptr(o)), "seqpool")
+    call(out, n)
+    ref = np.stack([H[e * T:e * T + L[e], :D].astype(np.float64).mean(0) for e in range(n)]) @ Wh.T.astype(np.float64) + bh
+    got = out.cpu().numpy().reshape(n, 2)
+    assert np.max(np.abs(got - ref) / (np.abs(ref).max(axis=1, keepdims=True) + np.sqrt(D))) <= 1e-5
+    few = torch.zeros(4, device=DEV)
+    call(few, 2)
+    assert torch.equal(few, out[:4])
+
+
+@pytest.mark.parametrize("M", [1, 31, 33, 65, 257, 600])
+@pytest.mark.parametrize("N,K", [(128, 64), (1024, 192), (4096, 448), (8192, 576)])
+def test_gemm_bf16_few_rows(M, N, K):
+    # every tile of launches of few rows (32 x 32, 64 x 32, 64 x 64 with 4 and 2
+    # waves, 128 x 128) at their row edges, with fewer k-steps than stages and
+    # with remainders of every length: fp64 within the rounding of the stored
+    # bf16 (2^-9) plus fp32 sums, and the bits of a launch of many rows
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    X = torch.randn(2048, K, device=DEV, generator=g).to(torch.bfloat16)
+    W = (torch.randn(N, K, device=DEV, generator=g) / K ** 0.5).to(torch.bfloat16)
+    b = torch.randn(N, device=DEV, generator=g)
+    outs = []
+    for m in (M, 2048):
+        Y = torch.full((m + 1, N), -3.0, device=DEV, dtype=torch.bfloat16)
+        rb.check(rb.lib().rb_k_gemm_bf16(_stream(), rb.dptr(X), K, rb.dptr(W), K, rb.dptr(b), rb.dptr(Y), N, m, N, K,
+                                         rb.RB_ACT_RELU, 0), "gemm")
+        assert bool((Y[m] == -3.0).all())
+        outs.append(Y[:M])
+    ref = (X[:M].double() @ W.double().T + b.double()).clamp(min=0)
+    assert bool(((outs[0].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-4).all())
+    assert torch.equal(outs[0], outs[1])
