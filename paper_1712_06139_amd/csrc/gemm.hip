@@ -6,20 +6,19 @@
 namespace {
 
 // Y = act(X W^T + b): X [M, K] and W [N, K] of element type TI (bf16 or
-// fp32), K contiguous; fp32 accumulation with v_mfma_f32_32x32x16_bf16 or
+// fp32), K contiguous; fp32 accumulation with v_mfma_f32_16x16x32_bf16 or
 // v_mfma_f32_32x32x2f32.
 //
 // Workgroup tile BM x BN, k-step of RB bytes per row (64 or 128: 32 or 64
 // bf16, 16 or 32 fp32), NT/64 waves each owning a WM x WN sub-tile
-// ((WM/32) x (WN/32) accumulators). Operand tiles go straight from global
+// ((WM/T) x (WN/T) accumulators; T = 16 bf16, 32 fp32). Operand tiles go straight from global
 // memory into a ring of S >= 2 LDS stages (global_load_lds: each wave load
 // instruction fills 1 KB of consecutive LDS rows; no register staging).
 // K-step kt reads stage kt % S while the stage of k-step kt - 1 is refilled
 // with k-step kt - 1 + S, its loads spread one every few MFMAs over the step
 // (over its first half when S = 2, where that refill is the next k-step):
 // issued back to back they stall the wave on the texture path with no MFMA in
-// flight. A sub-step covers 32 bytes of every row (16 bf16 or 8 fp32 k values)
-// and its MFMAs have the next sub-step's fragment reads between them. In the
+// flight. A sub-step covers 32 bf16 or 8 fp32 k values of every row and its MFMAs have the next sub-step's fragment reads between them. In the
 // last sub-step, after half of its MFMAs (three quarters with S = 2), the wave
 // waits for its loads of the next k-step and for its LDS reads, and all waves
 // meet at one barrier: the next stage has landed and nobody reads the current
@@ -27,17 +26,24 @@ namespace {
 // fragment reads between the MFMAs. The order of MFMAs, LDS reads and loads
 // within a step is fixed with scheduling barriers.
 //
-// A fragment is 16 bytes of one row: lane l holds row l % 32 and chunk
-// 2 kk + l / 32 of sub-step kk. bf16: one 32x32x16 MFMA per accumulator and
-// sub-step. fp32: chunk c holds k = 4c .. 4c + 3, and MFMA t (t = 0..3) of the
-// sub-step takes dword t, so it adds the products of k = 8 kk + t (lanes
-// 0..31) and k = 8 kk + 4 + t (lanes 32..63); the MFMAs of a sub-step run
-// t-major over the accumulators, so two MFMAs into one accumulator are NM
-// instructions apart.
+// A fragment is 16 bytes of one row: lane l holds row l % T and chunk l / T of
+// the sub-step's. bf16: one 16x16x32 MFMA per accumulator and sub-step. The chip
+// runs these layers at its power limit, and with random operands in registers
+// it sustains 2080 TFLOP/s of 16x16x32 against 1740 to 1800 of 32x32x16 (zeros:
+// 2450 with either); the results have the same bits. 8192 x 1024 x 1728
+// 28.4 -> 25.3 us, 32768 x 1024 x 1728 117 -> 96, 32768 x 512 x 1024 35 -> 32,
+// 4096 x 4096 x 8192 202 -> 189, 65536 x 8192 x 4096 3290 either way. fp32:
+// chunk c holds k = 4c .. 4c + 3, and MFMA t (t = 0..3) of the sub-step takes
+// dword t, so it adds the products of k = 8 kk + t (lanes 0..31) and k = 8 kk + 4
+// + t (lanes 32..63); the MFMAs of a sub-step run t-major over the accumulators,
+// so two MFMAs into one accumulator are NM instructions apart.
 //
 // LDS rows hold RB/16 16-byte chunks; chunk c of row r sits at chunk
 // c ^ ((r / (16 / (RB/16))) % (RB/16)), so the 16 rows one fragment read
-// serves per LDS cycle hit 16 distinct bank groups (64 banks).
+// serves per LDS cycle hit 16 distinct bank groups (64 banks). For bf16 the
+// column blocks of a wave come in pairs that take alternate groups of four of 32
+// rows of W, so that a lane ends up with eight consecutive output columns, and
+// W's rows have a permutation to match (swz_b).
 //
 // Every tile shape, k-step, stage count and tile order accumulates each output
 // element in the same k order with the same instructions, so results do not
@@ -67,11 +73,16 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   constexpr int RPI = 64 / CPR;  // rows filled per wave load instruction
   constexpr int SWZ = 16 / CPR;  // rows sharing one swizzle pattern
   constexpr int EPC = 16 / ES;   // elements per chunk
-  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int T = F32 ? 32 : 16;       // rows and columns of one MFMA
+  constexpr int NREG = T * T / 64;       // its accumulator registers
+  constexpr int TM = WM / T, TN = WN / T;
+  static_assert(F32 || TN % 2 == 0, "column blocks are stored in pairs");
+  typedef typename std::conditional<F32, floatx16_t, floatx4_t>::type acc_t;
   constexpr int SA = BM / RPI / NW, SB = BN / RPI / NW;  // load instructions per wave per stage
   static_assert(SA * NW * RPI == BM && SB * NW * RPI == BN, "loads cover the tile");
   constexpr int OPS = SA + SB;
-  constexpr int KK = RB / 32;    // MFMA sub-steps per k-step
+  constexpr int CPS = 64 / T;    // 16-byte chunks of a row per sub-step (lane l holds chunk l / T of row l % T)
+  constexpr int KK = CPR / CPS;  // MFMA sub-steps per k-step
   constexpr int NM = TM * TN;    // accumulators
   constexpr int MPF = F32 ? 4 : 1;  // MFMAs per accumulator and sub-step
   constexpr int NU = NM * MPF;   // MFMAs per sub-step
@@ -123,6 +134,18 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
     if (rw.src < 0 || m0 - e * skip_T >= rw.aux) return;
   }
 
+  // chunk c of row r sits at chunk c ^ swz(r); the column blocks of a pair take
+  // alternate groups of 4 rows of W's 32 (bf16), so their swizzle differs
+  auto swz_a = [](int r) { return (r / SWZ) % CPR; };
+  auto swz_b = [](int r) {
+    if constexpr (F32) return (r / SWZ) % CPR;
+    else return ((r >> 1) & 1) | (((r >> 3) & 3) << 1);
+  };
+  // the row of W's tile that row x of a wave's column block j is
+  auto b_row = [&](int j, int x) {
+    if constexpr (F32) return wn * WN + j * 32 + x;
+    else return wn * WN + (j >> 1) * 32 + (x >> 2) * 8 + (j & 1) * 4 + (x & 3);
+  };
   // lane l of a load instruction fills LDS row l / CPR (of its RPI), chunk l % CPR
   const int lr = lane / CPR, lc = lane % CPR;
   // byte offsets from the tile's first row (buffer resources based there; the
@@ -132,7 +155,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
     for (int i = 0; i < SA; ++i) {
       const int row = (wid * SA + i) * RPI + lr;
       const int ra = min(row, M - 1 - m0_);  // rows past M are computed on a copy and never stored
-      va_[i] = (uint32_t)(ra * ldx + (lc ^ ((row / SWZ) % CPR)) * EPC) * (uint32_t)ES;
+      va_[i] = (uint32_t)(ra * ldx + (lc ^ swz_a(row)) * EPC) * (uint32_t)ES;
     }
   };
   i32x4_t rA = buffer_rsrc(X + (int64_t)m0 * ldx), rB = buffer_rsrc(W + (int64_t)n0 * ldw);
@@ -141,7 +164,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
 #pragma unroll
   for (int i = 0; i < SB; ++i) {
     const int row = (wid * SB + i) * RPI + lr;
-    vb[i] = (uint32_t)(row * ldw + (lc ^ ((row / SWZ) % CPR)) * EPC) * (uint32_t)ES;
+    vb[i] = (uint32_t)(row * ldw + (lc ^ swz_b(row)) * EPC) * (uint32_t)ES;
   }
   // persistent: the next tile's origin, resources and A offsets (a copy of the
   // current tile's when there is none)
@@ -169,14 +192,14 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   };
   if constexpr (PERSIST) next_tile();
 
-  floatx16_t acc[TM][TN];
+  acc_t acc[TM][TN];
   auto zero_acc = [&]() {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int r = 0; r < NREG; ++r) acc[i][j][r] = 0.f;
   };
   zero_acc();
 
@@ -208,14 +231,14 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   // fragment read q (A fragment q for q < TM, then B) of sub-step kk of stage st
   auto read_one = [&](auto stc, int kk, auto qc, auto bufc) {
     constexpr int st = decltype(stc)::value, q = decltype(qc)::value, bf = decltype(bufc)::value;
-    // lane l holds row l % 32, chunk 2 kk + l / 32
-    const int ch = kk * 2 + (lane >> 5);
+    // lane l holds row l % T, chunk CPS kk + l / T
+    const int ch = kk * CPS + lane / T;
     if constexpr (q < TM) {
-      const int r = wm * WM + q * 32 + (lane & 31);
-      fa[bf][q] = sA[st][r * CPR + (ch ^ ((r / SWZ) % CPR))];
+      const int r = wm * WM + q * T + lane % T;
+      fa[bf][q] = sA[st][r * CPR + (ch ^ swz_a(r))];
     } else {
-      const int r = wn * WN + (q - TM) * 32 + (lane & 31);
-      fb[bf][q - TM] = sB[st][r * CPR + (ch ^ ((r / SWZ) % CPR))];
+      const int r = b_row(q - TM, lane % T);
+      fb[bf][q - TM] = sB[st][r * CPR + (ch ^ swz_b(r))];
     }
   };
   // k-step kt: stage stc, next stage nstc, refilled stage rstc (k-step kt - 1's)
@@ -235,7 +258,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
           acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x2f32(
               __uint_as_float(fa[cur][m / TN][t]), __uint_as_float(fb[cur][m % TN][t]), acc[m / TN][m % TN], 0, 0, 0);
         else
-          acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               __builtin_bit_cast(bf16x8_t, fa[cur][m / TN]), __builtin_bit_cast(bf16x8_t, fb[cur][m % TN]),
               acc[m / TN][m % TN], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
@@ -267,66 +290,87 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
     });
   };
 
-  // accumulator (i, j) register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4,
-  // column l%32 of its 32 x 32 block. Bias and activation are applied per
-  // column; then each group of four registers (four consecutive rows) is
-  // transposed across the four lanes of a quad, so that a lane holds four
-  // consecutive columns of one row and stores them at once (8 bytes bf16, 16
-  // bytes fp32) instead of four single elements.
+  // Bias and activation are applied per column; then each group of four
+  // registers (four consecutive rows of one column) is transposed across the
+  // four lanes of a quad, so that a lane holds four consecutive columns of one
+  // row. fp32: register r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4, column
+  // l % 32 of its 32 x 32 block. bf16: row 4 (l / 16) + r and row x = l % 16 of
+  // the column block, which is column b_row(j, x): the two blocks of a pair give
+  // a lane eight consecutive columns, stored at once (16 bytes bf16).
+  constexpr int NG = NREG / 4;                // groups of four registers per block
+  constexpr int NC = F32 ? 4 : 8;             // consecutive columns a lane stores
+  constexpr int JS = F32 ? 1 : 2;             // column blocks they come from
+  auto row_in = [&](int g) { return F32 ? 8 * g + 4 * (lane >> 5) + (lane & 3) : 4 * (lane >> 4) + (lane & 3); };
+  // the lane's NC columns of row block i, register group g, column blocks j, j + JS - 1
+  auto columns = [&](int i, int g, int j, const float (&bb)[JS], float (&q)[NC]) {
+#pragma unroll
+    for (int h = 0; h < JS; ++h) {
+      float x[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = act_fn<ACT>(acc[i][j + h][4 * g + k] + bb[h]);
+      quad_transpose4(x, lane);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q[4 * h + k] = x[k];
+    }
+  };
+  auto first_col = [&](int j) { return F32 ? wn * WN + j * 32 + (lane & 28) : b_row(j, lane & 12); };
   auto epilogue = [&]() {
   // with an output row map: the output offsets of this lane's rows, loaded
   // all at once before any is needed
   const bool mapped = OUT_F32 && om.rows != nullptr;  // uniform
-  int64_t ro[TM][4];
+  int64_t ro[TM][NG];
   if (mapped) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int r = m0 + wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
+      for (int g = 0; g < NG; ++g) {
+        const int r = m0 + wm * WM + i * T + row_in(g);
         ro[i][g] = r < M ? om.rows[r].out : -1;
       }
   }
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const float bb = bias[n0 + wn * WN + j * 32 + (lane & 31)];
-    const int colq = n0 + wn * WN + j * 32 + (lane & 28);  // first column of this lane's quad
+  for (int j = 0; j < TN; j += JS) {
+    float bb[JS];
+#pragma unroll
+    for (int h = 0; h < JS; ++h) bb[h] = bias[n0 + b_row(j + h, lane % T)];
+    const int colq = n0 + first_col(j);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float q[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = act_fn<ACT>(acc[i][j][4 * g + k] + bb);
-        quad_transpose4(q, lane);
-        const int row = m0 + wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
+      for (int g = 0; g < NG; ++g) {
+        float q[NC];
+        columns(i, g, j, bb, q);
+        const int row = m0 + wm * WM + i * T + row_in(g);
         // streaming (nontemporal) stores: the whole chip writes its tiles'
         // outputs at about the same time, and these drain faster than
         // stores that allocate in L2
         if constexpr (OUT_F32) {
+          float* dst = nullptr;
+          int n = NC;  // columns to store
           if (mapped) {
             const int64_t o = ro[i][g];
-            if (o >= 0) {
-              float* dst = om.out + o + colq;
-              if (colq + 3 < om.d_out && ((uintptr_t)dst & 15) == 0) {
-                const f32x4_t v = {q[0], q[1], q[2], q[3]};
-                __builtin_nontemporal_store(v, (f32x4_t*)dst);
-              } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                  if (colq + k < om.d_out) dst[k] = q[k];
-              }
-            }
-            continue;
+            if (o >= 0) dst = om.out + o + colq;
+            n = min(NC, om.d_out - colq);
+          } else if (row < M) {
+            dst = (float*)Y + (int64_t)row * ldy + colq;
           }
-        }
-        if (row < M) {
-          if (OUT_F32) {
-            const f32x4_t o = {q[0], q[1], q[2], q[3]};
-            __builtin_nontemporal_store(o, (f32x4_t*)((float*)Y + (int64_t)row * ldy + colq));
-          } else {
-            const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
-            __builtin_nontemporal_store(o, (u32x2_t*)((bf16_t*)Y + (int64_t)row * ldy + colq));
+          if (dst) {
+            if (n == NC && ((uintptr_t)dst & 15) == 0) {
+#pragma unroll
+              for (int k = 0; k < NC; k += 4) {
+                const f32x4_t v = {q[k], q[k + 1], q[k + 2], q[k + 3]};
+                __builtin_nontemporal_store(v, (f32x4_t*)(dst + k));
+              }
+            } else {
+#pragma unroll
+              for (int k = 0; k < NC; ++k)
+                if (k < n) dst[k] = q[k];
+            }
+          }
+        } else if (row < M) {
+          if constexpr (!F32) {
+            const u32x4_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3]), pack2_rne(q[4], q[5]), pack2_rne(q[6], q[7])};
+            __builtin_nontemporal_store(o, (u32x4_t*)((bf16_t*)Y + (int64_t)row * ldy + colq));
           }
         }
       }
@@ -358,20 +402,20 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
     const u32x4_t w0 = *(const u32x4_t*)(ha.w + l * 8), w1 = *(const u32x4_t*)(ha.w + 128 + l * 8);
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const float bb = bias[n0 + wn * WN + j * 32 + (lane & 31)];
-      const int colq = wn * WN + j * 32 + (lane & 28);
+    for (int j = 0; j < TN; j += JS) {
+      float bb[JS];
+#pragma unroll
+      for (int h = 0; h < JS; ++h) bb[h] = bias[n0 + b_row(j + h, lane % T)];
+      const int colq = first_col(j);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float q[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) q[k] = act_fn<ACT>(acc[i][j][4 * g + k] + bb);
-          quad_transpose4(q, lane);
-          const int rl = wm * WM + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
-          const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
-          *(u32x2_t*)(hb + rl * HLD + colq * 2) = o;
+        for (int g = 0; g < NG; ++g) {
+          float q[NC];
+          columns(i, g, j, bb, q);
+          const int rl = wm * WM + i * T + row_in(g);
+          const u32x4_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3]), pack2_rne(q[4], q[5]), pack2_rne(q[6], q[7])};
+          *(u32x4_t*)(hb + rl * HLD + colq * 2) = o;
         }
     }
     __syncthreads();
@@ -521,12 +565,10 @@ rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W
   // Tile shape, k-step, stage count and tile order only change speed: every
   // choice accumulates each output in the same k order with the same
   // instruction (identical bits). The largest tile that still gives every CU a
-  // tile: 256 x 256 (k-step 64, 2 stages, 128 KB LDS, every row's k-step a
-  // whole 128-byte line) as 4 waves of 128 x 128 when there are at least two
-  // tiles per CU (half the fragment reads per flop of 8 waves of 64 x 128), as
-  // 8 waves of 64 x 128 when fewer (two waves per SIMD hide more of the single
-  // round's start and end), else 256 x 128 (8 waves of 64 x 64, k-step
-  // 64, 3 stages, 144 KB), else
+  // tile: 256 x 256 (8 waves of 64 x 128, k-step 64, 2 stages, 128 KB LDS, every
+  // row's k-step a whole 128-byte line; 4 waves of 128 x 128 need every register
+  // and measured 1.3x slower), else 256 x 128 (8 waves of 64 x 64, k-step 64, 3
+  // stages, 144 KB), else
   // 128 x 128 (8 waves of 64 x 32, k-step 64, 4 stages, 128 KB) or smaller ones
   // for launches of few rows. XCD-contiguous
   // tile order when all of W fits in one XCD's L2 (each XCD then keeps its A
@@ -550,10 +592,7 @@ rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W
     return cus >= 8 && tiles > (int64_t)cus && nk >= st && nk % st == 0;
   };
   if (N % 256 == 0 && rows256 * (N / 256) >= 256) {
-    if (rows256 * (N / 256) >= 2 * (int64_t)cus)
-      RB_PICK(256, 256, 128, 128, 256, 64, 2, false);
-    else
-      RB_PICK(256, 256, 64, 128, 512, 64, 2, false);
+    RB_PICK(256, 256, 64, 128, 512, 64, 2, false);
   } else if (rows256 * (N / 128) >= 256) {
     if (persist(256, 128, 64, 3))
       RB_PICK(256, 128, 64, 64, 512, 64, 3, true);

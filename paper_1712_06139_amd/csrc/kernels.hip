@@ -957,7 +957,7 @@ __global__ __launch_bounds__(256) void k_head(const rb_k_row* __restrict__ rows,
 // (bias, ReLU, bf16) stay in LDS as the second layer's input while W3 streams
 // through two more stages; the second layer's outputs (bias, ReLU, bf16) go to
 // LDS and the head reads them there. Each output is accumulated in the same k
-// order with the same 32x32x16 bf16 MFMA as k_gemm_bf16, rounded the same way,
+// order with the same 16x16x32 bf16 MFMA as k_gemm_bf16, rounded the same way,
 // and the head sums exactly as k_head does (16 lanes per row, 8 consecutive
 // elements of every 128 per lane, then a 16-lane butterfly), so the results
 // are bit-identical to running the two layers and the head separately; only
@@ -1011,31 +1011,27 @@ __global__ __launch_bounds__(MT_NT) void k_mlp_tail(const bf16_t* __restrict__ H
 #pragma unroll
     for (int i = 0; i < 4; ++i) *(u32x4_t*)(base + MT_A_BYTES + mt_addr4(lrow + 128 * i, lc)) = r.b[i];
   };
-  floatx16_t acc[2][4];
+  floatx4_t acc[4][8];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  auto mma1 = [&](int st) {
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+  auto mma1 = [&](int st) {  // lane l holds row l % 16, chunk l / 16
     const unsigned char* base = lds + st * (MT_A_BYTES + MT_B_BYTES);
+    u32x4_t fa[4], fb[8];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int c = kk * 2 + (lane >> 5);
-      u32x4_t fa[2], fb[4];
+    for (int i = 0; i < 4; ++i) fa[i] = *(const u32x4_t*)(base + mt_addr4(wm * 64 + i * 16 + (lane & 15), lane >> 4));
 #pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = *(const u32x4_t*)(base + mt_addr4(wm * 64 + i * 32 + (lane & 31), c));
+    for (int j = 0; j < 8; ++j)
+      fb[j] = *(const u32x4_t*)(base + MT_A_BYTES + mt_addr4(wn * 128 + j * 16 + (lane & 15), lane >> 4));
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        fb[j] = *(const u32x4_t*)(base + MT_A_BYTES + mt_addr4(wn * 128 + j * 32 + (lane & 31), c));
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[i]),
-                                                              __builtin_bit_cast(bf16x8_t, fb[j]), acc[i][j], 0, 0, 0);
-    }
+      for (int j = 0; j < 8; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fa[i]),
+                                                            __builtin_bit_cast(bf16x8_t, fb[j]), acc[i][j], 0, 0, 0);
   };
   // k-step kt: load kt + 2 into the set kt held, multiply stage kt % 2, store
   // kt + 1 (loaded a k-step ago) into the other stage
@@ -1072,58 +1068,53 @@ __global__ __launch_bounds__(MT_NT) void k_mlp_tail(const bf16_t* __restrict__ H
   Op2 w0, w1;
   load2(w0, 0);
   load2(w1, 1);
-  // accumulator (i, j) register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4,
-  // column l % 32 of its 32 x 32 block; bias and ReLU per column, then each
-  // group of four rows transposed across the quad so a lane holds four
-  // consecutive columns of one row (as k_gemm_bf16's epilogue), rounded to bf16
+  // accumulator (i, j) register r of lane l: row 4 (l / 16) + r, column l % 16
+  // of its 16 x 16 block; bias and ReLU per column, then each group of four rows
+  // transposed across the quad so a lane holds four consecutive columns of one
+  // row, rounded to bf16 as k_gemm_bf16's epilogue rounds
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int col0 = wn * 128 + j * 32;
-    const float bb = b2[col0 + (lane & 31)];
-    const int colq = col0 + (lane & 28);
+  for (int j = 0; j < 8; ++j) {
+    const int col0 = wn * 128 + j * 16;
+    const float bb = b2[col0 + (lane & 15)];
+    const int colq = col0 + (lane & 12);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i) {
+      float q[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float q[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = act_fn<RB_ACT_RELU>(acc[i][j][4 * g + k] + bb);
-        quad_transpose4(q, lane);
-        const int row = wm * 64 + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
-        const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
-        *(u32x2_t*)(lds + MT_Y2 + mt_addr_y2(row, colq >> 3) + ((colq & 4) ? 8 : 0)) = o;
-      }
+      for (int k = 0; k < 4; ++k) q[k] = act_fn<RB_ACT_RELU>(acc[i][j][k] + bb);
+      quad_transpose4(q, lane);
+      const int row = wm * 64 + i * 16 + 4 * (lane >> 4) + (lane & 3);
+      const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
+      *(u32x2_t*)(lds + MT_Y2 + mt_addr_y2(row, colq >> 3) + ((colq & 4) ? 8 : 0)) = o;
+    }
   }
   store2(w0, 0);
   __syncthreads();
   // ---- second layer: Y3 = relu(Y2 W3^T + b3)
-  floatx16_t acc3[2][2];
+  floatx4_t acc3[4][4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc3[i][j][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc3[i][j][r] = 0.f;
   auto mma2 = [&](int kt) {
     const unsigned char* base = lds + MT_W3 + (kt & 1) * (MT_N3 * 64);
+    u32x4_t fa[4], fb[4];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int c = kk * 2 + (lane >> 5);
-      u32x4_t fa[2], fb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = wm * 64 + i * 32 + (lane & 31);
-        fa[i] = *(const u32x4_t*)(lds + MT_Y2 + mt_addr_y2(row, kt * 4 + c));
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) fb[j] = *(const u32x4_t*)(base + mt_addr4(wn * 64 + j * 32 + (lane & 31), c));
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc3[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[i]),
-                                                               __builtin_bit_cast(bf16x8_t, fb[j]), acc3[i][j], 0, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+      const int row = wm * 64 + i * 16 + (lane & 15);
+      fa[i] = *(const u32x4_t*)(lds + MT_Y2 + mt_addr_y2(row, kt * 4 + (lane >> 4)));
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      fb[j] = *(const u32x4_t*)(base + mt_addr4(wn * 64 + j * 16 + (lane & 15), lane >> 4));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc3[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fa[i]),
+                                                             __builtin_bit_cast(bf16x8_t, fb[j]), acc3[i][j], 0, 0, 0);
   };
   constexpr int nk3 = MT_N2 / MT_KS;
   auto step2 = [&](int kt, Op2& mine, Op2& next) {
@@ -1140,22 +1131,20 @@ __global__ __launch_bounds__(MT_NT) void k_mlp_tail(const bf16_t* __restrict__ H
   // layer's outputs (no longer read)
   unsigned char* y3 = lds;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int col0 = wn * 64 + j * 32;
-    const float bb = b3[col0 + (lane & 31)];
-    const int colq = col0 + (lane & 28);
+  for (int j = 0; j < 4; ++j) {
+    const int col0 = wn * 64 + j * 16;
+    const float bb = b3[col0 + (lane & 15)];
+    const int colq = col0 + (lane & 12);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i) {
+      float q[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float q[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = act_fn<RB_ACT_RELU>(acc3[i][j][4 * g + k] + bb);
-        quad_transpose4(q, lane);
-        const int row = wm * 64 + i * 32 + 8 * g + 4 * (lane >> 5) + (lane & 3);
-        const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
-        *(u32x2_t*)(y3 + row * (MT_N3 * 2) + colq * 2) = o;
-      }
+      for (int k = 0; k < 4; ++k) q[k] = act_fn<RB_ACT_RELU>(acc3[i][j][k] + bb);
+      quad_transpose4(q, lane);
+      const int row = wm * 64 + i * 16 + 4 * (lane >> 4) + (lane & 3);
+      const u32x2_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3])};
+      *(u32x2_t*)(y3 + row * (MT_N3 * 2) + colq * 2) = o;
+    }
   }
   __syncthreads();
   // ---- head, as k_head: 16 lanes per row, lane l taking elements
