@@ -49,8 +49,8 @@ HBM_PEAK_GBS = 8000.0
 # L2 read peak: 8 XCDs x 16 channels x 128 bytes per clock at 2.4 GHz
 L2_PEAK_GBS = 8 * 16 * 128 * 2.4
 BF16_PEAK_TFLOPS = 2500.0
-F32_PEAK_TFLOPS = 157.3
-KERNELS = ("route", "assemble", "embbag", "gemm_bf16", "gemm_f32", "gemm_head", "mlp_tail", "head", "seqpool", "split")
+F32_PEAK_TFLOPS = BF16_PEAK_TFLOPS / 6  # an fp32 layer takes six bf16 partial products per product
+KERNELS = ("route", "assemble", "token_rows", "embbag", "gemm_bf16", "gemm_f32", "gemm_head", "mlp_tail", "head", "seqpool", "split")
 
 DESCRIPTION = {
     "ranking": "ranking: 26 Zipf(1.1) embedding bags over 100k x 64 bf16 tables + 13 dense -> MLP "
@@ -96,10 +96,10 @@ def fused_head(m):
 def algorithmic_work(w, t, a, logd, qindex, window, fused=False):
     """Algorithmic bytes / flops of one replay, per kernel. Real model
     dimensions; padded rows count as rows, since the method pads them and
-    computes them. Sequence groups: padding tokens are not written by the
-    assembler and 64-token blocks of them are not computed by the GEMMs (the
-    pooling never reads them; with --seq-pack the layers run on the real tokens
-    alone), so both count real tokens only."""
+    computes them. Sequence groups run on their real tokens alone, so those
+    count; their token rows' arena offsets are 8 bytes each. Models whose first
+    layer reads the requests' rows in place launch no assembly, so its entry goes
+    unused."""
     work = collections.defaultdict(lambda: {"bytes": 0, "flops": 0})
     nb = logd["n_batches"]
     beg = logd["b_req_begin"][:nb + 1]
@@ -132,6 +132,8 @@ def algorithmic_work(w, t, a, logd, qindex, window, fused=False):
             Mw = int(n_dense[b]) // m.d_in if (m.kind == "seqpool" and T % 64 == 0) else M
             work["assemble"]["bytes"] += (int(n_dense[b]) * 4 + Mw * m.d_in * (2 if bf16 else 4)
                                           + (P if m.kind == "seqpool" else M) * row_desc)
+        if m.kind == "seqpool":
+            work["token_rows"]["bytes"] += P * row_desc + int(n_dense[b]) // m.d_in * 8
         layers = m.layers[:-1] if (m.kind == "ranking" and bf16 and m.layers[-1].fan_out == 1) else m.layers
         tail = fused and fused_tail(m)
         ghead = not tail and m.kind != "seqpool" and fused_head(m)

@@ -742,7 +742,7 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
   if (gather) {
     src = pack ? (const int64_t*)w->X : &w->rows->src;
     if (pack)
-      RB_LAUNCH(s, st_h, "assemble", rb_token_rows(st_h, w->rows, (int)slots, q->bucket, dense_len, m->d_in,
+      RB_LAUNCH(s, st_h, "token_rows", rb_token_rows(st_h, w->rows, (int)slots, q->bucket, dense_len, m->d_in,
                                                    (int64_t*)w->X, Ml, s->err_dev));
   } else  if (m->kind == RB_MODEL_RANKING) {
     if (ends)
