@@ -40,8 +40,8 @@ namespace {
 //
 // LDS rows hold RB/16 16-byte chunks; chunk c of row r sits at chunk
 // c ^ ((r / (16 / (RB/16))) % (RB/16)), so the 16 rows one fragment read
-// serves per LDS cycle hit 16 distinct bank groups (64 banks). For bf16 the
-// column blocks of a wave come in pairs that take alternate groups of four of 32
+// serves per LDS cycle hit 16 distinct bank groups (64 banks). For bf16
+// outputs the column blocks of a wave come in pairs that take alternate groups of four of 32
 // rows of W, so that a lane ends up with eight consecutive output columns, and
 // W's rows have a permutation to match (swz_b).
 //
@@ -76,7 +76,8 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   constexpr int T = F32 ? 32 : 16;       // rows and columns of one MFMA
   constexpr int NREG = T * T / 64;       // its accumulator registers
   constexpr int TM = WM / T, TN = WN / T;
-  static_assert(F32 || TN % 2 == 0, "column blocks are stored in pairs");
+  constexpr bool PAIR = !F32 && !OUT_F32;  // column blocks stored in pairs
+  static_assert(!PAIR || TN % 2 == 0, "column blocks are stored in pairs");
   typedef typename std::conditional<F32, floatx16_t, floatx4_t>::type acc_t;
   constexpr int SA = BM / RPI / NW, SB = BN / RPI / NW;  // load instructions per wave per stage
   static_assert(SA * NW * RPI == BM && SB * NW * RPI == BN, "loads cover the tile");
@@ -135,15 +136,15 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   }
 
   // chunk c of row r sits at chunk c ^ swz(r); the column blocks of a pair take
-  // alternate groups of 4 rows of W's 32 (bf16), so their swizzle differs
+  // alternate groups of 4 rows of W's 32, so their swizzle differs
   auto swz_a = [](int r) { return (r / SWZ) % CPR; };
   auto swz_b = [](int r) {
-    if constexpr (F32) return (r / SWZ) % CPR;
+    if constexpr (!PAIR) return (r / SWZ) % CPR;
     else return ((r >> 1) & 1) | (((r >> 3) & 3) << 1);
   };
   // the row of W's tile that row x of a wave's column block j is
   auto b_row = [&](int j, int x) {
-    if constexpr (F32) return wn * WN + j * 32 + x;
+    if constexpr (!PAIR) return wn * WN + j * T + x;
     else return wn * WN + (j >> 1) * 32 + (x >> 2) * 8 + (j & 1) * 4 + (x & 3);
   };
   // lane l of a load instruction fills LDS row l / CPR (of its RPI), chunk l % CPR
@@ -295,11 +296,15 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   // four lanes of a quad, so that a lane holds four consecutive columns of one
   // row. fp32: register r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4, column
   // l % 32 of its 32 x 32 block. bf16: row 4 (l / 16) + r and row x = l % 16 of
-  // the column block, which is column b_row(j, x): the two blocks of a pair give
-  // a lane eight consecutive columns, stored at once (16 bytes bf16).
+  // the column block, which is column b_row(j, x): for bf16 outputs the two blocks
+  // of a pair give a lane eight consecutive columns, stored at once (16 bytes);
+  // for fp32 outputs a lane's four columns of one block are 16 bytes, and a row's
+  // 16 columns one 64-byte piece (eight in a lane, half of them in each of two
+  // stores, made the large MLP's last layer slower: its backlog ran at 0.995 of
+  // the speed with 32x32x16, and runs at 1.037 of it this way).
   constexpr int NG = NREG / 4;                // groups of four registers per block
-  constexpr int NC = F32 ? 4 : 8;             // consecutive columns a lane stores
-  constexpr int JS = F32 ? 1 : 2;             // column blocks they come from
+  constexpr int NC = PAIR ? 8 : 4;            // consecutive columns a lane stores
+  constexpr int JS = PAIR ? 2 : 1;            // column blocks they come from
   auto row_in = [&](int g) { return F32 ? 8 * g + 4 * (lane >> 5) + (lane & 3) : 4 * (lane >> 4) + (lane & 3); };
   // the lane's NC columns of row block i, register group g, column blocks j, j + JS - 1
   auto columns = [&](int i, int g, int j, const float (&bb)[JS], float (&q)[NC]) {
@@ -313,7 +318,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
       for (int k = 0; k < 4; ++k) q[4 * h + k] = x[k];
     }
   };
-  auto first_col = [&](int j) { return F32 ? wn * WN + j * 32 + (lane & 28) : b_row(j, lane & 12); };
+  auto first_col = [&](int j) { return b_row(j, lane & (T - 4)); };
   auto epilogue = [&]() {
   // with an output row map: the output offsets of this lane's rows, loaded
   // all at once before any is needed
@@ -368,7 +373,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
             }
           }
         } else if (row < M) {
-          if constexpr (!F32) {
+          if constexpr (PAIR) {
             const u32x4_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3]), pack2_rne(q[4], q[5]), pack2_rne(q[6], q[7])};
             __builtin_nontemporal_store(o, (u32x4_t*)((bf16_t*)Y + (int64_t)row * ldy + colq));
           }
