@@ -230,7 +230,7 @@ def recorded_traffic(workload, kernel):
     import hashlib
     try:
         rec = json.load(open(os.path.join(ROOT, "profiles", "traffic.json")))
-        src = open(os.path.join(ROOT, rec["source"]), "rb").read()
+        src = b"".join(open(os.path.join(ROOT, f), "rb").read() for f in rec["sources"])
     except (OSError, ValueError, KeyError):
         return None
     if hashlib.sha256(src).hexdigest() != rec.get("sha256"):
@@ -761,7 +761,7 @@ def main():
     ap.add_argument("--version-swap", type=int, default=0,
                     help="also time this many steps while new versions of the largest servable load and swap in")
     ap.add_argument("--seq-pack", action="store_true",
-                    help="sequence models: pack the real tokens of each launch group (no time padding)")
+                    help="sequence models: the scheduler option seq_pack (replays pack the real tokens either way)")
     ap.add_argument("--emb-dedup", action="store_true",
                     help="ranking models: gather each distinct table row of a 64-row block once (rb_k_embbag_dedup)")
     ap.add_argument("--fused-tail", action="store_true",
@@ -903,7 +903,7 @@ def main():
         roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(ach / HBM_PEAK_GBS, 4)}
         roof["algorithmic_bytes_per_launch"] = round(wk["bytes"] / dk["launches"])
-    roof["traffic"] = recorded_traffic(w.name + ("_packed" if args.seq_pack and w.name == "ragged_seq" else ""), dom)
+    roof["traffic"] = recorded_traffic(w.name, dom)
     if "cold_avg_us" in dk:
         roof["cold"] = {"avg_launch_us": dk["cold_avg_us"],
                         "achieved": round(roof["achieved"] * dk["avg_us"] / dk["cold_avg_us"], 2),

@@ -744,7 +744,7 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
     if (pack)
       RB_LAUNCH(s, st_h, "token_rows", rb_token_rows(st_h, w->rows, (int)slots, q->bucket, dense_len, m->d_in,
                                                    (int64_t*)w->X, Ml, s->err_dev));
-  } else  if (m->kind == RB_MODEL_RANKING) {
+  } else if (m->kind == RB_MODEL_RANKING) {
     if (ends)
       RB_LAUNCH(s, st_h, "embbag", rb_embbag_ends(hs, w->rows, (int)slots, lens, ends, ids, ids_len,
                                                   (const void* const*)m->tables_dev, m->n_tables, m->table_rows,
