@@ -33,12 +33,22 @@ __device__ float k_zeros[64];  // one k-step of a row of zeros
 // Y = act(X W^T + b) with fp32 X, W, b and Y, on the bf16 matrix cores (fp32
 // MFMA peaks at 157 TFLOP/s, bf16 at 2500): every operand is the exact sum of
 // three bf16 parts, and a product is the sum of its six partial products down
-// to 2^-16 of it, smallest first, each exact in fp32, accumulated in fp32. The
-// three partial products left out are below 2^-26 of the product, under an
-// fp32 rounding, and the sum has fewer roundings than one fp32 MFMA per two k
-// values: the error against 64 bits is 0.8 of the fp32 MFMA kernel's (2.4e-7
-// against 2.9e-7 of the result's norm at K = 256, 4.9e-7 against 5.7e-7 at
-// K = 1024).
+// to 2^-16 of it, each exact in fp32, accumulated in fp32 (three-way splitting
+// as published for emulating single precision on bf16 units, Henry et al. 2019).
+// The three partial products left out are below 2^-26 of the product, under an
+// fp32 rounding.
+//
+// The products of the first parts have an accumulator of their own, and the
+// five smaller ones another (below 2^-7 of it, so that its roundings do not
+// count); the two meet at the end. The first one is then rounded once for
+// every 8 k values with a product that is not zero, where the fp32 MFMA rounds
+// once for each such product: on no input has the sum more roundings than the
+// fp32 MFMA's. With one accumulator for all six it had 12 for 16 k values,
+// more than the fp32 MFMA where half of X is zeros, as after a ReLU. Error
+// against 64 bits over the result's norm at K = 1024, of the fp32 MFMA, of one
+// accumulator and of two: normal inputs 5.7e-7, 4.9e-7, 1.8e-7; half of them
+// zeros 4.1e-7, 4.7e-7, 1.4e-7; nine of ten zeros 1.8e-7 and 0.6e-7 (the first
+// and the last).
 //
 // W comes split (rb_pack_f32_weights): per 32 rows and 16 k values the three
 // parts in the order of a wave's fragment, so a fragment is one coalesced load
@@ -52,14 +62,17 @@ __device__ float k_zeros[64];  // one k-step of a row of zeros
 // followed by its share of the k-step's other work, and the next fragments
 // are read before they are needed (512 x 1024 x 1024: 17 us, against 30 us in
 // program order). Otherwise four waves per SIMD overlap each other's phases
-// and the fragments take half the registers (262144 x 512 x 256: 378 us
-// against 430 us by hand at two waves per SIMD).
+// (64 x 256 tiles; 262144 x 512 x 256: 423 us, 384 us with 128 x 256 tiles and
+// one accumulator; two accumulators leave no registers for four waves of 128
+// rows, and 128 x 256 tiles of two waves per SIMD take 422 to 434 us, 64 x 256
+// with the six products summed from zero and added by vector adds 410 to 420 us
+// but 3 to 8% more for launches of few rows).
 //
 // Every tile shape accumulates an output element in the same k order with the
 // same instructions, so results depend neither on it nor on which rows share
 // a tile.
 template <int BM, int BN, int WM, int WN, int KS, int RBUF, bool PIPE, int ACT>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void k_gemm_f32_split(
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, PIPE ? 2 : 4) void k_gemm_f32_split(
     const float* __restrict__ X, int ldx, GatherArgs ga, const u32x4_t* __restrict__ Wp,
     const float* __restrict__ bias, float* __restrict__ Y, int ldy, int M, int N, int K, int xcd_order,
     const rb_k_row* __restrict__ skip_rows, int skip_T, OutMap om) {
@@ -146,23 +159,24 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void k_gemm_f32_spli
     fa[decltype(bufc)::value][p][i] =
         *(const u32x4_t*)((const unsigned char*)sA + (ra0 + st) + ((ks * (BM / 32) + i) * 3 + p) * ABLK * 16);
   };
-  floatx16_t acc[TM][TN];
+  floatx16_t acc[TM][TN], low[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
   constexpr int NM = TM * TN, NU = 6 * NM;  // MFMAs per sub-step
   constexpr int NS = KS * NU;               // MFMAs per k-step
   constexpr int UB = NS - NU / 2;           // of them before the barrier (PIPE)
-  // the parts of the six partial products, smallest first
+  // the parts of the six partial products, smallest first; the last one's sum is acc
   constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
   auto mfma = [&](auto abufc, auto bbufc, auto vc) {
     constexpr int v = decltype(vc)::value, p = v / NM, m = v % NM;
-    acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+    floatx16_t& sum = (p < 5 ? low : acc)[m / TN][m % TN];
+    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
         __builtin_bit_cast(bf16x8_t, fa[decltype(abufc)::value][PA[p]][m / TN]),
-        __builtin_bit_cast(bf16x8_t, fb[decltype(bbufc)::value][PB[p]][m % TN]), acc[m / TN][m % TN], 0, 0, 0);
+        __builtin_bit_cast(bf16x8_t, fb[decltype(bbufc)::value][PB[p]][m % TN]), sum, 0, 0, 0);
   };
   static_for<LA>([&](auto c) { load_a(c, 0); });
   static_for<RBUF - 1>([&](auto sc) { static_for<3 * TN>([&](auto qc) { load_b(sc, qc, decltype(sc)::value); }); });
@@ -221,6 +235,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void k_gemm_f32_spli
     }
     st = nst;
   }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
   // Infinities, NaN and values near the end of the fp32 range: an operand's
   // split then has infinite or NaN parts, which make every sum they enter
   // non-finite. Those elements (and no others, so that a row's result does not
@@ -325,12 +343,12 @@ rb_status rb_gemm_f32_split(hipStream_t s, const float* X, int ldx, const int64_
     else if (act == RB_ACT_SIGMOID) RB_S(__VA_ARGS__, RB_ACT_SIGMOID); \
     else RB_S(__VA_ARGS__, RB_ACT_NONE);                   \
   } while (0)
-  // The largest tile that fills the chip: 128 x 256 (8 waves) with two tiles
-  // for every compute unit, 64 x 128 (4 waves) with one, else 32 x 64 (2
-  // waves; 512 x 1024 x 1024: 17 us, against 22 us with 64 x 128).
+  // The largest tile that fills the chip: 64 x 256 (8 waves, four a SIMD) with
+  // four tiles for every compute unit, 64 x 128 (4 waves) with one, else
+  // 32 x 64 (2 waves; 512 x 1024 x 1024: 17 us, against 22 us with 64 x 128).
   const int64_t cus = device_cus();
-  if (!skip_rows && N % 256 == 0 && (int64_t)((M + 127) / 128) * (N / 256) >= 2 * cus)
-    RB_L(128, 256, 128, 32, 2, 2, false);
+  if (!skip_rows && N % 256 == 0 && (int64_t)((M + 63) / 64) * (N / 256) >= 4 * cus)
+    RB_L(64, 256, 64, 32, 2, 2, false);
   else if (N % 128 == 0 && (int64_t)((M + 63) / 64) * (N / 128) >= cus)
     RB_L(64, 128, 64, 32, 4, 4, true);
   else

@@ -75,8 +75,8 @@ def _err(y, ref):
     return np.max(np.abs(y - ref) / np.maximum(np.abs(ref).max(axis=1, keepdims=True), 1e-30))
 
 
-# rows around the 32-, 64- and 128-row tiles; widths for each tile (N a multiple
-# of 64, 128, 256); 33000 rows x 512 and 66000 x 256 take the 128 x 256 tile on
+# rows around the 32- and 64-row tiles; widths for each tile (N a multiple
+# of 64, 128, 256); 33000 rows x 512 and 66000 x 256 take the 64 x 256 tile on
 # 256 compute units, 8256 x 256 the 64 x 128 one. d_in not a multiple of 64 is
 # assembled first, the others are read from the arena, aligned or not.
 @pytest.mark.parametrize("M,dims,shift", [
@@ -101,6 +101,27 @@ def test_f32_layer_exact_products(ctx):
     W[:, 6] *= np.float32(1e30)
     y, _ = _run(ctx, [(W, np.zeros(64, np.float32), "none")], np.eye(64, dtype=np.float32))
     assert np.array_equal(y, W.T)
+
+
+# the 32 x 64, 64 x 128 and 64 x 256 tiles
+@pytest.mark.parametrize("M,N,K", [(256, 64, 64), (512, 256, 1024), (8256, 256, 256), (66000, 256, 192)])
+@pytest.mark.parametrize("density", [1.0, 0.5, 0.1, 0.02])
+def test_f32_layer_error_is_no_larger_than_the_fp32_mfma_kernels(ctx, M, N, K, density):
+    # dense inputs, inputs half zeros (a hidden layer's after a ReLU) and sparse
+    # ones: the error against 64 bits, over all outputs, is at most that of the
+    # kernel on fp32 operands (its sums have no fewer roundings)
+    rng = np.random.default_rng(K + N)
+    W = (rng.standard_normal((N, K)) / np.sqrt(K)).astype(np.float32)
+    b = np.zeros(N, np.float32)
+    X = (rng.standard_normal((M, K)) * (rng.random((M, K)) < density)).astype(np.float32)
+    y, _ = _run(ctx, [(W, b, "none")], X)
+    Xd, Wd, bd = (torch.from_numpy(a).to(DEV) for a in (X, W, b))
+    Y = torch.empty(M, N, device=DEV)
+    rb.check(rb.lib().rb_k_gemm_f32(rb.torch_stream_ptr(), rb.dptr(Xd), K, rb.dptr(Wd), K, rb.dptr(bd), rb.dptr(Y), N,
+                                    M, N, K, rb.RB_ACT_NONE, None, 0), "rb_k_gemm_f32")
+    ref = Xd.double() @ Wd.double().T
+    err = [float((torch.as_tensor(v).to(DEV).double() - ref).norm() / ref.norm()) for v in (y, Y)]
+    assert err[0] <= err[1], err
 
 
 @pytest.mark.parametrize("M", [40, 33000])
