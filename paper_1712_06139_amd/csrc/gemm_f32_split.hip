@@ -1,11 +1,14 @@
 // Dense layers of fp32 models on the bf16 matrix cores.
+#include <cmath>
+
 #include "device.h"
 
 namespace {
 
-// Two fp32 values as the exact sums of three bf16 values each (h + m + l; the
-// first value in the low halves): a bf16 holds 8 significant bits and each
-// remainder is exact in fp32, so three hold all 24.
+// Two fp32 values of at least 2^-110 (or 0) as the exact sums of three bf16
+// values each (h + m + l; the first value in the low halves): a bf16 holds 8
+// significant bits and each remainder is exact in fp32, so three hold all 24
+// (under 2^-110 the last part would fall below the smallest bf16, 2^-133).
 __device__ __forceinline__ void split3(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
   h = pack2_rne(a, b);
   const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
@@ -37,6 +40,12 @@ __device__ float k_zeros[64];  // one k-step of a row of zeros
 // as published for emulating single precision on bf16 units, Henry et al. 2019).
 // The three partial products left out are below 2^-26 of the product, under an
 // fp32 rounding.
+//
+// X is scaled by 2^40 before it is split, so that every fp32 value down to the
+// smallest, 2^-149, is the sum of its parts, and W by a power of two that the
+// model loader picks for its smallest weight (1 unless one is under 2^-110);
+// `unscale` takes both out of the sum. A sum that overflows for it (2^88 and
+// more, without such weights) is one of the non-finite ones below.
 //
 // The products of the first parts have an accumulator of their own, and the
 // five smaller ones another (below 2^-7 of it, so that its roundings do not
@@ -74,8 +83,8 @@ __device__ float k_zeros[64];  // one k-step of a row of zeros
 template <int BM, int BN, int WM, int WN, int KS, int RBUF, bool PIPE, int ACT>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, PIPE ? 2 : 4) void k_gemm_f32_split(
     const float* __restrict__ X, int ldx, GatherArgs ga, const u32x4_t* __restrict__ Wp,
-    const float* __restrict__ bias, float* __restrict__ Y, int ldy, int M, int N, int K, int xcd_order,
-    const rb_k_row* __restrict__ skip_rows, int skip_T, OutMap om) {
+    const float* __restrict__ bias, float* __restrict__ Y, int ldy, int M, int N, int K, float unscale,
+    int xcd_order, const rb_k_row* __restrict__ skip_rows, int skip_T, OutMap om) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int BK = 16 * KS;           // k values per k-step
@@ -132,7 +141,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, PIPE ? 2 : 4) void k_ge
   auto split_half = [&](uint32_t st, auto ic_, auto hc) {
     constexpr int i = decltype(ic_)::value, h = decltype(hc)::value;
     uint32_t a, b, c;
-    split3(ra[i][2 * h], ra[i][2 * h + 1], a, b, c);
+    split3(ra[i][2 * h] * 0x1p40f, ra[i][2 * h + 1] * 0x1p40f, a, b, c);
     sh[h] = a;
     sm[h] = b;
     sl[h] = c;
@@ -239,9 +248,9 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, PIPE ? 2 : 4) void k_ge
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
-  // Infinities, NaN and values near the end of the fp32 range: an operand's
-  // split then has infinite or NaN parts, which make every sum they enter
-  // non-finite. Those elements (and no others, so that a row's result does not
+  // Infinities, NaN and values that the scaling takes past the end of the fp32
+  // range: an operand's split then has infinite or NaN parts, which make every
+  // sum they enter non-finite. Those elements (and no others, so that a row's result does not
   // depend on its neighbours) are computed again with fp32 operands.
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -263,10 +272,14 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, PIPE ? 2 : 4) void k_ge
           const uint16_t* e = wr + (k >> 4) * 1536 + ((((k >> 3) & 1) << 5) + (lane & 31)) * 8 + (k & 7);
           float w = bf2f(e[0]);
           if (isfinite(w)) w += bf2f(e[512]) + bf2f(e[1024]);  // exact; a non-finite w has itself as its first part
+          w *= unscale * 0x1p40f;                              // W's part of the scale
           z = __builtin_amdgcn_mfma_f32_32x32x2f32(xr ? xr[k] : 0.f, w, z, 0, 0, 0);
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = isfinite(acc[i][j][r]) ? acc[i][j][r] : z[r];
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = isfinite(acc[i][j][r]) ? acc[i][j][r] * unscale : z[r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] *= unscale;
       }
     }
   // the store, as in gemm_mfma's epilogue: each group of four registers (four
@@ -318,10 +331,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, PIPE ? 2 : 4) void k_ge
 // order). X's rows are read at stride ldx, or gathered: row r from element
 // src[r * src_stride] of X (src_len elements; K of them per row). The output
 // goes to Y, or through the row map to out (out_rows given). skip_rows as in
-// rb_k_gemm_f32. K and N are multiples of 64.
+// rb_k_gemm_f32. K and N are multiples of 64. Wp holds W times 2^w_exp (0..39).
 rb_status rb_gemm_f32_split(hipStream_t s, const float* X, int ldx, const int64_t* src, int src_stride,
-                            int64_t src_len, int* err, const void* Wp, const float* b, float* Y, int ldy, int M, int N,
-                            int K, int act, const rb_k_row* skip_rows, int skip_T, const rb_k_row* out_rows, int d_out,
+                            int64_t src_len, int* err, const void* Wp, int w_exp, const float* b, float* Y, int ldy,
+                            int M, int N, int K, int act, const rb_k_row* skip_rows, int skip_T, const rb_k_row* out_rows, int d_out,
                             float* out) {
   if (M < 0 || N <= 0 || K <= 0 || N % 64 || K % 64 || !X || !Wp || !b || (!out_rows && (!Y || ldy < N)))
     return RB_EINVAL;
@@ -330,13 +343,14 @@ rb_status rb_gemm_f32_split(hipStream_t s, const float* X, int ldx, const int64_
   if (M == 0) return RB_OK;
   const GatherArgs ga{src, src_stride, src_len, err};
   const OutMap om{out_rows, out, d_out};
+  const float unscale = std::ldexp(1.f, -40 - w_exp);
   // XCD-contiguous tile order when all of W fits in one XCD's L2 (each XCD
   // then reads its X rows once), plain order otherwise
   const int xcd = (int64_t)N * K * 6 <= (4 << 20);
 #define RB_S(BM, BN, WM, WN, KS, RBUF, PIPE, A)                                                                     \
   hipLaunchKernelGGL((k_gemm_f32_split<BM, BN, WM, WN, KS, RBUF, PIPE, A>),                                         \
                      dim3((unsigned)((M + BM - 1) / BM) * (N / BN)), dim3((BM / WM) * (BN / WN) * 64), 0, s, X, ldx, ga, \
-                     (const u32x4_t*)Wp, b, Y, ldy, M, N, K, xcd, skip_rows, skip_T, om)
+                     (const u32x4_t*)Wp, b, Y, ldy, M, N, K, unscale, xcd, skip_rows, skip_T, om)
 #define RB_L(...)                                          \
   do {                                                     \
     if (act == RB_ACT_RELU) RB_S(__VA_ARGS__, RB_ACT_RELU); \

@@ -45,11 +45,11 @@ void rb_scrub_caches(hipStream_t stream, const void* buf, size_t bytes, unsigned
 // The launchers below are weak references: a build of this file for its
 // host-only paths links without them.
 #define RB_KERNEL __attribute__((weak))
-// gemm_f32_split.hip: one layer of an fp32 model on split weights (X's rows gathered when src is given; the
-// output through the row map when out_rows is)
+// gemm_f32_split.hip: one layer of an fp32 model on split weights, which hold W times 2^w_exp (X's rows gathered
+// when src is given; the output through the row map when out_rows is)
 RB_KERNEL rb_status rb_gemm_f32_split(hipStream_t s, const float* X, int ldx, const int64_t* src, int src_stride,
-                            int64_t src_len, int* err, const void* Wp, const float* b, float* Y, int ldy, int M, int N,
-                            int K, int act, const rb_k_row* skip_rows, int skip_T, const rb_k_row* out_rows, int d_out,
+                            int64_t src_len, int* err, const void* Wp, int w_exp, const float* b, float* Y, int ldy,
+                            int M, int N, int K, int act, const rb_k_row* skip_rows, int skip_T, const rb_k_row* out_rows, int d_out,
                             float* out);
 // kernels.hip: rb_k_route and rb_k_embbag, with the ends of every row's bags passed from one to the other
 extern "C" RB_KERNEL rb_status rb_route_bags(void* stream, int32_t kind, const rb_k_batch* batches, int32_t n_batches,
@@ -110,7 +110,8 @@ struct rb_ctx {
 
 struct DevLayer {
   int K = 0, N = 0, Kp = 0, Np = 0, act = 0;
-  void* w = nullptr;   // [Np, Kp] zero padded: bf16, or fp32 split into bf16 parts in fragment order
+  void* w = nullptr;   // [Np, Kp] zero padded: bf16, or fp32 times 2^w_exp split into bf16 parts in fragment order
+  int w_exp = 0;
   float* b = nullptr;  // [Np] zero padded
 };
 
@@ -349,12 +350,24 @@ rb_status upload_layer(rb_model* m, const rb_layer_desc& L, DevLayer& d, bool bf
   } else {
     // each element as three bf16 parts that sum to it exactly (its first part
     // is not rounded up to infinity); per 32 rows and 16 k values the parts one
-    // after another, in the order of a wave's 32 x 16 fragment
+    // after another, in the order of a wave's 32 x 16 fragment. The parts hold
+    // elements from 2^-110 on: if the smallest (but 0) is below, all are scaled
+    // by the power of two that takes it there, as far as the largest stays finite
+    // (a layer that spans more than 2^236 loses bits under 2^-134 of the scaled
+    // elements)
+    float lo = INFINITY, hi = 0.f;  // the smallest and the largest |element|, but 0 and non-finite ones
+    for (size_t i = 0; i < (size_t)d.N * d.K; ++i) {
+      const float v = std::fabs(L.w[i]);
+      if (v > 0.f) lo = std::min(lo, v);
+      if (std::isfinite(v)) hi = std::max(hi, v);
+    }
+    d.w_exp = lo >= 0x1p-110f ? 0 : std::max(0, std::min(-110 - std::ilogb(lo), 126 - std::ilogb(hi)));
+    const float scale = std::ldexp(1.f, d.w_exp);
     std::vector<uint16_t> h(n * 3, 0);
     for (int j = 0; j < d.N; ++j)
       for (int k = 0; k < d.K; ++k) {
         uint16_t* e = &h[((size_t)(j / 32) * (d.Kp / 16) + k / 16) * 1536 + ((k / 8 % 2) * 32 + j % 32) * 8 + k % 8];
-        float r = L.w[(size_t)j * d.K + k];
+        float r = L.w[(size_t)j * d.K + k] * scale;
         for (int p = 0; p < 3; ++p) {
           uint16_t v = host_f2bf(r);
           if ((v & 0x7fff) == 0x7f80 && std::isfinite(r)) v = (uint16_t)(v - 1);
@@ -775,8 +788,8 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
     const bool g = gather && i == 0;
     return rb_gemm_f32_split(st_h, (const float*)h, ldh, g ? src : nullptr,
                              pack ? 1 : (int)(sizeof(rb_k_row) / sizeof(int64_t)), dense_len,
-                             g && !pack ? s->err_dev : nullptr, L.w, L.b, y, L.Np, (int)Ml, L.Np, L.Kp, L.act,
-                             seq_skip ? w->rows : nullptr, seq_skip ? q->bucket : 0, y ? nullptr : w->rows, m->d_out,
+                             g && !pack ? s->err_dev : nullptr, L.w, L.w_exp, L.b, y, L.Np, (int)Ml, L.Np, L.Kp,
+                             L.act, seq_skip ? w->rows : nullptr, seq_skip ? q->bucket : 0, y ? nullptr : w->rows, m->d_out,
                              out);
   };
   for (size_t i = 0; i < nL - (tail ? 2 : 0) - (ghead ? 1 : 0); ++i) {

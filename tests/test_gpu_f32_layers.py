@@ -124,6 +124,70 @@ def test_f32_layer_error_is_no_larger_than_the_fp32_mfma_kernels(ctx, M, N, K, d
     assert err[0] <= err[1], err
 
 
+@pytest.mark.parametrize("M,N", [(64, 64), (8256, 256), (66000, 256)])
+@pytest.mark.parametrize("e", [100, 109, 110, 111, 115, 126, 135, 148])
+def test_f32_layer_keeps_the_bits_of_tiny_values(ctx, M, N, e):
+    # values around 2^-110, under which three bf16 parts no longer hold an fp32
+    # value, down to the smallest one: as inputs against weights of 1 to 2^120,
+    # and as weights. Every product here is an fp32 value, so outputs are exact.
+    rng = np.random.default_rng(e)
+    bits = min(24, 150 - e)  # of the values' significands
+    tiny = lambda n: np.ldexp(rng.integers(1 << (bits - 1), 1 << bits, n).astype(np.float64), 1 - bits - e)  # noqa: E731
+    rows = np.unique(np.concatenate([np.arange(0, M, max(1, M // 50)), [M - 1]]))
+    k = rng.integers(0, 64, len(rows))
+    x = tiny(len(rows)).astype(np.float32)
+    b = np.zeros(N, np.float32)
+    for s in (0, 60, 120):
+        X = rng.standard_normal((M, 64)).astype(np.float32)
+        W = np.zeros((N, 64), np.float32)
+        W[:, :] = np.ldexp(1.0, s + np.arange(N) % 2)[:, None]
+        W[N - 1] = 0.25
+        base, _ = _run(ctx, [(W, b, "none")], X)
+        X[rows] = 0
+        X[rows, k] = x
+        y, _ = _run(ctx, [(W, b, "none")], X)
+        want = x.astype(np.float64)[:, None] * W[:, 0].astype(np.float64)
+        exact = want == want.astype(np.float32)
+        assert exact[:, :N - 1].all() and np.array_equal(y[rows][exact], want[exact].astype(np.float32)), s
+        other = np.setdiff1d(np.arange(M), rows)
+        assert np.array_equal(y[other], base[other])
+        # the same values as weights (W of N rows, one value each), inputs 2^s
+        W = np.zeros((N, 64), np.float32)
+        w, kw = tiny(N).astype(np.float32), rng.integers(0, 64, N)
+        W[np.arange(N), kw] = w
+        y, _ = _run(ctx, [(W, b, "none")], np.full((M, 64), 2.0 ** s, np.float32))
+        assert np.array_equal(y, np.tile((w.astype(np.float64) * 2.0 ** s).astype(np.float32), (M, 1))), s
+
+
+def test_f32_layer_tiny_values_beside_ordinary_ones(ctx):
+    # a tiny value counts where its product does, and nowhere else
+    X = np.zeros((40, 64), np.float32)
+    X[:, 0] = np.float32(1.2345678) * np.float32(2.0 ** -120)
+    X[:, 1] = 1.0
+    W = np.zeros((64, 64), np.float32)
+    W[0, 0], W[0, 1] = 2.0 ** 120, 1.0   # 1 + 1.2345678
+    W[1, 0], W[1, 1] = 1.0, 1.0          # 1 + 2^-120: 1
+    W[2, 0], W[2, 1] = 2.0 ** 100, 0.0   # 2^-20
+    y, _ = _run(ctx, [(W, np.zeros(64, np.float32), "none")], X)
+    x = float(X[0, 0])
+    assert np.array_equal(y[:, 0], np.full(40, np.float32(1.0 + x * 2.0 ** 120)))
+    assert np.array_equal(y[:, 1], np.ones(40, np.float32))
+    assert np.array_equal(y[:, 2], np.full(40, np.float32(x * 2.0 ** 100))) and not y[:, 3:].any()
+
+
+def test_f32_layers_tiny_weights_and_huge_inputs(ctx):
+    # a tiny weight scales its layer: sums that overflow for it (or for X's own
+    # scale) are computed on fp32 operands, from the unscaled weights
+    rng = np.random.default_rng(7)
+    W = (rng.standard_normal((128, 64)) / 8).astype(np.float32)
+    W[0, 0] = 1e-44
+    X = rng.standard_normal((100, 64)).astype(np.float32)
+    X[3], X[5], X[7] = X[3] * np.float32(1e17), X[5] * np.float32(1e30), X[7] * np.float32(1e37)
+    X[9] = X[9] * np.float32(1e-36)
+    y, _ = _run(ctx, [(W, np.zeros(128, np.float32), "none")], X)
+    assert _err(y, X.astype(np.float64) @ W.astype(np.float64).T) <= 1e-6
+
+
 @pytest.mark.parametrize("M", [40, 33000])
 def test_f32_layers_non_finite_and_huge(ctx, M):
     # rows with infinities, NaN and values whose products or bf16 roundings
