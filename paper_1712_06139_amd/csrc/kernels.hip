@@ -94,7 +94,13 @@ __device__ __forceinline__ bool batch_in_range(const rb_k_batch& b, int max_rows
 // lengths it was 16.8.
 // fill: the rows that no batch in range covers are set to padding too: each
 // batch's workgroup sets those from its end to the next batch's start (the
-// first one also those before it; without any, the first workgroup all).
+// first one also those before it; without any, the first workgroup all). Every
+// workgroup reads every batch for it, so the launch does so for up to ROUTE_NT
+// batches, a descriptor a thread; more take a launch of their own first
+// (k_fill_rows). One-row batches of a 64-128-16 MLP, us for the whole group by
+// the routing launch and with a launch of its own: 1024 batches 25.6 and 18.8,
+// 8192 409 and 48, 65536 22770 and 341; up to 512 a launch costs more than it
+// reads (an idle server's ranking request: 2.5 of 36 us).
 template <int MAXR>
 __global__ __launch_bounds__(ROUTE_NT) void k_route(int kind, const rb_k_batch* __restrict__ batches, int n_batches,
                                                     const rb_k_req* __restrict__ reqs, int n_reqs,
@@ -258,6 +264,12 @@ __global__ __launch_bounds__(ROUTE_NT) void k_route(int kind, const rb_k_batch* 
     }
     rows[b.row_base + p] = rw;
   }
+}
+
+// Every row of a group's row space as padding.
+__global__ __launch_bounds__(256) void k_fill_rows(rb_k_row* __restrict__ rows, int n) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r < n) rows[r] = rb_k_row{-1, 0, -1, -1};
 }
 
 // ---------------------------------------------------------------- assemble
@@ -1403,6 +1415,12 @@ rb_status rb_route_bags(void* stream, int32_t kind, const rb_k_batch* batches, i
   if (kind != RB_MODEL_MLP && !lens) return RB_EINVAL;
   if (kind == RB_MODEL_RANKING && (n_tables < 1 || n_tables > MAX_TABLES)) return RB_EINVAL;
   if (n_batches == 0) return RB_OK;
+  if (fill && n_batches > ROUTE_NT) {
+    if (n_rows_total > 0)
+      hipLaunchKernelGGL(k_fill_rows, dim3((unsigned)(((int64_t)n_rows_total + 255) / 256)), dim3(256), 0,
+                         (hipStream_t)stream, rows, n_rows_total);
+    fill = 0;
+  }
 #define RB_R(MAXR)                                                                                                    \
   hipLaunchKernelGGL(k_route<MAXR>, dim3(n_batches), dim3(ROUTE_NT), 0, (hipStream_t)stream, kind, batches, n_batches, \
                      reqs, n_reqs, lens, lens_len, d_in, d_out, n_tables, rows, n_rows_total, out_len, ends, fill, err)

@@ -926,6 +926,57 @@ def test_route_fills_rows_no_batch_covers(layout, max_rows):
     assert np.array_equal(got[~covered], np.tile([-1, 0, -1, -1], (int((~covered).sum()), 1)))
 
 
+def _route_one_row_batches(n):
+    """n one-row batches at rows 1, 3, 5, ... of 2 n + 3 through rb_route_bags
+    with the rows between filled: a call, its row map and its inputs."""
+    kb = np.zeros(n, rb.K_BATCH_DTYPE)
+    kb["req_begin"], kb["n_req"], kb["padded"], kb["real"] = np.arange(n), 1, 1, 1
+    kb["row_base"] = 1 + 2 * np.arange(n)
+    kr = np.zeros(n, rb.K_REQ_DTYPE)
+    kr["n_rows"], kr["dense_off"], kr["dense_end"], kr["out_off"] = 1, np.arange(n) * 2, np.arange(n) * 2 + 2, np.arange(n)
+    rows = torch.full((2 * n + 3, 4), 77, dtype=torch.int64, device=DEV)
+    err, b_d, r_d = _err(), _dev(kb.view(np.uint8)), _dev(kr.view(np.uint8))
+    f = rb.lib().rb_route_bags
+    f.argtypes = rb.lib().rb_k_route.argtypes[:-1] + [rb.C.c_void_p, rb.C.c_int32, rb.C.c_int32, rb.C.c_void_p]
+    f.restype = rb.C.c_int32
+
+    def call():
+        rb.check(f(_stream(), rb.RB_MODEL_MLP, rb.dptr(b_d), n, rb.dptr(r_d), n, None, 0, 2, 1, 0, rb.dptr(rows),
+                   2 * n + 3, n, None, 1, 4096, rb.dptr(err)), "route")
+    return call, rows, (err, b_d, r_d)
+
+
+@pytest.mark.parametrize("n", [1, 511, 512, 513, 3000])
+def test_route_fills_around_many_batches(n):
+    # up to 512 batches the routing launch fills the rows between them itself,
+    # beyond them a launch of its own does
+    call, rows, (err, *_) = _route_one_row_batches(n)
+    call()
+    want = np.tile([-1, 0, -1, -1], (2 * n + 3, 1))
+    want[1:2 * n:2, 0], want[1:2 * n:2, 3] = np.arange(n) * 2, np.arange(n)
+    assert np.array_equal(rows.cpu().numpy(), want) and int(err) == 0
+
+
+def test_route_of_many_batches_takes_linear_time():
+    # 8 times the batches: about 8 times as long (64 times if every batch looked
+    # at every other one)
+    best = []
+    for n in (8192, 65536):
+        call, _, keep = _route_one_row_batches(n)
+        call()
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        best.append(min(times))
+    assert best[1] <= 20 * best[0], best
+
+
 @pytest.mark.parametrize("nt", [1, 3, 26, 33, 64])
 def test_route_ends_of_bags(nt):
     # 16-byte loads of the lengths at every alignment and tail, and the running
