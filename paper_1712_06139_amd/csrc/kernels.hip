@@ -202,9 +202,12 @@ __global__ __launch_bounds__(ROUTE_NT) void k_route(int kind, const rb_k_batch* 
         typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
         const int32_t* l = lens + rq.lens_off + (int64_t)e * n_tables;
         int32_t* en = ends ? ends + b.row_base + p : nullptr;
-        bool neg = false;
+        // 32-bit sums while every length is under 2^25 (64 tables then stay under
+        // 2^31): 64-bit ones with a test for negative lengths took 5.6 us for 8
+        // rows of 26 bags (5.5 this way), 7.8 for 512 batches of 16 rows of 64 (7.5)
+        uint32_t any = 0, sum = 0;  // the lengths' bits, their sum
         for (int f0 = 0; f0 < n_tables; f0 += 32) {
-          int v[32];
+          uint32_t v[32];
 #pragma unroll
           for (int u = 0; u < 32; u += 4) {
             const int f = f0 + u;
@@ -218,12 +221,21 @@ __global__ __launch_bounds__(ROUTE_NT) void k_route(int kind, const rb_k_batch* 
           }
 #pragma unroll
           for (int u = 0; u < 32; ++u) {
-            neg |= v[u] < 0;
-            c += v[u];
-            if (en && f0 + u < n_tables) en[(int64_t)(f0 + u) * n_rows_total] = (int32_t)c;
+            any |= v[u];
+            sum += v[u];
+            if (en && f0 + u < n_tables) en[(int64_t)(f0 + u) * n_rows_total] = (int32_t)sum;
           }
         }
-        if (neg || c > INT32_MAX) s_bad[i] = 1;
+        c = sum;
+        if (any >> 25) {
+          c = 0;
+          for (int f = 0; f < n_tables; ++f) {
+            if (l[f] < 0) s_bad[i] = 1;
+            c += l[f];
+            if (en) en[(int64_t)f * n_rows_total] = (int32_t)c;
+          }
+          if (c > INT32_MAX) s_bad[i] = 1;
+        }
       } else if (kind == RB_MODEL_SEQPOOL) {
         const int v = lens[rq.lens_off + e];
         if (v < 1 || v > b.seq_T) s_bad[i] = 1;

@@ -1015,6 +1015,36 @@ def test_route_ends_of_bags(nt):
     assert int(err) == 0
 
 
+@pytest.mark.parametrize("bad", [None, -1, 1 << 30])
+def test_route_long_and_bad_bags(bad):
+    # lengths of 2^25 and more are summed exactly beside short ones; a negative
+    # length, or a row of more than 2^31 ids, rejects its request alone
+    nt = 5
+    ln = np.array([[3, 1 << 25, 0, (1 << 26) + 7, 2], [1, 2, 3, 4, 5], [1 << 28] * 5, [0] * 5], np.int32)
+    if bad is not None:
+        ln[1] = bad
+    cnt = ln.astype(np.int64).sum(1)
+    kr = np.zeros(4, rb.K_REQ_DTYPE)
+    kr["n_rows"], kr["dense_off"], kr["dense_end"], kr["lens_off"] = 1, np.arange(4), np.arange(4) + 1, np.arange(4) * nt
+    kr["ids_off"], kr["out_off"] = np.arange(4) * 7, np.arange(4)
+    kr["ids_end"] = kr["ids_off"] + cnt
+    kb = np.array([(0, 4, 0, 5, 4, 0)], rb.K_BATCH_DTYPE)
+    rows, ends = torch.zeros((5, 4), dtype=torch.int64, device=DEV), torch.full((nt, 5), -5, dtype=torch.int32, device=DEV)
+    err, b_d, r_d, l_d = _err(), _dev(kb.view(np.uint8)), _dev(kr.view(np.uint8)), _dev(ln.reshape(-1))
+    f = rb.lib().rb_route_bags
+    f.argtypes = rb.lib().rb_k_route.argtypes[:-1] + [rb.C.c_void_p, rb.C.c_int32, rb.C.c_int32, rb.C.c_void_p]
+    f.restype = rb.C.c_int32
+    rb.check(f(_stream(), rb.RB_MODEL_RANKING, rb.dptr(b_d), 1, rb.dptr(r_d), 4, rb.dptr(l_d), ln.size, 1, 1, nt,
+               rb.dptr(rows), 5, 4, rb.dptr(ends), 0, 512, rb.dptr(err)), "route")
+    got, e = rows.cpu().numpy(), ends.cpu().numpy()
+    good = [r for r in range(4) if bad is None or r != 1]
+    assert int(err) == (bad is not None)
+    assert np.array_equal(got[good, 0], np.array(good)) and np.array_equal(got[good, 1], np.array(good) * 7)
+    assert np.array_equal(e[:, good], np.cumsum(ln.astype(np.int64), 1).T[:, good])
+    assert bad is None or (got[1, 0] == -1 and got[1, 3] == -1)
+    assert (got[4, [0, 3]] == -1).all()
+
+
 @pytest.mark.parametrize("n,T,D,ldh", [(3, 512, 256, 256), (3, 40, 1000, 1000), (2, 70, 517, 520), (2, 33, 513, 513),
                                        (600, 40, 256, 256), (600, 17, 6, 7)])
 def test_seqpool_parts_and_wave_counts(n, T, D, ldh):
