@@ -1202,20 +1202,81 @@ __global__ __launch_bounds__(MT_NT) void k_mlp_tail(const bf16_t* __restrict__ H
 
 constexpr int POOL_MAX_D = 1024, POOL_MAX_OUT = 16;
 
-// One workgroup per sequence slot. The slot's real tokens are summed in
-// POOL_PARTS consecutive parts (part p: tokens [p L / 16, (p + 1) L / 16); tokens
-// past L are never read, so padding cannot reach the mean), each in token
-// order; the partial sums are added in part order and divided by L: a fixed
-// order, so the result depends on the sequence only, not on NW. A wave sums
-// POOL_PARTS / NW parts side by side, each lane owning float4 columns, with 8
-// token loads in flight; a launch waits for one wave's chain of round trips,
-// so 16 waves take a sequence when there are few (60 sequences of up to 512
-// tokens: 20.4 us with 4 waves of one part and 4 loads each, now 12.8), and 4
-// otherwise. The first 256 threads
-// then compute the head logits with fixed-order reductions and thread 0 applies
-// the softmax and writes the request's output row.
-constexpr int POOL_PARTS = 16, POOL_COLS = 512;
-template <int NW>
+// One workgroup per sequence slot. The slot's real tokens are summed in P
+// consecutive parts (part p: tokens [p L / P, (p + 1) L / P); tokens past L are
+// never read, so padding cannot reach the mean), each in token order; the
+// partial sums are added in part order and divided by L: a fixed order, and P
+// depends on L only (4 up to POOL_SHORT tokens, else 16), so the result depends
+// on the sequence only, not on NW nor on its slot's length. A wave sums P / NW
+// parts side by side, each lane owning float4 columns, with 8 token loads (4 of
+// a short sequence) in flight; a launch waits for one wave's chain of round
+// trips, so 16 waves take a long sequence when there are few, and 4 otherwise.
+// Back to back, us, with 4 parts, with 16 and now (up to 512 tokens): 60
+// sequences x 1024 columns 52, 28 and 28; 256 x 256 16.7, 17.5 and 14.9; up to 4
+// tokens: 60 x 256 3.9, 4.7 and 4.0; 4096 x 1024 16.8, 35.7 and 17.8. The first
+// 256 threads then compute the head logits with fixed-order reductions and thread
+// 0 applies the softmax and writes the request's output row.
+// POOL_COLS: columns of 16 parts summed at a time (32 KB of LDS).
+constexpr int POOL_SHORT = 64, POOL_PARTS = 16, POOL_COLS = 512;
+
+// A wave's parts of columns [0, n) of h: parts p0 .. p0 + PP - 1 of `parts`, U
+// tokens of each at a time, to sums[p ld + c]. With PP > 1 or U > 4 every part
+// has at least one token.
+template <int PP, int U>
+__device__ __forceinline__ void pool_sum(const float* __restrict__ h, int ldh, int n, bool vec, int L, int parts, int p0,
+                                         float* sums, int ld, int lane) {
+  int t0[PP], t1[PP];
+#pragma unroll
+  for (int i = 0; i < PP; ++i) {
+    t0[i] = L * (p0 + i) / parts;
+    t1[i] = L * (p0 + i + 1) / parts;
+  }
+  if (vec) {
+    const int least = PP == 1 ? t1[0] - t0[0] : L / parts;  // tokens of a part: this many or one more
+    for (int c = lane * 4; c < n; c += 256) {
+      f32x4_t s[PP], v[PP][U];
+#pragma unroll
+      for (int i = 0; i < PP; ++i) s[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+      int k = 0;
+      for (; k + U <= least; k += U) {
+#pragma unroll
+        for (int i = 0; i < PP; ++i)
+#pragma unroll
+          for (int u = 0; u < U; ++u) v[i][u] = *(const f32x4_t*)(h + (int64_t)(t0[i] + k + u) * ldh + c);
+#pragma unroll
+        for (int i = 0; i < PP; ++i)
+#pragma unroll
+          for (int u = 0; u < U; ++u) s[i] += v[i][u];
+      }
+      if constexpr (PP == 1 && U <= 4) {
+        for (; k < least; ++k) s[0] += *(const f32x4_t*)(h + (int64_t)(t0[0] + k) * ldh + c);
+      } else {  // at most U tokens of each part are left: loads past them repeat its last one
+#pragma unroll
+        for (int i = 0; i < PP; ++i)
+#pragma unroll
+          for (int u = 0; u < U; ++u) v[i][u] = *(const f32x4_t*)(h + (int64_t)min(t0[i] + k + u, t1[i] - 1) * ldh + c);
+#pragma unroll
+        for (int i = 0; i < PP; ++i)
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (t0[i] + k + u < t1[i]) s[i] += v[i][u];
+      }
+#pragma unroll
+      for (int i = 0; i < PP; ++i) *(f32x4_t*)&sums[(p0 + i) * ld + c] = s[i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < PP; ++i)
+      for (int c = lane; c < n; c += 64) {
+        float s = 0.f;
+        for (int t = t0[i]; t < t1[i]; ++t) s += h[(int64_t)t * ldh + c];
+        sums[(p0 + i) * ld + c] = s;
+      }
+  }
+}
+
+// LONG: slots of more than POOL_SHORT tokens.
+template <int NW, bool LONG>
 __global__ __launch_bounds__(NW * 64) void k_seqpool(const rb_k_row* __restrict__ rows, int n_seqs, int T,
                                                      int64_t packed_rows, const float* __restrict__ H, int ldh, int D,
                                                      const float* __restrict__ Wh,
@@ -1227,63 +1288,36 @@ __global__ __launch_bounds__(NW * 64) void k_seqpool(const rb_k_row* __restrict_
   int L = (int)min(max(rw.aux, (int64_t)0), (int64_t)T);  // reads stay inside the slot
   // packed tokens: the sequence's rows [rows[r].lens, + L) of packed_rows
   if (packed_rows > 0 && (rw.lens < 0 || rw.lens + L > packed_rows)) L = 0;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  extern __shared__ float pool_lds[];  // partial sums of up to POOL_COLS columns, then the pooled row
-  const int ld = min(D, POOL_COLS);
-  float* pooled = pool_lds + POOL_PARTS * ld;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  extern __shared__ float pool_lds[];  // the pooled row, then the partial sums of a pass of columns
+  float* pooled = pool_lds;
+  float* sums = pool_lds + (D + 3) / 4 * 4;
   __shared__ float part[4][POOL_MAX_OUT];
   const float* h = H + (packed_rows > 0 ? rw.lens : (int64_t)r * T) * ldh;
-  constexpr int PP = POOL_PARTS / NW, U = 8 / PP;  // parts per wave, tokens in flight per part
-  int t0[PP], t1[PP], longest = 0;
-#pragma unroll
-  for (int i = 0; i < PP; ++i) {
-    const int p = wid * PP + i;
-    t0[i] = (int)((int64_t)L * p / POOL_PARTS);
-    t1[i] = (int)((int64_t)L * (p + 1) / POOL_PARTS);
-    longest = max(longest, t1[i] - t0[i]);
-  }
+  const bool vec = (D & 3) == 0 && (ldh & 3) == 0;
   const float inv = 1.f / (float)max(L, 1);
-  for (int c0 = 0; c0 < D; c0 += POOL_COLS) {
-    const int n = min(D - c0, POOL_COLS);
-    const float* hc = h + c0;
-    if ((D & 3) == 0 && (ldh & 3) == 0) {
-      for (int c = lane * 4; c < n; c += 256) {
-        f32x4_t s[PP];
+  if (!LONG || L <= POOL_SHORT) {
+    if (NW == 4 || wid < 4) pool_sum<1, 4>(h, ldh, D, vec, L, 4, wid, sums, D, lane);
+    __syncthreads();
+    for (int c = tid; c < D; c += NW * 64)
+      pooled[c] = (((sums[c] + sums[D + c]) + sums[2 * D + c]) + sums[3 * D + c]) * inv;
+    __syncthreads();
+  } else {
+    constexpr int PP = POOL_PARTS / NW;
+    const int ld = min(D, POOL_COLS);
+    for (int c0 = 0; c0 < D; c0 += POOL_COLS) {
+      const int n = min(D - c0, POOL_COLS);
+      pool_sum<PP, 8 / PP>(h + c0, ldh, n, vec, L, POOL_PARTS, wid * PP, sums, ld, lane);
+      __syncthreads();
+      for (int c = tid; c < n; c += NW * 64) {
+        float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < PP; ++i) s[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < longest; k += U) {
-          f32x4_t v[PP][U];
-#pragma unroll
-          for (int i = 0; i < PP; ++i)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-              if (t0[i] + k + u < t1[i]) v[i][u] = *(const f32x4_t*)(hc + (int64_t)(t0[i] + k + u) * ldh + c);
-#pragma unroll
-          for (int i = 0; i < PP; ++i)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-              if (t0[i] + k + u < t1[i]) s[i] += v[i][u];
-        }
-#pragma unroll
-        for (int i = 0; i < PP; ++i) *(f32x4_t*)&pool_lds[(wid * PP + i) * ld + c] = s[i];
+        for (int p = 0; p < POOL_PARTS; ++p) s += sums[p * ld + c];
+        pooled[c0 + c] = s * inv;
       }
-    } else {
-#pragma unroll
-      for (int i = 0; i < PP; ++i)
-        for (int c = lane; c < n; c += 64) {
-          float s = 0.f;
-          for (int t = t0[i]; t < t1[i]; ++t) s += hc[(int64_t)t * ldh + c];
-          pool_lds[(wid * PP + i) * ld + c] = s;
-        }
+      __syncthreads();
     }
-    __syncthreads();
-    for (int c = tid; c < n; c += NW * 64) {
-      float s = 0.f;
-#pragma unroll
-      for (int p = 0; p < POOL_PARTS; ++p) s += pool_lds[p * ld + c];
-      pooled[c0 + c] = s * inv;
-    }
-    __syncthreads();
   }
   for (int j = 0; j < n_out && tid < 256; ++j) {
     float s = 0.f;
@@ -1592,13 +1626,16 @@ rb_status rb_k_seqpool(void* stream, const rb_k_row* rows, int32_t n_seqs, int32
   if (act != RB_ACT_NONE && act != RB_ACT_SOFTMAX) return RB_EINVAL;
   if (!rows || !H || !Wh || !bh || !out) return RB_EINVAL;
   if (n_seqs == 0) return RB_OK;
-  const size_t lds = ((size_t)POOL_PARTS * std::min(D, POOL_COLS) + D) * sizeof(float);
-  if (n_seqs < (int)device_cus())  // fewer workgroups than compute units: a launch takes as long as one of them
-    hipLaunchKernelGGL(k_seqpool<16>, dim3(n_seqs), dim3(1024), lds, (hipStream_t)stream, rows, n_seqs, seq_T,
-                       packed_rows, H, ldh, D, Wh, bh, n_out, act, out);
-  else
-    hipLaunchKernelGGL(k_seqpool<4>, dim3(n_seqs), dim3(256), lds, (hipStream_t)stream, rows, n_seqs, seq_T, packed_rows,
-                       H, ldh, D, Wh, bh, n_out, act, out);
+  // the pooled row (whole 16 bytes) and the partial sums of 4 parts or, for long slots, of a pass of 16
+  const size_t sums = seq_T <= POOL_SHORT ? 4 * D : std::max(4 * D, POOL_PARTS * std::min(D, POOL_COLS));
+  const size_t lds = ((size_t)(D + 3) / 4 * 4 + sums) * sizeof(float);
+#define RB_P(NW, LONG)                                                                                               \
+  hipLaunchKernelGGL((k_seqpool<NW, LONG>), dim3(n_seqs), dim3(NW * 64), lds, (hipStream_t)stream, rows, n_seqs, seq_T, \
+                     packed_rows, H, ldh, D, Wh, bh, n_out, act, out)
+  if (seq_T <= POOL_SHORT) RB_P(4, false);
+  else if (n_seqs < (int)device_cus()) RB_P(16, true);  // a launch takes as long as one workgroup
+  else RB_P(4, true);
+#undef RB_P
   return launch_status();
 }
 

@@ -1069,6 +1069,33 @@ def test_seqpool_parts_and_wave_counts(n, T, D, ldh):
     assert torch.equal(few, out[:4])
 
 
+@pytest.mark.parametrize("D", [6, 256, 1000, 1024])
+def test_seqpool_bits_do_not_depend_on_the_slots_length(D):
+    # sequences of up to 64 tokens (four parts) and more (16) in slots of their
+    # own length, 64, 65 and 512 tokens, few and many of them: the kernels for
+    # short and long slots and both wave counts give a sequence the same bits
+    rng = np.random.default_rng(D)
+    lens = np.array([1, 2, 3, 4, 5, 31, 63, 64, 65, 66, 80, 300])
+    data = [rng.standard_normal((L, D)).astype(np.float32) for L in lens]
+    Wh, bh = rng.standard_normal((2, D)).astype(np.float32), rng.standard_normal(2).astype(np.float32)
+    Wd, bd = _dev(Wh), _dev(bh)
+    ref = np.stack([d.astype(np.float64).mean(0) for d in data]) @ Wh.T.astype(np.float64) + bh
+    got = {}
+    for T, copies in ((64, 1), (64, 60), (65, 1), (512, 1), (512, 30)):
+        pick = np.tile(np.nonzero(lens <= T)[0], copies)
+        H = torch.zeros(len(pick), T, D, device=DEV)
+        for i, p in enumerate(pick):
+            H[i, :lens[p]] = _dev(data[p]) if i < len(pick) // copies else H[i % (len(pick) // copies), :lens[p]]
+        rows = _rows_dev(np.zeros(len(pick)), lens[pick], np.arange(len(pick)) * 2)
+        out = torch.zeros(len(pick), 2, device=DEV)
+        rb.check(rb.lib().rb_k_seqpool(_stream(), rb.dptr(rows), len(pick), T, 0, rb.dptr(H), D, D, rb.dptr(Wd),
+                                       rb.dptr(bd), 2, rb.RB_ACT_NONE, rb.dptr(out)), "seqpool")
+        for p, y in zip(pick, out.cpu().numpy()):
+            assert np.array_equal(got.setdefault(p, y), y), (T, copies, lens[p])
+    err = np.abs(np.stack([got[p] for p in range(len(lens))]) - ref)
+    assert np.max(err / (np.abs(ref).max(axis=1, keepdims=True) + np.sqrt(D))) <= 1e-6
+
+
 @pytest.mark.parametrize("M", [1, 31, 33, 65, 257, 600])
 @pytest.mark.parametrize("N,K", [(128, 64), (1024, 192), (4096, 448), (8192, 576)])
 def test_gemm_bf16_few_rows(M, N, K):
