@@ -443,8 +443,8 @@ constexpr int EMB_CHUNK = 8;      // ids loaded (one per lane of a group) per ro
 // 115 us).
 // A wave takes the bags of 8 ROUNDS rows, bag i in lane i first:
 //  - a bag's place among its row's ids comes from the routing step (`ends`:
-//    two loads per bag; without it, from an 8-lane sum of the preceding bag
-//    lengths);
+//    two loads per bag; without it, with 8 bags a wave, from an 8-lane sum of
+//    the preceding bag lengths);
 //  - the lanes rank the bags by length (six ballots on a capped key) and the
 //    wave walks 8 of them at a time, longest first: the bags of a round then have
 //    similar lengths, and the longest bounds the round's loop;
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(256, ROUNDS == 1 ? 8 : 7) void k_embbag(const rb_k_
   //    id's position in the ids arena
   int L = -1;
   pos_t pos = 0;
-  if (ends) {
+  if (ROUNDS > 1 || ends) {
     if (lane < NB && r0 + lane < n_rows) {
       const int row = r0 + lane;
       const int e1 = ends[(int64_t)t * n_rows + row], e0 = t ? ends[(int64_t)(t - 1) * n_rows + row] : 0;
@@ -492,39 +492,36 @@ __global__ __launch_bounds__(256, ROUNDS == 1 ? 8 : 7) void k_embbag(const rb_k_
       pos = to_pos(aux + e0);
     }
   } else {
-    for (int i = 0; i < ROUNDS; ++i) {
-      const int row = r0 + 8 * i + g;
-      int len = -1;
-      pos_t p = 0;
-      if (row < n_rows) {
-        const rb_k_row rw = rows[row];
-        if (rw.src < 0) {
-          len = -2;
-        } else {
-          // lane l8 loads the lengths of tables l8, l8 + 8, ... below t and
-          // the bag's own length, all issued before any is used
-          int v[MAX_TABLES / 8];
+    int len = -1;
+    pos_t p = 0;
+    if (r0 + g < n_rows) {
+      const rb_k_row rw = rows[r0 + g];
+      if (rw.src < 0) {
+        len = -2;
+      } else {
+        // lane l8 loads the lengths of tables l8, l8 + 8, ... below t and the
+        // bag's own length, all issued before any is used
+        int v[MAX_TABLES / 8];
 #pragma unroll
-          for (int u = 0; u < MAX_TABLES / 8; ++u) {
-            const int f = l8 + 8 * u;
-            v[u] = f < t ? lens[rw.lens + f] : 0;
-          }
-          len = lens[rw.lens + t];
-          int pre = 0;
-#pragma unroll
-          for (int u = 0; u < MAX_TABLES / 8; ++u) pre += v[u];
-          pre += __shfl_xor(pre, 1);
-          pre += __shfl_xor(pre, 2);
-          pre += __shfl_xor(pre, 4);
-          p = to_pos(rw.aux + pre);
+        for (int u = 0; u < MAX_TABLES / 8; ++u) {
+          const int f = l8 + 8 * u;
+          v[u] = f < t ? lens[rw.lens + f] : 0;
         }
+        len = lens[rw.lens + t];
+        int pre = 0;
+#pragma unroll
+        for (int u = 0; u < MAX_TABLES / 8; ++u) pre += v[u];
+        pre += __shfl_xor(pre, 1);
+        pre += __shfl_xor(pre, 2);
+        pre += __shfl_xor(pre, 4);
+        p = to_pos(rw.aux + pre);
       }
-      const int a = __shfl(len, l8 * 8);
-      const pos_t b = __shfl(p, l8 * 8);
-      if (g == i) {
-        L = a;
-        pos = b;
-      }
+    }
+    const int a = __shfl(len, l8 * 8);
+    const pos_t b = __shfl(p, l8 * 8);
+    if (g == 0) {
+      L = a;
+      pos = b;
     }
   }
   // 2. ranked longest first (ties by row; lengths past 60 count as equal): bag
@@ -1558,15 +1555,25 @@ rb_status rb_embbag_ends(void* stream, const rb_k_row* rows, int32_t n_rows_tota
   // waves on, else 8 (26 bags a row: 32768 rows 105 us with 32, 110 with 16, 121
   // with 8; 4096 rows 24, 17 and 17; 64 rows 11, 8.7 and 5.7)
   const int64_t bags = (int64_t)n_rows_total * n_tables, cus = device_cus();
-  const int rounds = bags >= 32 * 48 * cus ? 4 : (bags >= 16 * 24 * cus ? 2 : 1);
+  // Without the ends 8: the lengths that a wave reads for each round's bags, one
+  // round after another, cost more than the longer waves save (32768 rows: 189 us
+  // with 32, 172 with 16, 154 with 8). Tables or ids past 32-bit offsets take the
+  // same numbers (26 bags a row of a 4 GiB table: 512 rows 20.2
+  // us with 32, 8.0 with 8; 4096 rows 38.3 and 30.5).
+  const int rounds = !ends ? 1 : (bags >= 32 * 48 * cus ? 4 : (bags >= 16 * 24 * cus ? 2 : 1));
 #define RB_E(R, B)                                                                                                   \
   hipLaunchKernelGGL((k_embbag<R, B>), dim3((unsigned)((n_rows_total + 32 * R - 1) / (32 * R)) * n_tables), dim3(256), 0, \
                      (hipStream_t)stream, rows, n_rows_total, lens, ends, ids, ids_len, (const bf16_t* const*)tables, \
                      n_tables, table_rows, dense, n_dense, (bf16_t*)X, ldx, pad, err)
-  if (big) RB_E(4, true);
-  else if (rounds == 4) RB_E(4, false);
-  else if (rounds == 2) RB_E(2, false);
-  else RB_E(1, false);
+  if (big) {
+    if (rounds == 4) RB_E(4, true);
+    else if (rounds == 2) RB_E(2, true);
+    else RB_E(1, true);
+  } else {
+    if (rounds == 4) RB_E(4, false);
+    else if (rounds == 2) RB_E(2, false);
+    else RB_E(1, false);
+  }
 #undef RB_E
   return launch_status();
 }

@@ -836,13 +836,24 @@ def test_split_vector_and_scalar_paths(d_out, ldy):
     assert np.array_equal(o, want)
 
 
+def _embbag_ends(*args):
+    """rb_embbag_ends: rb_k_embbag's arguments with the bags' ends after the lengths."""
+    f = rb.lib().rb_embbag_ends
+    ts = list(rb.lib().rb_k_embbag.argtypes)
+    f.argtypes, f.restype = ts[:4] + [rb.C.c_void_p] + ts[4:], rb.C.c_int32
+    rb.check(f(*args), "rb_embbag_ends")
+
+
+@pytest.mark.parametrize("ends,big", [(False, False), (True, False), (False, True), (True, True)])
 @pytest.mark.parametrize("nt", [1, 26, 64])
 @pytest.mark.parametrize("rows", [1, 8, 9, 33, 70, 3900, 16400])
-def test_embbag_waves_of_8_16_and_32_bags(rows, nt):
-    # every number of bags per wave (8, 16 and 32, by rows x tables), at its row
-    # edges: the sums of exactly representable table rows match integer sums bit
-    # for bit, whatever the bag's rank (lengths with ties, zeros and more than
-    # the 60 that rank as equal), and the last row's bags are whole
+def test_embbag_waves_of_8_16_and_32_bags(rows, nt, ends, big):
+    # every number of bags per wave (with the bags' ends 8, 16 and 32, by rows x
+    # tables; from the lengths 8), at its row edges, with 32-bit offsets and (an
+    # arena declared past them) 64-bit ones: the sums of exactly representable
+    # table rows match integer sums bit for bit, whatever the bag's rank (lengths
+    # with ties, zeros and more than the 60 that rank as equal), and the last row's
+    # bags are whole
     g = torch.Generator(device=DEV).manual_seed(rows * nt)
     tr = 50
     tabs = torch.randint(0, 2, (nt, tr, 64), device=DEV, generator=g).to(torch.bfloat16)
@@ -858,15 +869,47 @@ def test_embbag_waves_of_8_16_and_32_bags(rows, nt):
     dense = torch.randn(rows, device=DEV, generator=g)
     X = torch.full((rows + 1, ldx), -9.0, device=DEV, dtype=torch.bfloat16)
     l32, err = lens.to(torch.int32).reshape(-1).contiguous(), _err()
-    rb.check(rb.lib().rb_k_embbag(_stream(), rb.dptr(rows_d), rows, rb.dptr(l32), rb.dptr(ids), ids.numel(),
-                                  rb.dptr(ptrs), nt, tr, 64, rb.dptr(dense), 1, rb.dptr(X), ldx, 0.0, rb.dptr(err)),
-             "embbag")
+    e32 = torch.cumsum(lens, 1).to(torch.int32).T.contiguous()  # table after table
+    # every bag lies inside the ids: a longer arena is never read past them
+    _embbag_ends(_stream(), rb.dptr(rows_d), rows, rb.dptr(l32), rb.dptr(e32) if ends else None, rb.dptr(ids),
+                 1 << 31 if big else ids.numel(), rb.dptr(ptrs), nt, tr, 64, rb.dptr(dense), 1, rb.dptr(X), ldx, 0.0,
+                 rb.dptr(err))
     bag = torch.repeat_interleave(torch.arange(rows * nt, device=DEV), lens.reshape(-1))
     ref = torch.zeros(rows * nt, 64, device=DEV)
     ref.index_add_(0, bag, tabs.float()[bag % nt, ids.long()])  # sums of at most 70 ones: exact in fp32 and bf16
     assert torch.equal(X[:rows, :nt * 64].float(), ref.reshape(rows, -1))
     assert torch.equal(X[:rows, nt * 64], dense.to(torch.bfloat16)) and not X[:rows, nt * 64 + 1:].any()
     assert bool((X[rows] == -9.0).all()) and int(err) == 0
+
+
+def test_embbag_past_32_bit_offsets_is_as_fast_for_few_rows():
+    # 512 rows of 26 bags: with 64-bit offsets (an arena declared past the 32-bit
+    # ones) a launch takes about as long, not that of waves of 32 bags
+    rows, nt, tr = 512, 26, 1000
+    g = torch.Generator(device=DEV).manual_seed(1)
+    tabs = torch.randn((nt, tr, 64), device=DEV, generator=g).to(torch.bfloat16)
+    ptrs = torch.tensor([tabs[t].data_ptr() for t in range(nt)], dtype=torch.int64, device=DEV)
+    lens = torch.randint(1, 21, (rows, nt), device=DEV, generator=g)
+    ids = torch.randint(0, tr, (int(lens.sum()),), device=DEV, generator=g).to(torch.int32)
+    rm = np.zeros(rows, rb.K_ROW_DTYPE)
+    rm["aux"], rm["lens"] = (torch.cumsum(lens.sum(1), 0) - lens.sum(1)).cpu().numpy(), np.arange(rows) * nt
+    rows_d, l32 = _dev(rm.view(np.uint8)), lens.to(torch.int32).reshape(-1).contiguous()
+    X, err = torch.empty((rows, nt * 64), device=DEV, dtype=torch.bfloat16), _err()
+    best = []
+    for n_ids in (ids.numel(), 1 << 31):
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(50):
+                rb.check(rb.lib().rb_k_embbag(_stream(), rb.dptr(rows_d), rows, rb.dptr(l32), rb.dptr(ids), n_ids,
+                                              rb.dptr(ptrs), nt, tr, 64, None, 0, rb.dptr(X), nt * 64, 0.0,
+                                              rb.dptr(err)), "embbag")
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        best.append(min(times))
+    assert best[1] <= 1.6 * best[0], best
 
 
 def test_embbag_table_past_32_bit_offsets():
