@@ -77,7 +77,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   constexpr int NREG = T * T / 64;       // its accumulator registers
   constexpr int TM = WM / T, TN = WN / T;
   constexpr bool PAIR = !F32 && !OUT_F32;  // column blocks stored in pairs
-  static_assert(!PAIR || TN % 2 == 0, "column blocks are stored in pairs");
+  static_assert(F32 || TN % 2 == 0, "column blocks are stored in pairs");
   typedef typename std::conditional<F32, floatx16_t, floatx4_t>::type acc_t;
   constexpr int SA = BM / RPI / NW, SB = BN / RPI / NW;  // load instructions per wave per stage
   static_assert(SA * NW * RPI == BM && SB * NW * RPI == BN, "loads cover the tile");
@@ -298,15 +298,15 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   // l % 32 of its 32 x 32 block. bf16: row 4 (l / 16) + r and row x = l % 16 of
   // the column block, which is column b_row(j, x): for bf16 outputs the two blocks
   // of a pair give a lane eight consecutive columns, stored at once (16 bytes);
-  // for fp32 outputs a lane's four columns of one block are 16 bytes, and a row's
-  // 16 columns one 64-byte piece (eight in a lane, half of them in each of two
-  // stores, made the large MLP's last layer slower: its backlog ran at 0.995 of
-  // the speed with 32x32x16, and runs at 1.037 of it this way).
+  // for fp32 outputs two neighbouring blocks exchange halves, so that a store covers
+  // 32 columns, a whole line, of eight rows (32768 x 512 x 1024 38.3 us, 32768 x
+  // 1024 x 4096 237; with 16 columns of 16 rows a store 42.8 and 249, and 40.0 and
+  // 234 on the 32x32x16 instruction, whose blocks are 32 columns wide).
   constexpr int NG = NREG / 4;                // groups of four registers per block
-  constexpr int NC = PAIR ? 8 : 4;            // consecutive columns a lane stores
-  constexpr int JS = PAIR ? 2 : 1;            // column blocks they come from
+  constexpr int JS = F32 ? 1 : 2;             // column blocks stored at a time
+  constexpr int NC = 4 * JS;                  // values a lane holds of them
   auto row_in = [&](int g) { return F32 ? 8 * g + 4 * (lane >> 5) + (lane & 3) : 4 * (lane >> 4) + (lane & 3); };
-  // the lane's NC columns of row block i, register group g, column blocks j, j + JS - 1
+  // the lane's four columns of row block i, register group g of each of column blocks j .. j + JS - 1
   auto columns = [&](int i, int g, int j, const float (&bb)[JS], float (&q)[NC]) {
 #pragma unroll
     for (int h = 0; h < JS; ++h) {
@@ -323,16 +323,42 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   // with an output row map: the output offsets of this lane's rows, loaded
   // all at once before any is needed
   const bool mapped = OUT_F32 && om.rows != nullptr;  // uniform
-  int64_t ro[TM][NG];
+  constexpr int NO = F32 ? NG : 2;                    // rows of a row block that a lane stores
+  int64_t ro[TM][NO];
+  // the lane's o-th row of a row block (fp32 outputs of a bf16 layer: after the exchange)
+  auto out_row = [&](int o) { return F32 ? row_in(o) : 8 * o + 4 * ((lane >> 4) & 1) + (lane & 3); };
   if (mapped) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const int r = m0 + wm * WM + i * T + row_in(g);
-        ro[i][g] = r < M ? om.rows[r].out : -1;
+      for (int o = 0; o < NO; ++o) {
+        const int r = m0 + wm * WM + i * T + out_row(o);
+        ro[i][o] = r < M ? om.rows[r].out : -1;
       }
   }
+  // four fp32 columns from colq of the lane's o-th row of row block i. Streaming
+  // (nontemporal) stores: the whole chip writes its tiles' outputs at about the
+  // same time, and these drain faster than stores that allocate in L2
+  auto store_f32 = [&](int i, int o, int colq, const float* q) {
+    const int row = m0 + wm * WM + i * T + out_row(o);
+    float* dst = nullptr;
+    int n = 4;  // columns to store
+    if (mapped) {
+      if (ro[i][o] >= 0) dst = om.out + ro[i][o] + colq;
+      n = min(4, om.d_out - colq);
+    } else if (row < M) {
+      dst = (float*)Y + (int64_t)row * ldy + colq;
+    }
+    if (!dst) return;
+    if (n == 4 && ((uintptr_t)dst & 15) == 0) {
+      const f32x4_t v = {q[0], q[1], q[2], q[3]};
+      __builtin_nontemporal_store(v, (f32x4_t*)dst);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < n) dst[k] = q[k];
+    }
+  };
 #pragma unroll
   for (int j = 0; j < TN; j += JS) {
     float bb[JS];
@@ -346,37 +372,23 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
         float q[NC];
         columns(i, g, j, bb, q);
         const int row = m0 + wm * WM + i * T + row_in(g);
-        // streaming (nontemporal) stores: the whole chip writes its tiles'
-        // outputs at about the same time, and these drain faster than
-        // stores that allocate in L2
-        if constexpr (OUT_F32) {
-          float* dst = nullptr;
-          int n = NC;  // columns to store
-          if (mapped) {
-            const int64_t o = ro[i][g];
-            if (o >= 0) dst = om.out + o + colq;
-            n = min(NC, om.d_out - colq);
-          } else if (row < M) {
-            dst = (float*)Y + (int64_t)row * ldy + colq;
-          }
-          if (dst) {
-            if (n == NC && ((uintptr_t)dst & 15) == 0) {
+        if constexpr (OUT_F32 && F32) {
+          store_f32(i, g, colq, q);
+        } else if constexpr (OUT_F32) {
+          // the upper half of block j against the lower half of block j + 1: the
+          // lanes then hold 32 columns of rows 0..7 in q[0..3], of rows 8..15 in q[4..7]
 #pragma unroll
-              for (int k = 0; k < NC; k += 4) {
-                const f32x4_t v = {q[k], q[k + 1], q[k + 2], q[k + 3]};
-                __builtin_nontemporal_store(v, (f32x4_t*)(dst + k));
-              }
-            } else {
-#pragma unroll
-              for (int k = 0; k < NC; ++k)
-                if (k < n) dst[k] = q[k];
-            }
+          for (int k = 0; k < 4; ++k) {
+            const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(q[k]), __float_as_uint(q[4 + k]), false, false);
+            q[k] = __uint_as_float(x[0]);
+            q[4 + k] = __uint_as_float(x[1]);
           }
+          const int c = colq + 16 * (lane >> 5);
+          store_f32(i, 0, c, q);
+          store_f32(i, 1, c, q + 4);
         } else if (row < M) {
-          if constexpr (PAIR) {
-            const u32x4_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3]), pack2_rne(q[4], q[5]), pack2_rne(q[6], q[7])};
-            __builtin_nontemporal_store(o, (u32x4_t*)((bf16_t*)Y + (int64_t)row * ldy + colq));
-          }
+          const u32x4_t o = {pack2_rne(q[0], q[1]), pack2_rne(q[2], q[3]), pack2_rne(q[4], q[5]), pack2_rne(q[6], q[7])};
+          __builtin_nontemporal_store(o, (u32x4_t*)((bf16_t*)Y + (int64_t)row * ldy + colq));
         }
       }
   }

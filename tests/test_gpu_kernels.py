@@ -1160,3 +1160,33 @@ def test_gemm_bf16_few_rows(M, N, K):
     ref = (X[:M].double() @ W.double().T + b.double()).clamp(min=0)
     assert bool(((outs[0].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-4).all())
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("M,N,K", [(31, 128, 64), (65, 1024, 192), (200, 4096, 128), (300, 4096, 192), (600, 4096, 448),
+                                   (5000, 256, 192), (9000, 512, 128), (17000, 1024, 128), (33000, 512, 192)])
+def test_gemm_bf16_fp32_outputs_are_the_unrounded_ones(M, N, K):
+    # on every tile: fp32 outputs rounded to bf16 are the bf16 outputs, all in
+    # their places and nothing beside them, and the ones that go through a row
+    # map (rows back to front at odd offsets, fewer columns than N) are the same
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    X = torch.randn(M, K, device=DEV, generator=g).to(torch.bfloat16)
+    W = (torch.randn(N, K, device=DEV, generator=g) / K ** 0.5).to(torch.bfloat16)
+    b = torch.randn(N, device=DEV, generator=g)
+    Y16 = torch.empty(M, N, device=DEV, dtype=torch.bfloat16)
+    Y32 = torch.full((M + 1, N + 8), -3.0, device=DEV)
+    for Y, ldy, f32 in ((Y16, N, 0), (Y32, N + 8, 1)):
+        rb.check(rb.lib().rb_k_gemm_bf16(_stream(), rb.dptr(X), K, rb.dptr(W), K, rb.dptr(b), rb.dptr(Y), ldy, M, N, K,
+                                         rb.RB_ACT_RELU, f32), "gemm")
+    assert torch.equal(Y32[:M, :N].to(torch.bfloat16), Y16)
+    assert bool((Y32[M] == -3.0).all()) and bool((Y32[:, N:] == -3.0).all())
+    for d_out in (N, N - 27):
+        at = (M - 1 - np.arange(M)) * (d_out + 3) + 1
+        at[M // 2] = -1  # a padding row
+        rows = _rows_dev(np.zeros(M), np.zeros(M), at)
+        out = torch.full((M * (d_out + 3) + 1,), -3.0, device=DEV)
+        rb.check(rb.lib().rb_k_gemm_bf16_rows(_stream(), rb.dptr(X), K, rb.dptr(W), K, rb.dptr(b), M, N, K,
+                                              rb.RB_ACT_RELU, rb.dptr(rows), d_out, rb.dptr(out)), "gemm rows")
+        got = out[1:].reshape(M, d_out + 3).flip(0)
+        want = Y32[:M, :d_out].clone()
+        want[M // 2] = -3.0
+        assert torch.equal(got[:, :d_out], want) and bool((got[:, d_out:] == -3.0).all()) and float(out[0]) == -3.0
