@@ -619,17 +619,19 @@ rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W
     // fewer tiles than that. A wave issues its loads, LDS reads and MFMAs one
     // after another, and a compute unit's loads enter at 64 bytes a clock, so a
     // launch of few rows takes as long as one tile's k-loop: the smallest tiles
-    // that still leave one (or two) to a compute unit. Cold weights, us:
-    //                     32 x 32  64 x 32  64 x 64  128 x 64  128 x 128
-    //   64 x 1024 x 1728      6.9      7.1      8.1
-    //   512 x 1024 x 1728     7.5      7.2      8.0                12.5
-    //   128 x 4096 x 8192      33       31       39
-    //   128 x 8192 x 8192      83       68       47        56
-    //   256 x 8192 x 8192     141      124       65        77
-    //   512 x 8192 x 4096                        58                  42
-    //   2816 x 1024 x 1728                       23                  14
-    // (64 x 64 tiles with 4 waves of 32 x 32 in one round, 2 of 64 x 32 in two:
-    // 47 against 47, 65 against 72)
+    // that still leave one to a compute unit, and 128 x 64 once 64 x 64 would be
+    // two. Back to back, us, with W from HBM (and on one W, from the caches):
+    //                     32 x 32      64 x 32      64 x 64      128 x 64     128 x 128
+    //   64 x 1024 x 1728   6.0 (6.2)    6.3 (6.4)    7.5 (6.9)    8.9 (8.9)  10.7 (10.6)
+    //   512 x 1024 x 1728  7.8 (7.0)    7.3 (6.8)    8.1 (7.7)    9.9 (9.0)  12.6 (11.1)
+    //   64 x 8192 x 8192                40 (33)      45 (29)      47 (33)      61 (39)
+    //   128 x 8192 x 8192  81 (68)      67 (63)      45 (36)      56 (41)      75 (44)
+    //   256 x 8192 x 8192                            70 (55)      57 (43)      76 (44)
+    //   512 x 3072 x 3008               27 (24)      20 (19)      21 (16)      30 (20)
+    //   1024 x 2048 x 2048                           16.2 (14.8)  12.5 (12.5)  14.8 (15.1)
+    //   2816 x 512 x 1024                                 (7.4)        (7.1)
+    // (64 x 64 tiles with two waves of 64 x 32 instead of four of 32 x 32: 15.1
+    // (14.2) for 1024 x 2048 x 2048, 63 (46) for 256 x 8192 x 8192)
     const int64_t rows64 = (M + 63) / 64, rows32 = (M + 31) / 32;
     if (rows32 * (N / 32) <= (int64_t)cus)
       RB_PICK(32, 32, 32, 32, 64, 64, 6, false);
@@ -638,7 +640,7 @@ rb_status gemm_bf16_impl(void* stream, const void* X, int32_t ldx, const void* W
     else if (rows64 * (N / 64) <= (int64_t)cus)
       RB_PICK(64, 64, 32, 32, 256, 64, 4, false);
     else if (rows64 * (N / 64) <= 2 * (int64_t)cus)
-      RB_PICK(64, 64, 64, 32, 128, 64, 4, false);
+      RB_PICK(128, 64, 64, 32, 256, 64, 4, false);
     else
       RB_PICK(128, 128, 64, 32, 512, 64, 4, false);
   }

@@ -1142,8 +1142,8 @@ def test_seqpool_bits_do_not_depend_on_the_slots_length(D):
 @pytest.mark.parametrize("M", [1, 31, 33, 65, 257, 600])
 @pytest.mark.parametrize("N,K", [(128, 64), (1024, 192), (4096, 448), (8192, 576)])
 def test_gemm_bf16_few_rows(M, N, K):
-    # every tile of launches of few rows (32 x 32, 64 x 32, 64 x 64 with 4 and 2
-    # waves, 128 x 128) at their row edges, with fewer k-steps than stages and
+    # every tile of launches of few rows (32 x 32, 64 x 32, 64 x 64, 128 x 64,
+    # 128 x 128) at their row edges, with fewer k-steps than stages and
     # with remainders of every length: fp64 within the rounding of the stored
     # bf16 (2^-9) plus fp32 sums, and the bits of a launch of many rows
     g = torch.Generator(device=DEV).manual_seed(M + N + K)
