@@ -45,7 +45,7 @@ def build(verbose: bool = False) -> str:
             if job.returncode:
                 raise subprocess.CalledProcessError(job.returncode, cmd)
         out_tmp = LIB + ".tmp"
-        cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", out_tmp, *objs, "-lpthread"]
+        cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-Wl,-z,defs", "-o", out_tmp, *objs, "-lpthread"]
         subprocess.run(cmd, check=True)
         os.replace(out_tmp, LIB)
     finally:

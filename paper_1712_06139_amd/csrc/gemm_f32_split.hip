@@ -2,6 +2,7 @@
 #include <cmath>
 
 #include "device.h"
+#include "launch.h"
 
 namespace {
 

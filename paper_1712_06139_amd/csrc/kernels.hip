@@ -30,6 +30,7 @@
 #include <mutex>
 
 #include "device.h"
+#include "launch.h"
 
 namespace {
 

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include "rb.h"
+#include "../../paper_1712_06139_amd/csrc/launch.h"
 
 #include <cstdio>
 #include <cstdlib>
@@ -88,9 +89,25 @@ rb_status rb_k_seqpool(void*, const rb_k_row*, int32_t, int32_t, int64_t, const 
 rb_status rb_k_split(void*, const rb_k_row*, int32_t, const float*, int32_t, int32_t, float*) {
   reached("rb_k_split");
 }
+rb_status rb_route_bags(void*, int32_t, const rb_k_batch*, int32_t, const rb_k_req*, int32_t, const int32_t*, int64_t,
+                        int32_t, int32_t, int32_t, rb_k_row*, int32_t, int64_t, int32_t*, int32_t, int32_t, int32_t*) {
+  reached("rb_route_bags");
+}
+rb_status rb_embbag_ends(void*, const rb_k_row*, int32_t, const int32_t*, const int32_t*, const int32_t*, int64_t,
+                         const void* const*, int32_t, int64_t, int32_t, const float*, int32_t, void*, int32_t, float,
+                         int32_t*) {
+  reached("rb_embbag_ends");
+}
 }
 
 void rb_scrub_caches(hipStream_t, const void*, size_t, unsigned*) { reached("rb_scrub_caches"); }
-void rb_fill_padding_rows(hipStream_t, rb_k_row*, int64_t) { reached("rb_fill_padding_rows"); }
+rb_status rb_gemm_f32_split(hipStream_t, const float*, int, const int64_t*, int, int64_t, int*, const void*, int,
+                            const float*, float*, int, int, int, int, int, const rb_k_row*, int, const rb_k_row*, int,
+                            float*) {
+  reached("rb_gemm_f32_split");
+}
+rb_status rb_token_rows(hipStream_t, const rb_k_row*, int, int, int64_t, int, int64_t*, int64_t, int*) {
+  reached("rb_token_rows");
+}
 rb_status rb_static_scratch_setup(int) { reached("rb_static_scratch_setup"); }
 void* rb_static_scratch(int) { reached("rb_static_scratch"); }

@@ -44,3 +44,18 @@ def test_host_runtime_under_address_and_undefined_behaviour_sanitizers(tmp_path)
 def test_host_runtime_loader_threads_under_thread_sanitizer(tmp_path):
     out = _build_and_run(tmp_path, ["-fsanitize=thread"], ["--threads"])
     print(out)
+
+
+def test_runtime_links_only_with_every_kernel_launcher(tmp_path):
+    # no reference of the runtime to a kernel launcher is weak (a missing one
+    # would then load as a call of address 0), and the stand-ins cover them all
+    syms = {}
+    for src in SRC[:2]:
+        obj = str(tmp_path / (os.path.basename(src) + ".o"))
+        subprocess.run(["g++", *FLAGS, "-c", src, "-o", obj], check=True, capture_output=True, timeout=300)
+        out = subprocess.run(["nm", "-C", obj], check=True, capture_output=True, text=True).stdout
+        syms[src] = [line[17:].split(" ", 1) for line in out.splitlines()]
+    names = {t: {n for k, n in syms[SRC[0]] if k == t and n.startswith("rb_")} for t in "Uwv"}
+    assert not names["w"] and not names["v"]
+    assert any(n.startswith("rb_gemm_f32_split(") for n in names["U"]) and "rb_route_bags" in names["U"]
+    assert names["U"] <= {n for k, n in syms[SRC[1]] if k == "T"}
