@@ -142,9 +142,9 @@ typedef struct {
    * batches). 1 runs every batch on its own. */
   int32_t window_batches;
   /* Value written into padding rows (and padding tokens) before the forward
-   * pass, where the padded batch is assembled (a first layer that reads the
-   * requests' rows in place takes padding rows as zeros). 0 in production;
-   * NaN shows that padding never reaches an output. */
+   * pass. 0 in production: the library may then leave padding out (a first
+   * layer that reads the requests' rows in place, packed sequences). NaN shows
+   * that padding never reaches an output. */
   float pad_value;
   /* 1: time every kernel launch with HIP events (rb_sched_kernel_stats);
    * 2: the same with cold caches: before each timed launch the scheduler
@@ -160,10 +160,10 @@ typedef struct {
    * sequences are packed into consecutive rows (no time padding) for the
    * token-wise layers, then each sequence is pooled from its own rows (the
    * sub-graph batching the paper's Batch/Unbatch operations allow, section on
-   * batching). Replays and the serving calls always do so. For rb_run_group
-   * and rb_run_group_static, whose callers name the packed rows, 1 does so and
-   * 0 pads every sequence to its queue's bucket. Outputs are identical either
-   * way. */
+   * batching). With 1 all calls do so. With 0 replays and the serving calls do so
+   * while pad_value is 0, and rb_run_group and rb_run_group_static, whose callers
+   * name the packed rows, pad every sequence to its queue's bucket, as the others
+   * do with another pad_value. Outputs are identical either way. */
   int32_t seq_pack;
   /* Device mode, rb_sim_run: 0 runs the trace as a backlogged device would
    * (every launch window holds window_batches consecutive dispatched batches,

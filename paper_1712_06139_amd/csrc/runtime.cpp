@@ -713,17 +713,21 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
   // sequence groups of an fp32 model: the real tokens take `tokens` consecutive
   // rows and the layers run on those alone (every layer is row-wise and the
   // pooling reads a sequence's own tokens). Descriptors that the caller built
-  // name those rows only with seq_pack; without it slot e owns rows
-  // [e bucket, (e + 1) bucket), padding tokens are not assembled and tiles of
-  // them alone are not computed (replayed, 8000 requests: 10.3 ms with that
-  // layout, 5.3 ms packed; the outputs' bits are the same)
-  const bool pack = m->kind == RB_MODEL_SEQPOOL && !bf16 && (s->opts.seq_pack || !fill_rows);
+  // name those rows only with seq_pack, and a pad value other than 0 without it
+  // asks for padding rows to be there; then slot e owns rows
+  // [e bucket, (e + 1) bucket), padding tokens are not assembled where the bucket
+  // is a multiple of 64 and tiles of them alone are not computed (replayed, 8000
+  // requests: 10.3 ms with that layout, 5.3 ms packed; the outputs' bits are the
+  // same)
+  const bool pack = m->kind == RB_MODEL_SEQPOOL && !bf16 && (s->opts.seq_pack || (!fill_rows && pad == 0.f));
   const bool seq_skip = m->kind == RB_MODEL_SEQPOOL && !pack && q->bucket % 64 == 0;
   const int64_t Ml = pack ? tokens : M;  // rows of the layers
   // fp32 models whose rows need no zero columns: the first layer reads the
   // requests' rows (packed tokens through a map of their arena offsets, kept
-  // where the assembled rows would be) and nothing is assembled
-  const bool gather = !bf16 && m->kind != RB_MODEL_RANKING && m->d_in == Kp0 && (pack || m->kind == RB_MODEL_MLP);
+  // where the assembled rows would be) and nothing is assembled; padding rows are
+  // read as zeros, so another pad value has them assembled
+  const bool gather = !bf16 && m->kind != RB_MODEL_RANKING && m->d_in == Kp0 &&
+                      (pack || (m->kind == RB_MODEL_MLP && pad == 0.f));
   const int64_t* src = nullptr;
   if (gather) {
     src = pack ? (const int64_t*)w->X : &w->rows->src;

@@ -101,6 +101,28 @@ def test_nan_padding_never_leaks(ctx, name):
     assert np.array_equal(out0, out1)
 
 
+@pytest.mark.parametrize("name", ["small_mlp", "ragged_seq"])
+def test_pad_value_puts_padding_into_the_layers(ctx, name):
+    # with the pad value 0 the first layer reads the requests' rows in place and
+    # sequences are packed: no padding exists. Another pad value assembles the
+    # padded batches, so that it can be seen not to reach an output
+    w = synth.workload(name)
+    t, a = trace_and_arenas(name, PREFIX[name])
+    assembled, packed = [], []
+    for pad in (0.0, float("nan"), 1.0):
+        dep = Deployment(w, ctx, device=True, window_batches=8, pad_value=pad, service_ns=service_table(w), profile=1)
+        try:
+            dt = dep.upload(t, a)
+            dep.replay(dt)
+            dep.sched.sync()
+            assembled.append(dep.sched.kernel_stats("assemble")[0])
+            packed.append(dep.sched.kernel_stats("token_rows")[0])
+        finally:
+            dep.destroy()
+    assert assembled[0] == 0 and assembled[1] > 0 and assembled[2] == assembled[1]
+    assert packed[1:] == [0, 0] and (packed[0] > 0) == (name == "ragged_seq")
+
+
 @pytest.mark.parametrize("name", ["small_mlp", "ranking", "large_mlp", "ragged_seq"])
 def test_outputs_independent_of_launch_window(ctx, name):
     n = min(PREFIX[name], 600)
