@@ -207,10 +207,11 @@ def test_fused_mlp_tail_bit_identical(ctx, name, window):
 def test_packed_tokens_match_padded(ctx, window, pad):
     # sub-graph batching of the token-wise layers (real tokens packed, no time
     # padding): same batches, outputs bit-identical to the padded path, so
-    # within the oracle's tolerance too
+    # within the oracle's tolerance too. A NaN pad value without seq_pack selects
+    # the padded path
     name = "ragged_seq"
     n = min(PREFIX[name], 1500)
-    w, t, a, qindex, log0, out0, out_off = run(ctx, name, n, window=window)
+    w, t, a, qindex, log0, out0, out_off = run(ctx, name, n, window=window, pad=float("nan"))
     _, _, _, _, log1, out1, _ = run(ctx, name, n, window=window, pad=pad, seq_pack=True)
     assert lib_batches(log0, qindex) == lib_batches(log1, qindex)
     assert np.isfinite(out1).all()

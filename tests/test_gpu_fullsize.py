@@ -81,9 +81,9 @@ def test_full_trace(ctx, name):
 
 def test_full_ragged_seq_packed_tokens_bit_identical(ctx):
     # the whole ragged-sequence trace with the token-wise layers on packed
-    # real tokens: the same batches, and every output bit-identical to the
-    # padded path (whose sampled outputs test_full_trace checks against the
-    # oracle)
+    # real tokens (whose sampled outputs test_full_trace checks against the
+    # oracle): the same batches, and every output bit-identical to the padded
+    # path, which a NaN pad value without seq_pack selects
     name = "ragged_seq"
     w = synth.workload(name)
     t = synth.trace(w)
@@ -91,7 +91,8 @@ def test_full_ragged_seq_packed_tokens_bit_identical(ctx):
     svc = service_table(w)
     logs, outs = [], []
     for pack in (False, True):
-        dep = Deployment(w, ctx, device=True, window_batches=WINDOW, service_ns=svc, seq_pack=pack)
+        dep = Deployment(w, ctx, device=True, window_batches=WINDOW, service_ns=svc, seq_pack=pack,
+                         pad_value=0.0 if pack else float("nan"))
         try:
             dt = dep.upload(t, a)
             log = dep.replay(dt)
