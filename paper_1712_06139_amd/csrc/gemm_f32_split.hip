@@ -60,7 +60,7 @@ __device__ float k_zeros[64];  // one k-step of a row of zeros
 // zeros 4.1e-7, 4.7e-7, 1.4e-7; nine of ten zeros 1.8e-7 and 0.6e-7 (the first
 // and the last).
 //
-// W comes split (rb_pack_f32_weights): per 32 rows and 16 k values the three
+// W comes split (rb_split_f32_weights): per 32 rows and 16 k values the three
 // parts in the order of a wave's fragment, so a fragment is one coalesced load
 // from L2 into registers, RBUF - 1 sub-steps of 16 k values ahead. X is split
 // once per workgroup and k-step (16 KS values) on its way from registers to one
@@ -325,7 +325,49 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, PIPE ? 2 : 4) void k_ge
   }
 }
 
+// W [N, K] times scale as three bf16 parts per element that sum to it exactly
+// (a finite element's first part is not rounded up to infinity, a non-finite one
+// is its own first part), [Np, Kp] zero padded: per 32 rows and 16 k values the
+// parts one after another, each in the order of a wave's 32 x 16 fragment. A
+// thread splits eight k values of a row, consecutive threads consecutive rows
+// (whole lines stored; 4096 x 4096 at load: 114 ms with the split on the host).
+__global__ __launch_bounds__(256) void k_split_weights(const float* __restrict__ W, int N, int K, int Np, int Kp,
+                                                       float scale, u32x4_t* __restrict__ Wp) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // unit i % 64 of 16 k values of 32 rows
+  if (i >= (int64_t)Np * Kp / 8) return;
+  const int64_t block = i >> 6;
+  const int u = (int)(i & 63), nsub = Kp / 16;
+  const int j = (int)(block / nsub) * 32 + (u & 31), k0 = (int)(block % nsub) * 16 + (u >> 5) * 8;
+  uint32_t part[3][8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    float r = j < N && k0 + k < K ? W[(int64_t)j * K + k0 + k] * scale : 0.f;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      uint32_t v = f2bf(r);
+      if ((v & 0x7fff) == 0x7f80 && isfinite(r)) --v;
+      part[p][k] = v;
+      r = (v & 0x7f80) == 0x7f80 ? 0.f : r - bf2f(v);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    const uint32_t* h = part[p];
+    Wp[block * 192 + p * 64 + u] =
+        (u32x4_t){h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+  }
+}
+
 }  // namespace
+
+// Runtime support (not part of the C ABI): split weights (above) from fp32 ones
+// in device memory.
+rb_status rb_split_f32_weights(hipStream_t s, const float* W, int N, int K, int Np, int Kp, float scale, void* Wp) {
+  if (N < 1 || K < 1 || Np < N || Kp < K || Np % 32 || Kp % 16 || !W || !Wp) return RB_EINVAL;
+  hipLaunchKernelGGL(k_split_weights, dim3((unsigned)(((int64_t)Np * Kp / 8 + 255) / 256)), dim3(256), 0, s, W, N, K, Np,
+                     Kp, scale, (u32x4_t*)Wp);
+  return launch_status();
+}
 
 // Runtime support (not part of the C ABI): one layer of an fp32 model on
 // weights split by the model loader (three bf16 parts per element, in fragment

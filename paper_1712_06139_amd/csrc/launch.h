@@ -14,6 +14,8 @@ rb_status rb_gemm_f32_split(hipStream_t s, const float* X, int ldx, const int64_
                             int64_t src_len, int* err, const void* Wp, int w_exp, const float* b, float* Y, int ldy,
                             int M, int N, int K, int act, const rb_k_row* skip_rows, int skip_T,
                             const rb_k_row* out_rows, int d_out, float* out);
+// gemm_f32_split.hip: split weights, W [N, K] times scale, [Np, Kp] zero padded
+rb_status rb_split_f32_weights(hipStream_t s, const float* W, int N, int K, int Np, int Kp, float scale, void* Wp);
 // kernels.hip: rb_k_route and rb_k_embbag, with the ends of every row's bags passed from one to the other
 extern "C" rb_status rb_route_bags(void* stream, int32_t kind, const rb_k_batch* batches, int32_t n_batches,
                                    const rb_k_req* reqs, int32_t n_reqs, const int32_t* lens, int64_t lens_len,

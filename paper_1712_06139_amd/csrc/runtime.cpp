@@ -302,6 +302,15 @@ bool copy_h2d(rb_model* m, void* dst, const void* src, size_t n) {
   return hip_ok(hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, m->upload)) && hip_ok(hipStreamSynchronize(m->upload));
 }
 
+// Device memory for the context's deleter thread to free.
+void release(rb_ctx* c, std::vector<void*> ptrs) {
+  {
+    std::lock_guard<std::mutex> lk(c->mu);
+    c->pending.push_back(DevFree{std::move(ptrs)});
+  }
+  c->cv.notify_all();
+}
+
 bool valid_hidden_act(int a) { return a == RB_ACT_NONE || a == RB_ACT_RELU; }
 bool valid_last_act(int a) { return a == RB_ACT_NONE || a == RB_ACT_RELU || a == RB_ACT_SIGMOID; }
 
@@ -321,39 +330,36 @@ rb_status upload_layer(rb_model* m, const rb_layer_desc& L, DevLayer& d, bool bf
     if ((st = dev_alloc(m, n * 2, &d.w)) != RB_OK) return st;
     if (!copy_h2d(m, d.w, h.data(), n * 2)) return RB_EDEVICE;
   } else {
-    // each element as three bf16 parts that sum to it exactly (its first part
-    // is not rounded up to infinity); per 32 rows and 16 k values the parts one
-    // after another, in the order of a wave's 32 x 16 fragment. The parts hold
-    // elements from 2^-110 on: if the smallest (but 0) is below, all are scaled
-    // by the power of two that takes it there, as far as the largest stays finite
-    // (a layer that spans more than 2^236 loses bits under 2^-134 of the scaled
-    // elements)
-    float lo = INFINITY, hi = 0.f;  // the smallest and the largest |element|, but 0 and non-finite ones
+    // split on the device. The parts hold elements from 2^-110 on: if the smallest
+    // (but 0) is below, all are scaled by the power of two that takes it there, as
+    // far as the largest stays finite (a layer that spans more than 2^236 loses
+    // bits under 2^-134 of the scaled elements)
+    uint32_t lo = 0xffffffffu, hi = 0;  // bits of the smallest |element| - 1 (0: the largest), of the largest finite one
     for (size_t i = 0; i < (size_t)d.N * d.K; ++i) {
-      const float v = std::fabs(L.w[i]);
-      if (v > 0.f) lo = std::min(lo, v);
-      if (std::isfinite(v)) hi = std::max(hi, v);
+      uint32_t u;
+      std::memcpy(&u, &L.w[i], 4);
+      u &= 0x7fffffffu;
+      lo = std::min(lo, u - 1);
+      hi = std::max(hi, u < 0x7f800000u ? u : 0u);
     }
-    d.w_exp = lo >= 0x1p-110f ? 0 : std::max(0, std::min(-110 - std::ilogb(lo), 126 - std::ilogb(hi)));
-    const float scale = std::ldexp(1.f, d.w_exp);
-    std::vector<uint16_t> h(n * 3, 0);
-    for (int j = 0; j < d.N; ++j)
-      for (int k = 0; k < d.K; ++k) {
-        uint16_t* e = &h[((size_t)(j / 32) * (d.Kp / 16) + k / 16) * 1536 + ((k / 8 % 2) * 32 + j % 32) * 8 + k % 8];
-        float r = L.w[(size_t)j * d.K + k] * scale;
-        for (int p = 0; p < 3; ++p) {
-          uint16_t v = host_f2bf(r);
-          if ((v & 0x7fff) == 0x7f80 && std::isfinite(r)) v = (uint16_t)(v - 1);
-          e[p * 512] = v;
-          if ((v & 0x7f80) == 0x7f80) break;
-          uint32_t u = (uint32_t)v << 16;
-          float f;
-          std::memcpy(&f, &u, 4);
-          r -= f;
-        }
-      }
+    ++lo;
+    if (lo > 0 && lo < 17u << 23) {  // 2^-110 has exponent bits 17
+      float flo, fhi;
+      std::memcpy(&flo, &lo, 4);
+      std::memcpy(&fhi, &hi, 4);
+      d.w_exp = std::max(0, std::min(-110 - std::ilogb(flo), 126 - std::ilogb(fhi)));
+    }
+    const size_t raw_bytes = (size_t)d.N * d.K * 4;
+    void* raw = nullptr;
     if ((st = dev_alloc(m, n * 6, &d.w)) != RB_OK) return st;
-    if (!copy_h2d(m, d.w, h.data(), n * 6)) return RB_EDEVICE;
+    if (!hip_ok(hipMalloc(&raw, raw_bytes))) return RB_ENOMEM;
+    st = copy_h2d(m, raw, L.w, raw_bytes) ? RB_OK : RB_EDEVICE;
+    if (st == RB_OK) {
+      st = rb_split_f32_weights(m->upload, (const float*)raw, d.N, d.K, d.Np, d.Kp, std::ldexp(1.f, d.w_exp), d.w);
+      if (!hip_ok(hipStreamSynchronize(m->upload)) && st == RB_OK) st = RB_EDEVICE;
+    }
+    release(m->ctx, {raw});  // a free here would wait for the scheduler's streams
+    if (st != RB_OK) return st;
   }
   std::vector<float> hb(d.Np, 0.f);
   std::memcpy(hb.data(), L.b, sizeof(float) * d.N);
@@ -378,15 +384,7 @@ void model_ref(rb_model* m) { m->refs.fetch_add(1, std::memory_order_relaxed); }
 void model_unref(rb_model* m) {
   if (m->refs.fetch_sub(1, std::memory_order_acq_rel) != 1) return;
   rb_ctx* c = m->ctx;
-  if (!m->allocs.empty()) {
-    DevFree f;
-    f.ptrs = std::move(m->allocs);
-    {
-      std::lock_guard<std::mutex> lk(c->mu);
-      c->pending.push_back(std::move(f));
-    }
-    c->cv.notify_all();
-  }
+  if (!m->allocs.empty()) release(c, std::move(m->allocs));
   delete m;
 }
 

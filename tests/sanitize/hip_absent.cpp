@@ -106,6 +106,9 @@ rb_status rb_gemm_f32_split(hipStream_t, const float*, int, const int64_t*, int,
                             float*) {
   reached("rb_gemm_f32_split");
 }
+rb_status rb_split_f32_weights(hipStream_t, const float*, int, int, int, int, float, void*) {
+  reached("rb_split_f32_weights");
+}
 rb_status rb_token_rows(hipStream_t, const rb_k_row*, int, int, int64_t, int, int64_t*, int64_t, int*) {
   reached("rb_token_rows");
 }
