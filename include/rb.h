@@ -200,7 +200,8 @@ rb_status rb_sched_destroy(rb_sched* s);
 rb_status rb_sync(rb_sched* s);
 /* Kernel timings of a profiling scheduler since its creation (after rb_sync),
  * for measuring the batched Run() of paper section 2.2.1: kernel names are
- * those of rb_k_* without the prefix ("embbag", ...). RB_EINVAL on NULL. */
+ * those of rb_k_* without the prefix ("embbag", ...), and "token_rows" (the
+ * rows of packed sequences). RB_EINVAL on NULL. */
 rb_status rb_sched_kernel_stats(rb_sched* s, const char* kernel, int64_t* launches, double* total_ms);
 /* The scheduler's HIP stream (hipStream_t) on the shared device (paper
  * section 2.2.1), for callers that order their own work after the

@@ -9,8 +9,8 @@ namespace {
 // fp32), K contiguous; fp32 accumulation with v_mfma_f32_16x16x32_bf16 or
 // v_mfma_f32_32x32x2f32.
 //
-// Workgroup tile BM x BN, k-step of RB bytes per row (64 or 128: 32 or 64
-// bf16, 16 or 32 fp32), NT/64 waves each owning a WM x WN sub-tile
+// Workgroup tile BM x BN, k-step of RB bytes per row (64 or 128: 16 or 32
+// fp32; bf16 outputs take 128, 64 bf16), NT/64 waves each owning a WM x WN sub-tile
 // ((WM/T) x (WN/T) accumulators; T = 16 bf16, 32 fp32). Operand tiles go straight from global
 // memory into a ring of S >= 2 LDS stages (global_load_lds: each wave load
 // instruction fills 1 KB of consecutive LDS rows; no register staging).
@@ -78,6 +78,7 @@ __device__ __forceinline__ void gemm_mfma(const TI* __restrict__ X, int ldx, con
   constexpr int TM = WM / T, TN = WN / T;
   constexpr bool PAIR = !F32 && !OUT_F32;  // column blocks stored in pairs
   static_assert(F32 || TN % 2 == 0, "column blocks are stored in pairs");
+  static_assert(!PAIR || CPR == 8, "the paired blocks' swizzle permutes eight chunks");
   typedef typename std::conditional<F32, floatx16_t, floatx4_t>::type acc_t;
   constexpr int SA = BM / RPI / NW, SB = BN / RPI / NW;  // load instructions per wave per stage
   static_assert(SA * NW * RPI == BM && SB * NW * RPI == BN, "loads cover the tile");
