@@ -715,7 +715,7 @@ rb_status run_chain(rb_sched* s, hipStream_t st_h, const rb_queue* q, int n_batc
   // asks for padding rows to be there; then slot e owns rows
   // [e bucket, (e + 1) bucket), padding tokens are not assembled where the bucket
   // is a multiple of 64 and tiles of them alone are not computed (replayed, 8000
-  // requests: 10.3 ms with that layout, 5.3 ms packed; the outputs' bits are the
+  // requests: 10.3 ms with that layout, 6.0 ms packed; the outputs' bits are the
   // same)
   const bool pack = m->kind == RB_MODEL_SEQPOOL && !bf16 && (s->opts.seq_pack || (!fill_rows && pad == 0.f));
   const bool seq_skip = m->kind == RB_MODEL_SEQPOOL && !pack && q->bucket % 64 == 0;
