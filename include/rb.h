@@ -94,6 +94,9 @@ typedef struct {
  * dtype RB_DT_BF16 stores weights and tables as bf16 (rounded to nearest even
  * from the given fp32), rounds every layer input to bf16 and accumulates in
  * fp32; the last layer's output stays fp32. RB_DT_F32 keeps fp32 throughout.
+ * (fp32 layers run on the bf16 matrix cores, every operand as three bf16 parts
+ * that sum to it, with no larger error than fp32 products summed one by one;
+ * their weights take 6 bytes each.)
  * RB_ACT_SIGMOID and RB_ACT_SOFTMAX are allowed only on the last layer (MLP
  * and ranking: sigmoid with fan_out 1) and on the head.
  * All host arrays are copied; the caller may free them when this returns.

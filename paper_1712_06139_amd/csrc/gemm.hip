@@ -27,10 +27,10 @@ namespace {
 // within a step is fixed with scheduling barriers.
 //
 // A fragment is 16 bytes of one row: lane l holds row l % T and chunk l / T of
-// the sub-step's. bf16: one 16x16x32 MFMA per accumulator and sub-step. The chip
-// runs these layers at its power limit, and with random operands in registers
-// it sustains 2080 TFLOP/s of 16x16x32 against 1740 to 1800 of 32x32x16 (zeros:
-// 2450 with either); the results have the same bits. 8192 x 1024 x 1728
+// the sub-step's. bf16: one 16x16x32 MFMA per accumulator and sub-step. It takes
+// less power: with random operands in registers the chip sustains 2080 TFLOP/s
+// of 16x16x32 against 1740 to 1800 of 32x32x16 (zeros: 2450 with either); the
+// results have the same bits. 8192 x 1024 x 1728
 // 28.4 -> 25.3 us, 32768 x 1024 x 1728 117 -> 96, 32768 x 512 x 1024 35 -> 32,
 // 4096 x 4096 x 8192 202 -> 189, 65536 x 8192 x 4096 3290 either way. fp32:
 // chunk c holds k = 4c .. 4c + 3, and MFMA t (t = 0..3) of the sub-step takes
